@@ -45,6 +45,7 @@ struct Job {
   int status;
   unsigned int done;              // 0 pending, 1 finished (written last)
   int wide;                       // server: queued on the wide ring
+  int linear;                     // input: 1 if the code may be built from its generators
 };
 
 // Job queue.  `submitted` and `shutdown` may live in host memory (server);
@@ -128,6 +129,15 @@ int pick_grid(unsigned int requested, unsigned int *grid);
 unsigned int spin_limit_from_env();
 void fill_job(Job *J, int n, int d, int ordering, uint32_t *words, uint64_t capacity, uint64_t *count,
               const gc_tuning *tuning);
+// Whether a job's code is linear and no tuning asks for the screens; its code
+// is then built from its generators.
+bool linear_job(const Job &J);
+// Builds such a single code on `stream` and waits for it: outputs into *J and
+// *built, kernel_ms (may be null) the device time.  `fixed`: a workspace of
+// fixed_bytes to use instead of the pool (may be null).  *built stays false
+// when the search does not fit the workspace or the prefix is not the code's
+// beginning: the screens then build the code.
+int run_linear(Job *J, hipStream_t stream, char *fixed, size_t fixed_bytes, float *kernel_ms, bool *built);
 // Validates a caller's job array and fills `J` (caller order) and `order`
 // (queue position -> caller index, longest jobs first).
 int prepare_batch(const gc_job *jobs, int njobs, Job *J, int *order);

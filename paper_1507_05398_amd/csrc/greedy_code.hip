@@ -59,6 +59,7 @@
 
 #include "gc_internal.h"
 #include "greedy_code.h"
+#include "linear.h"
 
 #define GC_VERSION_STRING "greedy_code 0.2.0 (gfx950)"
 
@@ -110,6 +111,8 @@ struct TeamWs {
   uint32_t *deep_word;       // kSMax
   uint32_t *deep_idx;        // kSMax
   uint32_t *deep_fail;       // kSMax / 32
+  LinResult *lin;            // linear codes: the generators
+  unsigned long long *lin_bits;  // kLinTeamWords: label bitmaps past LDS
 };
 
 constexpr size_t align256(size_t x) { return (x + 255) / 256 * 256; }
@@ -130,7 +133,14 @@ constexpr size_t kOffAdj = kOffDead + 2 * kDeadBytes;
 constexpr size_t kOffDword = kOffAdj + align256(kAdjWords * sizeof(unsigned long long));
 constexpr size_t kOffDidx = kOffDword + align256(kSMax * sizeof(uint32_t));
 constexpr size_t kOffDfail = kOffDidx + align256(kSMax * sizeof(uint32_t));
-constexpr size_t kTeamWsBytes = kOffDfail + align256(kSMax / 32 * sizeof(uint32_t));
+// Linear codes: label bitmaps of a team's search, 16 KiB in LDS and then
+// 384 KiB of the workspace (enough for d <= 10 up to n = 26; a search that
+// needs more leaves its code to the screens).
+constexpr int kLinLdsWords = 2048;
+constexpr unsigned int kLinTeamWords = 49152;
+constexpr size_t kOffLin = kOffDfail + align256(kSMax / 32 * sizeof(uint32_t));
+constexpr size_t kOffLinBits = kOffLin + align256(sizeof(LinResult));
+constexpr size_t kTeamWsBytes = kOffLinBits + kLinTeamWords * sizeof(unsigned long long);
 
 __host__ __device__ inline TeamWs team_ws(char *base) {
   TeamWs w;
@@ -142,6 +152,8 @@ __host__ __device__ inline TeamWs team_ws(char *base) {
   w.deep_word = reinterpret_cast<uint32_t *>(base + kOffDword);
   w.deep_idx = reinterpret_cast<uint32_t *>(base + kOffDidx);
   w.deep_fail = reinterpret_cast<uint32_t *>(base + kOffDfail);
+  w.lin = reinterpret_cast<LinResult *>(base + kOffLin);
+  w.lin_bits = reinterpret_cast<unsigned long long *>(base + kOffLinBits);
   return w;
 }
 
@@ -205,6 +217,7 @@ struct Lds {
   unsigned long long capacity, total, near_depth;
   unsigned long long p_start, m_start, classes;
   unsigned int target, deep_tile;
+  int linear;                          // may be built from its generators
   int mfma;                            // screens (other than self-orthogonal ones) on the matrix cores
   // window
   unsigned long long p0, m0, w, pe, lo;
@@ -224,6 +237,7 @@ struct Lds {
   union alignas(16) {
     TileLds t;
     ResolveLds r;
+    uint32_t lin[4][256];              // linear codes: byte tables of the words
   } u;
 };
 
@@ -1411,6 +1425,43 @@ __device__ void emit_ordering(Lds &L, const TeamWs &W) {
   }
 }
 
+// Generators of a linear job by one workgroup of its team.  Not inlined, with
+// LDS of its own: the screens' registers are not affected.
+__device__ __noinline__ void find_generators(int n, int d, int ord, unsigned long long capacity, LinResult *res,
+                                             unsigned long long *bits) {
+  __shared__ LinLds<kLinLdsWords> S;
+  const bool ok = lin_search(S, n, d, ord, 0, bits, kLinTeamWords);
+  if (threadIdx.x < 32) res->gen[threadIdx.x] = (int)threadIdx.x < S.dim ? S.gen[threadIdx.x] : 0u;
+  if (threadIdx.x == 0) {
+    const unsigned long long all = 1ull << S.dim;
+    res->ok = ok;
+    res->dim = S.dim;
+    res->status = all > capacity ? GC_ECAPACITY : GC_OK;
+    res->begin = 0;
+    res->end = all < capacity ? all : capacity;
+  }
+}
+
+// A linear code (whole lex or Gray walk) from its generators: team rank 0
+// finds them while the others wait, then the team writes the words.  False
+// (alike in every workgroup) when the search did not fit its workspace.
+__device__ __forceinline__ bool build_linear(Lds &L, const Params &P, const TeamWs &W) {
+  if (L.team_rank == 0) find_generators(L.n, L.d, L.ord, L.capacity, W.lin, W.lin_bits);
+  team_barrier(L, P, P.spin_limit);
+  if (L.abort) return true;
+  if (ld_relaxed(&W.lin->ok) == 0) return false;
+  const unsigned long long end = ld_relaxed(&W.lin->end);
+  lin_word_tables(L.u.lin, W.lin->gen, ld_relaxed(&W.lin->dim));
+  __syncthreads();
+  lin_emit(L.u.lin, L.code, 0, end, (unsigned long long)L.team_rank * kBlock + threadIdx.x,
+           (unsigned long long)L.team_size * kBlock);
+  if (L.team_rank == 0 && threadIdx.x == 0) {
+    W.ctl->m = end;
+    if (W.lin->status != 0) set_status(W.ctl, W.lin->status);
+  }
+  return true;
+}
+
 // ---------------------------------------------------------------------------
 // The persistent kernel: teams pull jobs until the queue is empty
 // ---------------------------------------------------------------------------
@@ -1454,7 +1505,9 @@ __device__ int claim_job(const Params &P, unsigned int team) {
 
 // Body of the persistent kernel: the team claims jobs until the queue is empty
 // (batch), the host shuts it down or it stays idle too long (server).
-template <bool SO>
+// kLinear: jobs may be linear (batch and server; a single linear code has
+// kernels of its own).
+template <bool SO, bool kLinear>
 __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
   const int tid = threadIdx.x;
   if (tid < 256) L.lut8[tid] = make_uint2(signed_bytes((uint32_t)tid & 15u), signed_bytes((uint32_t)tid >> 4));
@@ -1504,6 +1557,7 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
       const unsigned int dt = ld_sys(&J->deep_tile);
       L.deep_tile = dt ? dt : (unsigned int)kTile;
       L.mfma = ld_sys(&J->valu_screen) == 0;
+      L.linear = ld_sys(&J->linear);
       const int wclass = ld_sys(&J->wclass);
       L.walk.n = L.n;
       L.walk.ord = L.ord;
@@ -1550,7 +1604,7 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
     team_barrier(L, P, P.spin_limit);
 
     if (L.d <= 1 && !L.walk.so) emit_ordering(L, W);
-    else build_code<SO>(L, P, W);
+    else if (!kLinear || !L.linear || !build_linear(L, P, W)) build_code<SO>(L, P, W);
 
     __syncthreads();
     if (tid == 0) {
@@ -1612,24 +1666,24 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
 // launches, the batch launches and the server launches apart.
 __global__ void __launch_bounds__(kBlock) greedy_code_kernel(Params P) {
   __shared__ Lds L;
-  persistent_body<false>(L, P);
+  persistent_body<false, false>(L, P);
 }
 
 __global__ void __launch_bounds__(kBlock) greedy_batch_kernel(Params P) {
   __shared__ Lds L;
-  persistent_body<false>(L, P);
+  persistent_body<false, true>(L, P);
 }
 
 __global__ void __launch_bounds__(kBlock) greedy_server_kernel(Params P) {
   __shared__ Lds L;
-  persistent_body<false>(L, P);
+  persistent_body<false, true>(L, P);
 }
 
 // Self-orthogonal codes: the same body with the extra clash rule compiled in
 // (a kernel of its own, so the plain screen's registers are unaffected).
 __global__ void __launch_bounds__(kBlock) greedy_code_so_kernel(Params P) {
   __shared__ Lds L;
-  persistent_body<true>(L, P);
+  persistent_body<true, false>(L, P);
 }
 
 // Reset of the barrier block and the device queue before a launch (a kernel
@@ -1666,7 +1720,7 @@ __global__ void init_job_kernel(Bar *bar, DevQueue *dq, Job *dst, Job job) {
 }
 
 // Workspace of greedy_code_device_noalloc: barrier block, queue, one job and
-// one team workspace (about 154 KiB), held by every device the library runs
+// one team workspace (about 540 KiB), held by every device the library runs
 // on until the process ends.  Host code reaches it only through the address
 // hipGetSymbolAddress returns for the current device.
 constexpr size_t kScratchBytes =
@@ -1993,6 +2047,7 @@ int prepare_batch(const gc_job *jobs, int njobs, Job *J, int *order) {
     if (!g.d_words || ((uintptr_t)g.d_words & 15u) || g.capacity == 0)
       return fail(GC_EINVAL, "job %d: d_words must be a 16-byte aligned device array", i);
     fill_job(&J[i], g.n, g.d, g.ordering, g.d_words, g.capacity, g.d_count, nullptr);
+    J[i].linear = linear_job(J[i]);
   }
   // Teams claim jobs in queue order; the queue holds the jobs longest first
   // (by the exhaustive-scan work bound 2^n * capacity), so that the largest
@@ -2236,6 +2291,15 @@ int greedy_code_problem_device(const gc_problem *p, uint32_t *d_words, uint64_t 
   Job J;
   fill_job_problem(&J, *p, d_words, capacity, d_count, tuning);
   float ms = 0.f;
+  if (linear_job(J) && !(tuning && tuning->grid_blocks)) {
+    bool built = false;
+    rc = run_linear(&J, stream, nullptr, 0, stats ? &ms : nullptr, &built);
+    if (rc) return rc;
+    if (built) {
+      copy_stats(stats, J, ms);
+      return job_result(J, capacity);
+    }
+  }
   rc = run_batch(&J, 1, 1, tuning ? tuning->grid_blocks : 0, stream, &ms,
                  p->self_orthogonal ? LaunchKind::kSingleSO : LaunchKind::kSingle);
   if (rc) return rc;
@@ -2276,13 +2340,19 @@ int greedy_code_device_noalloc(int n, int d, int ordering, uint32_t *d_words, ui
   char *base = nullptr;
   rc = scratch_address(&base);
   if (rc) return rc;
+  Job J;
+  fill_job(&J, n, d, ordering, d_words, capacity, d_count, nullptr);
+  hipStream_t stream = (hipStream_t)hip_stream;
+  if (linear_job(J)) {
+    bool built = false;
+    rc = run_linear(&J, stream, base, kScratchBytes, nullptr, &built);
+    if (rc) return rc;
+    if (built) return job_result(J, capacity);
+  }
   unsigned int grid = 0;
   rc = pick_grid(0, &grid);
   if (rc) return rc;
-  Job J;
-  fill_job(&J, n, d, ordering, d_words, capacity, d_count, nullptr);
   const Params P = launch_params(base, lay, 1, 1);
-  hipStream_t stream = (hipStream_t)hip_stream;
   hipLaunchKernelGGL(init_job_kernel, dim3(4), dim3(256), 0, stream, P.bar, P.dq, P.jobs, J);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = launch_persistent(P, grid, stream, LaunchKind::kSingle);
@@ -2502,6 +2572,7 @@ int greedy_code_tune(int n, int d, int ordering, void *hip_stream, gc_tuning *be
       {~0ull, 0, 0, 0, 0},        {65536ull, 0, 0, 2, 0}, {65536ull, 0, 0, 1, 0},
       {16384ull, 0, 0, 2, 0},     {16384ull, 0, 0, 1, 0}, {4096ull, 0, 0, 2, 0},
   };
+  if (ordering == GC_LEX || ordering == GC_GRAY) cands.push_back({0, 0, 0, 0, 0});  // from its generators
   uint32_t *words = nullptr;
   HIP_TRY(hipMalloc((void **)&words, (size_t)cap * sizeof(uint32_t)));
   std::vector<uint32_t> ref, cur;
@@ -2511,7 +2582,9 @@ int greedy_code_tune(int n, int d, int ordering, void *hip_stream, gc_tuning *be
   auto run = [&](const gc_tuning &t, float *ms, std::vector<uint32_t> &out) -> int {
     Job J;
     fill_job(&J, n, d, ordering, words, cap, nullptr, &t);
-    int r = run_batch(&J, 1, 1, 0, st, ms, LaunchKind::kSingle);
+    bool built = false;
+    int r = linear_job(J) ? run_linear(&J, st, nullptr, 0, ms, &built) : GC_OK;
+    if (r == GC_OK && !built) r = run_batch(&J, 1, 1, 0, st, ms, LaunchKind::kSingle);
     if (r) return r;
     r = job_result(J, cap);
     if (r) return r;

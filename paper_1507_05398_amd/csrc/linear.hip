@@ -1,0 +1,357 @@
+// linear.hip -- single linear codes (lex, Gray, B-ordering, self-orthogonal
+// lex and Gray): the generator search by one workgroup, then the words by the
+// whole GPU.  Two ordinary launches (three for a long B-ordering list); the
+// mathematics is in linear.h.
+//
+// What bounds it: launch latency and the chain of n search levels (one wave
+// while the label bitmaps are short).  One call, without and with this path:
+// n = 15 d = 3 to host memory 600 and 78 us, n = 20 d = 4 3236 and 56 us,
+// n = 26 d = 3 (2^21 words) 520 ms and 66 us, n = 30 d = 10 128 ms and 382 us
+// (2^19 labels: the bitmaps leave LDS), a random basis at n = 23 d = 5 2774
+// and 96 us.
+#include <hip/hip_runtime.h>
+
+#include <stdint.h>
+#include <string.h>
+
+#include <algorithm>
+
+#include "gc_internal.h"
+#include "greedy_code.h"
+#include "linear.h"
+
+namespace gcimpl {
+
+int acquire_workspace(size_t bytes, char **ptr, int *slot);
+void release_workspace(int slot);
+
+namespace {
+
+// Label words in LDS (128 KiB): a search with more goes on in global memory
+// (lex, Gray) or is left to the screens (B-ordering).
+constexpr int kLinWords = 16384;
+// Global label bitmaps of a search: up to 16 MiB of the workspace pool.
+constexpr size_t kLinGlobalBytes = 16u << 20;
+// B-ordering: low-weight words listed per workgroup, and in all.
+constexpr unsigned int kSegWords = 4096;
+constexpr unsigned long long kMaxListed = 1ull << 21;
+constexpr int kScanBlock = 256;
+constexpr int kEmitBlock = 256;
+
+struct BinomTable {
+  uint32_t c[33][33];
+};
+constexpr BinomTable make_binom() {
+  BinomTable t{};
+  for (int a = 0; a <= 32; ++a)
+    for (int b = 0; b <= a; ++b) t.c[a][b] = b == 0 || b == a ? 1u : t.c[a - 1][b - 1] + t.c[a - 1][b];
+  return t;
+}
+__constant__ BinomTable kBinom = make_binom();
+
+struct LinArgs {
+  int n, d, ord, so;
+  unsigned long long start, stop, prefix, capacity;
+  uint32_t *code;
+  LinResult *res;
+  unsigned long long *gbits;
+  unsigned int gwords;
+  unsigned int segs;      // B-ordering: segments of the word list
+  unsigned int listed;    // words in it
+  uint32_t *list;         // segs x kSegWords: positions of low-weight words, by top position bit
+  uint32_t *offs;         // segs x 33: where each top bit's run starts in its segment
+  uint32_t basis[32];     // B-ordering: b_1 .. b_n
+  uint32_t inv[32];       // position of the unit vector 2^i
+};
+
+struct ScanLds {
+  uint32_t inv[4][256];
+  uint32_t hist[33];
+};
+
+// Segment `seg` of the list of all words z with 0 < wt(z) < d: their
+// positions, sorted by top position bit (kept as a run, the bit itself
+// cleared).  Whole workgroup of kThreads; a thread takes consecutive words in
+// the order weight, value (the next word of a weight by the usual bit trick).
+template <int kThreads>
+__device__ __forceinline__ void list_segment(const LinArgs &P, ScanLds &S, unsigned int seg) {
+  const int tid = threadIdx.x;
+  constexpr int kPer = kSegWords / kThreads;
+  for (int i = tid; i < 4 * 256; i += kThreads) {
+    uint32_t x = 0;
+    for (int j = 0; j < 8; ++j)
+      if ((i >> j) & 1) x ^= P.inv[8 * (i >> 8) + j];
+    S.inv[i >> 8][i & 255] = x;
+  }
+  if (tid < 33) S.hist[tid] = 0;
+  __syncthreads();
+  unsigned int rank = seg * kSegWords + (unsigned int)tid * kPer;
+  uint32_t p[kPer], slot[kPer];
+  unsigned int have = rank < P.listed ? (P.listed - rank < kPer ? P.listed - rank : kPer) : 0;
+  int s = 1;
+  unsigned long long z = 0;
+  if (have) {
+    while (rank >= kBinom.c[P.n][s]) rank -= kBinom.c[P.n][s++];
+    int left = s;
+    for (int b = P.n - 1; b >= 0 && left > 0; --b) {
+      const uint32_t c = kBinom.c[b][left];
+      if (rank >= c) {
+        z |= 1ull << b;
+        rank -= c;
+        --left;
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    if (i < (int)have) {
+      p[i] = S.inv[0][z & 255] ^ S.inv[1][(z >> 8) & 255] ^ S.inv[2][(z >> 16) & 255] ^ S.inv[3][(z >> 24) & 255];
+      slot[i] = atomicAdd(&S.hist[31 - __builtin_clz(p[i])], 1u);
+      const unsigned long long low = z & (~z + 1), up = z + low;
+      z = up | (((z ^ up) >> 2) >> __builtin_ctzll(low));
+      if (z >> P.n) z = (1ull << ++s) - 1;  // the next weight's first word
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    uint32_t acc = 0;
+    for (int b = 0; b < 33; ++b) {
+      const uint32_t c = S.hist[b];
+      S.hist[b] = acc;
+      P.offs[seg * 33 + b] = acc;
+      acc += c;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    if (i < (int)have) {
+      const int b = 31 - __builtin_clz(p[i]);
+      P.list[seg * kSegWords + S.hist[b] + slot[i]] = p[i] ^ (1u << b);
+    }
+  }
+  __syncthreads();
+}
+
+__global__ void __launch_bounds__(kScanBlock) lin_list_kernel(LinArgs P) {
+  __shared__ ScanLds S;
+  list_segment<kScanBlock>(P, S, blockIdx.x);
+}
+
+// B-ordering: V_k is no coordinate subspace, so the low-weight words of
+// F_2^n are listed once by top position bit and each marks its label at that
+// bit's level (byte tables give the label of a position).
+__device__ __forceinline__ bool border_search(LinLds<kLinWords> &L, ScanLds &S, uint32_t (*lam)[256], const LinArgs &P) {
+  const int tid = threadIdx.x, n = P.n;
+  if (P.segs == 1) list_segment<kBlock>(P, S, 0);
+  if (tid < 32) L.img[tid] = P.basis[tid];
+  for (int i = tid; i < 4 * 256; i += kBlock) lam[i >> 8][i & 255] = 0;
+  if (tid < 2) L.best[tid] = ~0u;
+  int r = 0, dim = 0, k = 0;
+  uint32_t *bits32 = reinterpret_cast<uint32_t *>(L.bits);
+  for (; k < n; ++k) {
+    const unsigned int nw = r < 6 ? 1u : 1u << (r - 6);
+    if (nw > (unsigned int)kLinWords) break;
+    for (unsigned int w = tid; w < nw; w += kBlock) L.bits[w] = 0;
+    __syncthreads();
+    for (unsigned int seg = tid >> 6; seg < P.segs; seg += kBlock / 64) {
+      const uint32_t e = P.offs[seg * 33 + k + 1];
+      for (uint32_t i = P.offs[seg * 33 + k] + (tid & 63); i < e; i += 64) {
+        const uint32_t p = P.list[seg * kSegWords + i];
+        const uint32_t l = lam[0][p & 255] ^ lam[1][(p >> 8) & 255] ^ lam[2][(p >> 16) & 255] ^ lam[3][p >> 24];
+        atomicOr(&bits32[l >> 5], 1u << (l & 31));
+      }
+    }
+    __syncthreads();
+    const uint32_t m = lin_min_label<kBlock>(nw, &L.best[k & 1], [&](unsigned int w) {
+      return r < 6 ? ~L.bits[w] & ((1ull << (1 << r)) - 1) : ~L.bits[w];
+    });
+    const uint32_t h = m == ~0u ? 1u << r : m;
+    if (tid == 0) L.best[(k + 1) & 1] = ~0u;
+    lin_record(L, m, k, r, dim);
+    if (tid < 256 && ((tid >> (k & 7)) & 1)) lam[k >> 3][tid] = lam[k >> 3][tid ^ (1 << (k & 7))] ^ h;
+    if (m == ~0u) ++r;
+    else ++dim;
+  }
+  __syncthreads();
+  if (tid == 0) L.dim = dim;
+  lin_generators(L, dim);
+  __syncthreads();
+  return k >= n;
+}
+
+// One workgroup: the generators, the range of code words to write, and (a
+// resumed construction) whether the given prefix is the code's beginning.
+template <bool kBorder>
+__global__ void __launch_bounds__(kBlock) lin_find_kernel(LinArgs P) {
+  __shared__ LinLds<kLinWords> L;
+  __shared__ uint32_t tab[4][256];
+  __shared__ unsigned long long begin_s;
+  __shared__ int ok_s;
+  const int tid = threadIdx.x;
+  bool ok;
+  if constexpr (kBorder) {
+    __shared__ ScanLds S;
+    ok = border_search(L, S, tab, P);
+  } else {
+    ok = lin_search(L, P.n, P.d, P.ord, P.so, P.gbits, P.gwords);
+  }
+  if (tid == 0) {
+    begin_s = ok ? lin_count_below(L, P.start) : 0;
+    ok_s = ok && begin_s == P.prefix;
+  }
+  __syncthreads();
+  if (ok_s && P.prefix) {
+    lin_word_tables(tab, L.gen, L.dim);
+    __syncthreads();
+    bool same = true;
+    for (unsigned long long i = tid; i < P.prefix; i += kBlock) same &= P.code[i] == lin_word(tab, i);
+    if (!__syncthreads_and(same)) ok_s = 0;
+    __syncthreads();
+  }
+  if (tid < 32) P.res->gen[tid] = tid < L.dim ? L.gen[tid] : 0u;
+  if (tid == 0) {
+    const unsigned long long all = ok_s ? lin_count_below(L, P.stop) : 0;
+    P.res->ok = ok_s;
+    P.res->dim = L.dim;
+    P.res->status = all > P.capacity ? GC_ECAPACITY : GC_OK;
+    P.res->begin = begin_s;
+    P.res->end = all < P.capacity ? all : P.capacity;
+  }
+}
+
+__global__ void __launch_bounds__(kEmitBlock) lin_emit_kernel(const LinResult *res, uint32_t *code,
+                                                              unsigned long long *count) {
+  __shared__ __align__(16) uint32_t tab[4][256];
+  if (!res->ok) return;
+  lin_word_tables(tab, res->gen, res->dim);
+  __syncthreads();
+  lin_emit(tab, code, res->begin, res->end, (unsigned long long)blockIdx.x * kEmitBlock + threadIdx.x,
+           (unsigned long long)gridDim.x * kEmitBlock);
+  if (blockIdx.x == 0 && threadIdx.x == 0 && count) *count = res->end;
+}
+
+// Positions of the unit vectors: the inverse of the basis by elimination.
+void invert_basis(const uint32_t *basis, int n, uint32_t *inv) {
+  uint32_t v[32], tag[32];
+  for (int j = 0; j < n; ++j) {
+    v[j] = basis[j];
+    tag[j] = 1u << j;
+  }
+  for (int b = 0; b < n; ++b) {
+    int at = b;
+    while (!((v[at] >> b) & 1)) ++at;  // the basis is independent (checked by the caller)
+    std::swap(v[at], v[b]);
+    std::swap(tag[at], tag[b]);
+    for (int j = 0; j < n; ++j)
+      if (j != b && ((v[j] >> b) & 1)) {
+        v[j] ^= v[b];
+        tag[j] ^= tag[b];
+      }
+  }
+  for (int b = 0; b < n; ++b) inv[b] = tag[b];
+}
+
+size_t up256(size_t x) { return (x + 255) / 256 * 256; }
+
+}  // namespace
+
+bool linear_job(const Job &J) {
+  return (J.ord == GC_LEX || J.ord == GC_GRAY || J.ord == GC_BORDER) && J.wclass == 0 && (J.d >= 2 || J.so) &&
+         J.near_depth == 0 && J.target == 0 && J.mode == 0 && J.deep_tile == 0 && J.valu_screen == 0;
+}
+
+int run_linear(Job *J, hipStream_t stream, char *fixed, size_t fixed_bytes, float *kernel_ms, bool *built) {
+  *built = false;
+  const int K = J->n - J->so;
+  LinArgs P;
+  memset(&P, 0, sizeof(P));
+  P.n = J->n;
+  P.d = J->d;
+  P.ord = J->ord;
+  P.so = J->so;
+  P.start = J->p_start;
+  P.stop = J->p_stop ? J->p_stop : 1ull << K;
+  P.prefix = J->m_start;
+  P.capacity = J->capacity;
+  P.code = J->code;
+  size_t bytes = up256(sizeof(LinResult));
+  size_t off_offs = 0, off_list = 0, off_bits = bytes;
+  const int dmax = std::min(J->d - 1, J->n);
+  if (J->ord == GC_BORDER) {
+    unsigned long long listed = 0;
+    for (int s = 1; s <= dmax; ++s) listed += make_binom().c[J->n][s];
+    if (listed > kMaxListed) return GC_OK;  // the screens build it
+    P.listed = (unsigned int)listed;
+    P.segs = (P.listed + kSegWords - 1) / kSegWords;
+    off_offs = bytes;
+    off_list = off_offs + up256(sizeof(uint32_t) * 33 * P.segs);
+    bytes = off_list + sizeof(uint32_t) * kSegWords * P.segs;
+    memcpy(P.basis, J->basis, sizeof(P.basis));
+    invert_basis(J->basis, J->n, P.inv);
+  } else {
+    // Global bitmaps for the labels that can occur: once 2^r exceeds the
+    // number of words of weight <= d - 2, some label is always free.
+    unsigned long long low = 1;
+    for (int s = 1; s <= std::min(J->d - 2, J->n - 1); ++s) low += make_binom().c[J->n - 1][s];
+    unsigned long long words = 2;
+    while (words * 32 < low) words *= 2;
+    const unsigned long long need = words * ((unsigned int)(J->d > 1 ? J->d - 1 : 0) | 1u);
+    if (need > (unsigned long long)kLinWords)
+      bytes += (size_t)std::min<unsigned long long>(need * 8, fixed ? fixed_bytes - bytes : kLinGlobalBytes);
+  }
+  char *ws = fixed;
+  int slot = -1;
+  if (!fixed) {
+    const int rc = acquire_workspace(bytes, &ws, &slot);
+    if (rc) return rc;
+  }
+  P.res = reinterpret_cast<LinResult *>(ws);
+  P.offs = reinterpret_cast<uint32_t *>(ws + off_offs);
+  P.list = reinterpret_cast<uint32_t *>(ws + off_list);
+  P.gbits = reinterpret_cast<unsigned long long *>(ws + off_bits);
+  P.gwords = (unsigned int)((bytes - off_bits) / 8);
+  // Words of the code, at most: four a thread and step, up to four
+  // workgroups per compute unit.
+  const unsigned long long most = std::min<unsigned long long>(J->capacity, 1ull << K);
+  const unsigned int grid = (unsigned int)std::min<unsigned long long>(1024, most / (4 * kEmitBlock) + 1);
+  hipEvent_t ev0 = nullptr, ev1 = nullptr;
+  hipError_t e = hipSuccess;
+  if (kernel_ms) {
+    e = hipEventCreate(&ev0);
+    if (e == hipSuccess) e = hipEventCreate(&ev1);
+    if (e == hipSuccess) e = hipEventRecord(ev0, stream);
+  }
+  if (e == hipSuccess && P.segs > 1) {
+    hipLaunchKernelGGL(lin_list_kernel, dim3(P.segs), dim3(kScanBlock), 0, stream, P);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) {
+    if (J->ord == GC_BORDER) hipLaunchKernelGGL(lin_find_kernel<true>, dim3(1), dim3(kBlock), 0, stream, P);
+    else hipLaunchKernelGGL(lin_find_kernel<false>, dim3(1), dim3(kBlock), 0, stream, P);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(lin_emit_kernel, dim3(grid), dim3(kEmitBlock), 0, stream, P.res, J->code, J->count);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess && kernel_ms) e = hipEventRecord(ev1, stream);
+  LinResult res;
+  memset(&res, 0, sizeof(res));
+  if (e == hipSuccess) e = hipMemcpyAsync(&res, P.res, sizeof(res), hipMemcpyDeviceToHost, stream);
+  const hipError_t es = hipStreamSynchronize(stream);
+  if (e == hipSuccess) e = es;
+  if (e == hipSuccess && kernel_ms) e = hipEventElapsedTime(kernel_ms, ev0, ev1);
+  if (slot >= 0 && es == hipSuccess) release_workspace(slot);
+  if (ev0) (void)hipEventDestroy(ev0);
+  if (ev1) (void)hipEventDestroy(ev1);
+  if (e != hipSuccess) return fail(GC_EDEVICE, "linear code kernels failed: %s", hipGetErrorString(e));
+  if (!res.ok) return GC_OK;
+  J->out_count = res.end;
+  J->status = res.status;
+  J->done = 1;
+  *built = true;
+  return GC_OK;
+}
+
+}  // namespace gcimpl

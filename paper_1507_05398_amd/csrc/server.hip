@@ -242,6 +242,7 @@ int pump(gc_server *s) {
       J->deep_tile = tu.deep_tile;
       J->valu_screen = tu.valu_screen;
     }
+    J->linear = linear_job(*J);
     s->slot_ticket[t.slot] = id;
     s->inflight.insert(id);
     ++s->published;
