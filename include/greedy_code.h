@@ -65,7 +65,8 @@ enum { GC_JOB_WAITING = 0,   /* submitted, waiting for device memory */
  * distance checks (candidate x codeword pairs) by the kernel phase that ran
  * them; they measure the device's total work, which includes speculation.
  * A linear code built from its generators (see gc_tuning) runs no windows
- * and no checks: only count and kernel_ms are set. */
+ * and no checks: only count and kernel_ms are set.  A code built by cover
+ * marks sets resolve_rounds (its rounds) besides. */
 typedef struct gc_stats {
     uint64_t count;           /* |C| */
     uint64_t windows;         /* candidate windows processed */
@@ -83,8 +84,10 @@ typedef struct gc_stats {
 /* Tuning knobs (optional input; zero fields take the built-in defaults).
  * The greedy codes of GC_LEX, GC_GRAY and GC_BORDER walks (self-orthogonal
  * ones included, a weight not) are linear; with every field zero they are
- * built from their generators.  Any field set asks for the windowed screens,
- * which build the same code. */
+ * built from their generators.  GC_GRLEX and GC_GREVLEX codes (a weight too,
+ * not self-orthogonal) of d = 2, 3 or 4 and n <= 24 are built by marking the
+ * ball of each accepted word in a bitmap of the space.  Any field set asks
+ * for the windowed screens, which build the same code. */
 typedef struct gc_tuning {
     uint64_t near_depth;    /* newest code words screened before the in-window
                                resolve; 0 = default, UINT64_MAX = whole code */
@@ -122,7 +125,7 @@ int greedy_code(int n, int d, int ordering, uint32_t *out_words, uint64_t *out_c
  * `capacity` uint32, caller-owned, e.g. a torch tensor's data_ptr), the count
  * to *d_count (one device uint64), both written on `hip_stream` (a
  * hipStream_t, NULL = null stream).  The call uses a device workspace of
- * at most 16 MiB (about 0.6 MiB, or for linear codes what their
+ * at most 16 MiB (about 3.6 MiB, or for linear codes what their
  * generator search needs) from a pool the library keeps per device (allocated with
  * hipMalloc the first time a call needs one, reused by later calls, held
  * until the process ends; concurrent calls get distinct workspaces).
@@ -228,7 +231,7 @@ int greedy_code_cw64(int n, int w, int d, uint64_t *d_words, uint64_t capacity, 
  * allocate device memory (tight serving loops, harnesses that forbid
  * hipMalloc).  Same arguments, result and errors as greedy_code_device, but
  * the call allocates nothing: its device workspace (barrier block, queue, one
- * job and one team workspace, about 540 KiB) is a fixed array that the
+ * job and one team workspace, about 3.6 MiB) is a fixed array that the
  * library holds on every device it runs on until the process ends, and the
  * job descriptor reaches the device as a kernel argument.  A launch needs a
  * fixed workspace size, checked against the array's (GC_EINVAL if it were

@@ -1,0 +1,45 @@
+// cover.h -- storage of the cover builder (cover_build.h): graded codes of
+// distance at most 4 from a bitmap of the whole space.
+#pragma once
+
+#include <stdint.h>
+
+namespace gcimpl {
+
+constexpr int kCovTeam = 32;             // workgroups (slices of the space), at most
+constexpr int kCovWords = 8192;          // 64-bit words of a slice, at most
+constexpr int kCovMaxN = 24;             // 2^24 bits: 32 slices of 8192 words
+constexpr int kCovMaxD = 4;
+constexpr unsigned int kCovSeg = 4096;   // words a slice accepts in one round, at most
+constexpr unsigned int kCovOwn = 512;
+constexpr int kCovShared = 12;           // words a wave tests together with 16 lanes each, at most
+constexpr unsigned int kCovMaxRounds = 1u << 19;
+constexpr int kCovDiffs = 384;           // word-index differences of weight <= 3 in 13 bits: 378
+
+struct CoverLds {
+  unsigned long long dead[kCovWords + 1];  // the slice: 1 = accepted, rejected or no candidate; then a word of ones
+  unsigned long long acc[kCovWords];     // accepted in the current level
+  uint16_t queue[kCovWords];             // words with undecided candidates of the level
+  uint16_t diff[kCovDiffs];              // word-index differences, by weight
+  unsigned int cum[kCovMaxD + 1];        // differences of weight below j
+  uint8_t other[kCovTeam];               // differences of slice numbers, by weight
+  unsigned long long level[64];          // [32 + j]: the bits of a word whose index has weight j
+  unsigned long long ball[kCovMaxD][64]; // ball[r][b]: bit indices within distance r of b
+  unsigned int cnt[kCovTeam];            // per slice: words it accepted in the last round
+  unsigned int total[kCovTeam];          // per slice: words it accepted in the level
+  uint32_t own[kCovOwn];                 // the first words this slice accepted in the round
+  unsigned int wsum[16];
+  unsigned int qn, segn, seg_ok, left, accn, open;
+  unsigned int epoch;                    // workgroups that have passed the team's barriers
+};
+
+// Global memory of a cover team: every exchange is within one XCD (one L2).
+struct CoverWs {
+  unsigned long long active[(1u << (kCovMaxN - 6)) + 32];  // undecided candidates of the level; then zeros
+  uint32_t seg[2][kCovTeam][kCovSeg];                    // words accepted in a round, by slice
+  unsigned long long slot[2][kCovTeam];                  // what a slice reports at a barrier
+  unsigned int arrived;                                  // barrier: arrivals so far
+  unsigned int pad[63];
+};
+
+}  // namespace gcimpl

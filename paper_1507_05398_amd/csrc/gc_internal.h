@@ -46,6 +46,7 @@ struct Job {
   unsigned int done;              // 0 pending, 1 finished (written last)
   int wide;                       // server: queued on the wide ring
   int linear;                     // input: 1 if the code may be built from its generators
+  int cover;                      // input: 1 if it may be built by cover marks
 };
 
 // Job queue.  `submitted` and `shutdown` may live in host memory (server);
@@ -132,7 +133,9 @@ void fill_job(Job *J, int n, int d, int ordering, uint32_t *words, uint64_t capa
 // Whether a job's code is linear and no tuning asks for the screens; its code
 // is then built from its generators.
 bool linear_job(const Job &J);
-// Builds such a single code on `stream` and waits for it: outputs into *J and
+// Whether a job's code may be built by cover marks (small distance, graded).
+bool cover_job(const Job &J);
+// Builds a linear single code on `stream` and waits for it: outputs into *J and
 // *built, kernel_ms (may be null) the device time.  `fixed`: a workspace of
 // fixed_bytes to use instead of the pool (may be null).  *built stays false
 // when the search does not fit the workspace or the prefix is not the code's

@@ -57,6 +57,7 @@
 #include <string>
 #include <vector>
 
+#include "cover.h"
 #include "gc_internal.h"
 #include "greedy_code.h"
 #include "linear.h"
@@ -113,6 +114,7 @@ struct TeamWs {
   uint32_t *deep_fail;       // kSMax / 32
   LinResult *lin;            // linear codes: the generators
   unsigned long long *lin_bits;  // kLinTeamWords: label bitmaps past LDS
+  CoverWs *cover;            // graded codes of small distance
 };
 
 constexpr size_t align256(size_t x) { return (x + 255) / 256 * 256; }
@@ -140,7 +142,8 @@ constexpr int kLinLdsWords = 2048;
 constexpr unsigned int kLinTeamWords = 49152;
 constexpr size_t kOffLin = kOffDfail + align256(kSMax / 32 * sizeof(uint32_t));
 constexpr size_t kOffLinBits = kOffLin + align256(sizeof(LinResult));
-constexpr size_t kTeamWsBytes = kOffLinBits + kLinTeamWords * sizeof(unsigned long long);
+constexpr size_t kOffCover = kOffLinBits + align256(kLinTeamWords * sizeof(unsigned long long));
+constexpr size_t kTeamWsBytes = kOffCover + align256(sizeof(CoverWs));
 
 __host__ __device__ inline TeamWs team_ws(char *base) {
   TeamWs w;
@@ -154,6 +157,7 @@ __host__ __device__ inline TeamWs team_ws(char *base) {
   w.deep_fail = reinterpret_cast<uint32_t *>(base + kOffDfail);
   w.lin = reinterpret_cast<LinResult *>(base + kOffLin);
   w.lin_bits = reinterpret_cast<unsigned long long *>(base + kOffLinBits);
+  w.cover = reinterpret_cast<CoverWs *>(base + kOffCover);
   return w;
 }
 
@@ -205,9 +209,6 @@ struct ResolveLds {
 
 struct Lds {
   uint2 lut8[256];                     // byte -> its 8 bits as signed bytes (matrix screens)
-  uint32_t s1w[kSMax];                 // window survivors, in position order
-  uint32_t s1off[kSMax];               // their offsets from the window start
-  uint8_t st[kSMax];                   // deep status of each survivor (resolve only)
   Tables tab;
   Walk walk;
   // job
@@ -218,6 +219,7 @@ struct Lds {
   unsigned long long p_start, m_start, classes;
   unsigned int target, deep_tile;
   int linear;                          // may be built from its generators
+  int by_cover;                        // may be built by cover marks
   int mfma;                            // screens (other than self-orthogonal ones) on the matrix cores
   // window
   unsigned long long p0, m0, w, pe, lo;
@@ -231,15 +233,29 @@ struct Lds {
   int status, action, abort;
   // team
   unsigned int xcd, xcd_members, team, team_rank, team_size, team_xcds;
+  unsigned int sub_size, sub_rank;     // the team's workgroups on one XCD: their number, this one's (~0: elsewhere)
   unsigned int tgen;                   // team barriers passed (generation of the team's barrier)
   unsigned long long cnt_near, cnt_deep, cnt_pairs;   // this workgroup's executed checks
   unsigned int wsum[kWaves];
   union alignas(16) {
-    TileLds t;
-    ResolveLds r;
-    uint32_t lin[4][256];              // linear codes: byte tables of the words
-  } u;
+    struct {                           // the windowed screens
+      uint32_t s1w[kSMax];             // window survivors, in position order
+      uint32_t s1off[kSMax];           // their offsets from the window start
+      uint8_t st[kSMax];               // deep status of each survivor (resolve only)
+      union alignas(16) {
+        TileLds t;
+        ResolveLds r;
+      } u;
+    };
+    LinLds<kLinLdsWords> gens;         // linear codes: the search
+    uint32_t lin[4][256];              // and then the byte tables of the words
+    CoverLds cover;
+  };
 };
+
+// The LDS of every persistent kernel, one object: functions that are not
+// inlined reach it directly (not through generic pointers).
+__shared__ Lds g_lds;
 
 // ---------------------------------------------------------------------------
 // Small device helpers
@@ -346,7 +362,8 @@ __device__ __forceinline__ void team_join(Lds &L, const Params &P) {
     Bar *B = P.bar;
     const unsigned int x = xcc_id();
     const unsigned int t = team_of(P, x);
-    __hip_atomic_fetch_add(&B->xcd[x][2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned int xcd_rank =
+        __hip_atomic_fetch_add(&B->xcd[x][2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const unsigned int rank =
         __hip_atomic_fetch_add(&B->team[t][2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_fetch_add(&B->join_count, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -359,9 +376,20 @@ __device__ __forceinline__ void team_join(Lds &L, const Params &P) {
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    unsigned int nx = 0;
+    // The team's XCDs, and the one with the most members (the lowest of
+    // several), where jobs that want one L2 are built.
+    unsigned int nx = 0, sub = 0, sub_size = 0;
     for (int i = 0; i < kMaxXcd; ++i)
-      if (team_of(P, (unsigned int)i) == t && ld_relaxed(&B->xcd[i][2]) > 0) ++nx;
+      if (team_of(P, (unsigned int)i) == t) {
+        const unsigned int members = ld_relaxed(&B->xcd[i][2]);
+        nx += members > 0;
+        if (members > sub_size) {
+          sub = (unsigned int)i;
+          sub_size = members;
+        }
+      }
+    L.sub_size = sub_size;
+    L.sub_rank = x == sub ? xcd_rank : ~0u;
     L.xcd = x;
     L.xcd_members = ld_relaxed(&B->xcd[x][2]);
     L.team = t;
@@ -1425,11 +1453,11 @@ __device__ void emit_ordering(Lds &L, const TeamWs &W) {
   }
 }
 
-// Generators of a linear job by one workgroup of its team.  Not inlined, with
-// LDS of its own: the screens' registers are not affected.
+// Generators of a linear job by one workgroup of its team.  Not inlined: the
+// screens' registers are not affected.
 __device__ __noinline__ void find_generators(int n, int d, int ord, unsigned long long capacity, LinResult *res,
                                              unsigned long long *bits) {
-  __shared__ LinLds<kLinLdsWords> S;
+  LinLds<kLinLdsWords> &S = g_lds.gens;
   const bool ok = lin_search(S, n, d, ord, 0, bits, kLinTeamWords);
   if (threadIdx.x < 32) res->gen[threadIdx.x] = (int)threadIdx.x < S.dim ? S.gen[threadIdx.x] : 0u;
   if (threadIdx.x == 0) {
@@ -1451,9 +1479,9 @@ __device__ __forceinline__ bool build_linear(Lds &L, const Params &P, const Team
   if (L.abort) return true;
   if (ld_relaxed(&W.lin->ok) == 0) return false;
   const unsigned long long end = ld_relaxed(&W.lin->end);
-  lin_word_tables(L.u.lin, W.lin->gen, ld_relaxed(&W.lin->dim));
+  lin_word_tables(L.lin, W.lin->gen, ld_relaxed(&W.lin->dim));
   __syncthreads();
-  lin_emit(L.u.lin, L.code, 0, end, (unsigned long long)L.team_rank * kBlock + threadIdx.x,
+  lin_emit(L.lin, L.code, 0, end, (unsigned long long)L.team_rank * kBlock + threadIdx.x,
            (unsigned long long)L.team_size * kBlock);
   if (L.team_rank == 0 && threadIdx.x == 0) {
     W.ctl->m = end;
@@ -1461,6 +1489,8 @@ __device__ __forceinline__ bool build_linear(Lds &L, const Params &P, const Team
   }
   return true;
 }
+
+#include "cover_build.h"
 
 // ---------------------------------------------------------------------------
 // The persistent kernel: teams pull jobs until the queue is empty
@@ -1558,6 +1588,7 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
       L.deep_tile = dt ? dt : (unsigned int)kTile;
       L.mfma = ld_sys(&J->valu_screen) == 0;
       L.linear = ld_sys(&J->linear);
+      L.by_cover = ld_sys(&J->cover);
       const int wclass = ld_sys(&J->wclass);
       L.walk.n = L.n;
       L.walk.ord = L.ord;
@@ -1601,10 +1632,13 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
          k += (unsigned long long)L.team_size * kBlock)
       W.cur[k] = 0;
     if (L.team_rank == 0 && tid < kSMax / 32) W.deep_fail[tid] = 0;
+    if (L.sub_rank == 0 && tid == 0)
+      __hip_atomic_store(&W.cover->arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     team_barrier(L, P, P.spin_limit);
 
     if (L.d <= 1 && !L.walk.so) emit_ordering(L, W);
-    else if (!kLinear || !L.linear || !build_linear(L, P, W)) build_code<SO>(L, P, W);
+    else if ((!kLinear || !L.linear || !build_linear(L, P, W)) && (SO || !L.by_cover || !build_cover(L, P, W)))
+      build_code<SO>(L, P, W);
 
     __syncthreads();
     if (tid == 0) {
@@ -1665,25 +1699,21 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
 // Three entry symbols with one body, so that profiles tell the single-code
 // launches, the batch launches and the server launches apart.
 __global__ void __launch_bounds__(kBlock) greedy_code_kernel(Params P) {
-  __shared__ Lds L;
-  persistent_body<false, false>(L, P);
+  persistent_body<false, false>(g_lds, P);
 }
 
 __global__ void __launch_bounds__(kBlock) greedy_batch_kernel(Params P) {
-  __shared__ Lds L;
-  persistent_body<false, true>(L, P);
+  persistent_body<false, true>(g_lds, P);
 }
 
 __global__ void __launch_bounds__(kBlock) greedy_server_kernel(Params P) {
-  __shared__ Lds L;
-  persistent_body<false, true>(L, P);
+  persistent_body<false, true>(g_lds, P);
 }
 
 // Self-orthogonal codes: the same body with the extra clash rule compiled in
 // (a kernel of its own, so the plain screen's registers are unaffected).
 __global__ void __launch_bounds__(kBlock) greedy_code_so_kernel(Params P) {
-  __shared__ Lds L;
-  persistent_body<true, false>(L, P);
+  persistent_body<true, false>(g_lds, P);
 }
 
 // Reset of the barrier block and the device queue before a launch (a kernel
@@ -1720,7 +1750,7 @@ __global__ void init_job_kernel(Bar *bar, DevQueue *dq, Job *dst, Job job) {
 }
 
 // Workspace of greedy_code_device_noalloc: barrier block, queue, one job and
-// one team workspace (about 540 KiB), held by every device the library runs
+// one team workspace (about 3.6 MiB), held by every device the library runs
 // on until the process ends.  Host code reaches it only through the address
 // hipGetSymbolAddress returns for the current device.
 constexpr size_t kScratchBytes =
@@ -1781,7 +1811,7 @@ __global__ void __launch_bounds__(kBlock) probe_matrix_loop_kernel(int iters, un
 
 // Team barriers alone: the grid joins one team and crosses `iters` barriers.
 __global__ void __launch_bounds__(kBlock) probe_barrier_kernel(Params P, int iters) {
-  __shared__ Lds L;
+  Lds &L = g_lds;
   team_join(L, P);
   for (int i = 0; i < iters && !L.abort; ++i) team_barrier(L, P, P.spin_limit);
 }
@@ -2039,6 +2069,11 @@ void fill_job(Job *J, int n, int d, int ordering, uint32_t *words, uint64_t capa
   }
 }
 
+bool cover_job(const Job &J) {
+  return (J.ord == GC_GRLEX || J.ord == GC_GREVLEX) && !J.so && J.n <= kCovMaxN && J.d >= 2 && J.d <= kCovMaxD &&
+         J.near_depth == 0 && J.target == 0 && J.mode == 0 && J.deep_tile == 0 && J.valu_screen == 0;
+}
+
 int prepare_batch(const gc_job *jobs, int njobs, Job *J, int *order) {
   for (int i = 0; i < njobs; ++i) {
     const gc_job &g = jobs[i];
@@ -2048,6 +2083,7 @@ int prepare_batch(const gc_job *jobs, int njobs, Job *J, int *order) {
       return fail(GC_EINVAL, "job %d: d_words must be a 16-byte aligned device array", i);
     fill_job(&J[i], g.n, g.d, g.ordering, g.d_words, g.capacity, g.d_count, nullptr);
     J[i].linear = linear_job(J[i]);
+    J[i].cover = cover_job(J[i]);
   }
   // Teams claim jobs in queue order; the queue holds the jobs longest first
   // (by the exhaustive-scan work bound 2^n * capacity), so that the largest
@@ -2300,6 +2336,7 @@ int greedy_code_problem_device(const gc_problem *p, uint32_t *d_words, uint64_t 
       return job_result(J, capacity);
     }
   }
+  J.cover = cover_job(J) && !(tuning && tuning->grid_blocks);
   rc = run_batch(&J, 1, 1, tuning ? tuning->grid_blocks : 0, stream, &ms,
                  p->self_orthogonal ? LaunchKind::kSingleSO : LaunchKind::kSingle);
   if (rc) return rc;
@@ -2349,6 +2386,7 @@ int greedy_code_device_noalloc(int n, int d, int ordering, uint32_t *d_words, ui
     if (rc) return rc;
     if (built) return job_result(J, capacity);
   }
+  J.cover = cover_job(J);
   unsigned int grid = 0;
   rc = pick_grid(0, &grid);
   if (rc) return rc;
@@ -2572,7 +2610,7 @@ int greedy_code_tune(int n, int d, int ordering, void *hip_stream, gc_tuning *be
       {~0ull, 0, 0, 0, 0},        {65536ull, 0, 0, 2, 0}, {65536ull, 0, 0, 1, 0},
       {16384ull, 0, 0, 2, 0},     {16384ull, 0, 0, 1, 0}, {4096ull, 0, 0, 2, 0},
   };
-  if (ordering == GC_LEX || ordering == GC_GRAY) cands.push_back({0, 0, 0, 0, 0});  // from its generators
+  cands.push_back({0, 0, 0, 0, 0});  // no tuning: from the generators, by cover marks, or the defaults
   uint32_t *words = nullptr;
   HIP_TRY(hipMalloc((void **)&words, (size_t)cap * sizeof(uint32_t)));
   std::vector<uint32_t> ref, cur;
@@ -2583,6 +2621,7 @@ int greedy_code_tune(int n, int d, int ordering, void *hip_stream, gc_tuning *be
     Job J;
     fill_job(&J, n, d, ordering, words, cap, nullptr, &t);
     bool built = false;
+    J.cover = cover_job(J);
     int r = linear_job(J) ? run_linear(&J, st, nullptr, 0, ms, &built) : GC_OK;
     if (r == GC_OK && !built) r = run_batch(&J, 1, 1, 0, st, ms, LaunchKind::kSingle);
     if (r) return r;

@@ -243,6 +243,7 @@ int pump(gc_server *s) {
       J->valu_screen = tu.valu_screen;
     }
     J->linear = linear_job(*J);
+    J->cover = cover_job(*J);
     s->slot_ticket[t.slot] = id;
     s->inflight.insert(id);
     ++s->published;

@@ -1,0 +1,94 @@
+"""Graded codes of distance 2 to 4 built by cover marks against the screens:
+one word, one and several workgroups, every slice count, the limit of words a
+slice accepts in a round, constant weights, ranges, prefixes, capacities.
+
+The screens build the same code when a tuning asks for them (target_survivors
+here), and are checked against the oracle elsewhere; results are words, so
+they have to be equal."""
+import sys
+
+import numpy as np
+import pytest
+
+import paper_1507_05398_amd as gc
+
+pytestmark = pytest.mark.gpu
+SCREENS = dict(target_survivors=1000)
+
+
+def log(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module", autouse=True)
+def cuda():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a ROCm device"
+    gc.load()
+    return torch
+
+
+def both(p, prefix_words=None):
+    a, _ = gc.device_problem_code(p, prefix_words=prefix_words)
+    b, _ = gc.device_problem_code(p, prefix_words=prefix_words, **SCREENS)
+    return a.cpu().numpy().view(np.uint32), b.cpu().numpy().view(np.uint32)
+
+
+# n <= 6: one bitmap word; 16 and 17: one workgroup, then four; 18, 19, 20: up
+# to 32.  At n = 20, d = 2 slices accept more words in a round than they may.
+@pytest.mark.parametrize("o", ["grlex", "grevlex"])
+@pytest.mark.parametrize("n,d", [(1, 2), (2, 2), (3, 3), (4, 4), (5, 2), (5, 3), (6, 3), (6, 4), (7, 4), (9, 3), (13, 4),
+                                 (16, 3), (16, 4), (17, 2), (17, 3), (18, 4), (19, 3), (20, 2), (20, 4), (21, 3),
+                                 (23, 4)])
+def test_walks(n, d, o):
+    log(f"[cover] n={n} d={d} {o}")
+    got, ref = both(gc.problem(n, d, o))
+    assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("o", ["lex", "grlex", "grevlex"])
+@pytest.mark.parametrize("n,w,d", [(5, 0, 3), (6, 6, 4), (9, 1, 2), (13, 6, 4), (17, 8, 3), (20, 10, 2), (22, 3, 4)])
+def test_constant_weight(n, w, d, o):
+    log(f"[cover] n={n} w={w} d={d} {o}")
+    got, ref = both(gc.problem(n, d, o, weight=w))
+    assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("n,d,o,w", [(11, 3, "grlex", -1), (17, 4, "grevlex", -1), (17, 3, "grlex", 7),
+                                     (15, 4, "grevlex", 6)])
+def test_ranges_and_prefixes(n, d, o, w):
+    total = gc.problem_positions(gc.problem(n, d, o, weight=w))
+    full, _ = both(gc.problem(n, d, o, weight=w))
+    for cut in (1, 2, total // 3, total // 2 + 1, total - 1):
+        log(f"[cover] {o} n={n} w={w} cut {cut} of {total}")
+        head, ref = both(gc.problem(n, d, o, weight=w, stop=cut))
+        assert np.array_equal(head, ref) and np.array_equal(head, full[: len(head)])
+        got, ref = both(gc.problem(n, d, o, weight=w, start=cut, prefix=len(head)), prefix_words=head)
+        assert np.array_equal(got, ref) and np.array_equal(got, full)
+        # Any words may be given: not the code's, and not of length n either.
+        other = np.random.default_rng(cut).integers(0, 1 << n + 2, size=50).astype(np.uint32)
+        got, ref = both(gc.problem(n, d, o, weight=w, start=cut, prefix=50), prefix_words=other)
+        assert np.array_equal(got, ref)
+
+
+def test_capacity_keeps_the_beginning_and_nothing_past_it(cuda):
+    full, _ = both(gc.problem(17, 3, "grlex"))
+    for cap in (1, 2, 1001, len(full) - 1):
+        words = cuda.full((cap + 8,), -1, dtype=cuda.int32, device="cuda")
+        count = cuda.zeros(1, dtype=cuda.int64, device="cuda")
+        with pytest.raises(gc.GreedyCodeError) as e:
+            gc.greedy_code_device(17, 3, "grlex", words[:cap], count)
+        assert e.value.rc == gc.GC_ECAPACITY and int(count.item()) == cap
+        got = words.cpu().numpy().view(np.uint32)
+        assert np.array_equal(got[:cap], full[:cap]) and (got[cap:] == 0xFFFFFFFF).all()
+
+
+@pytest.mark.parametrize("teams", [1, 2, 4, 8])
+def test_batch(teams):
+    jobs = [(n, d, o) for o in ("grlex", "grevlex") for n, d in [(3, 2), (9, 3), (16, 4), (17, 3), (20, 4)]]
+    log(f"[cover] batch teams={teams}")
+    words, _, _ = gc.greedy_code_batch(jobs, teams=teams)
+    for (n, d, o), w in zip(jobs, words):
+        ref, _ = gc.device_code(n, d, o, **SCREENS)
+        assert np.array_equal(w.cpu().numpy(), ref.cpu().numpy()), (n, d, o)
