@@ -66,7 +66,7 @@ enum { GC_JOB_WAITING = 0,   /* submitted, waiting for device memory */
  * them; they measure the device's total work, which includes speculation.
  * A linear code built from its generators (see gc_tuning) runs no windows
  * and no checks: only count and kernel_ms are set.  A code built by cover
- * marks sets resolve_rounds (its rounds) besides. */
+ * marks sets resolve_rounds or windows (its rounds or windows) besides. */
 typedef struct gc_stats {
     uint64_t count;           /* |C| */
     uint64_t windows;         /* candidate windows processed */
@@ -85,8 +85,8 @@ typedef struct gc_stats {
  * The greedy codes of GC_LEX, GC_GRAY and GC_BORDER walks (self-orthogonal
  * ones included, a weight not) are linear; with every field zero they are
  * built from their generators.  GC_GRLEX and GC_GREVLEX codes (a weight too,
- * not self-orthogonal) of d = 2, 3 or 4 and n <= 24 are built by marking the
- * ball of each accepted word in a bitmap of the space.  Any field set asks
+ * not self-orthogonal) of n <= 24 are built by marking the ball of each
+ * accepted word in a bitmap of the space.  Any field set asks
  * for the windowed screens, which build the same code. */
 typedef struct gc_tuning {
     uint64_t near_depth;    /* newest code words screened before the in-window

@@ -1,7 +1,8 @@
-// cover.h -- storage of the cover builder (cover_build.h): graded codes of
-// distance at most 4 from a bitmap of the whole space.
+// cover.h -- storage of the cover builder (cover_build.h): graded codes from
+// a bitmap of the whole space.
 #pragma once
 
+#include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace gcimpl {
@@ -9,33 +10,57 @@ namespace gcimpl {
 constexpr int kCovTeam = 32;             // workgroups (slices of the space), at most
 constexpr int kCovWords = 8192;          // 64-bit words of a slice, at most
 constexpr int kCovMaxN = 24;             // 2^24 bits: 32 slices of 8192 words
-constexpr int kCovMaxD = 4;
+constexpr int kCovMaxD = 4;              // by rounds; larger distances by windows
 constexpr unsigned int kCovSeg = 4096;   // words a slice accepts in one round, at most
 constexpr unsigned int kCovOwn = 512;
 constexpr int kCovShared = 12;           // words a wave tests together with 16 lanes each, at most
 constexpr unsigned int kCovMaxRounds = 1u << 19;
 constexpr int kCovDiffs = 384;           // word-index differences of weight <= 3 in 13 bits: 378
+constexpr int kCovWin = 1024;            // candidates of a window, at most (one a thread)
+constexpr int kCovBlocks = kCovWin / 64;
+constexpr int kCovLevels = 8;            // levels listed at once, at most
 
 struct CoverLds {
   unsigned long long dead[kCovWords + 1];  // the slice: 1 = accepted, rejected or no candidate; then a word of ones
-  unsigned long long acc[kCovWords];     // accepted in the current level
-  uint16_t queue[kCovWords];             // words with undecided candidates of the level
-  uint16_t diff[kCovDiffs];              // word-index differences, by weight
-  unsigned int cum[kCovMaxD + 1];        // differences of weight below j
-  uint8_t other[kCovTeam];               // differences of slice numbers, by weight
   unsigned long long level[64];          // [32 + j]: the bits of a word whose index has weight j
-  unsigned long long ball[kCovMaxD][64]; // ball[r][b]: bit indices within distance r of b
-  unsigned int cnt[kCovTeam];            // per slice: words it accepted in the last round
-  unsigned int total[kCovTeam];          // per slice: words it accepted in the level
-  uint32_t own[kCovOwn];                 // the first words this slice accepted in the round
-  unsigned int wsum[16];
-  unsigned int qn, segn, seg_ok, left, accn, open;
+  unsigned int wsum[32];
   unsigned int epoch;                    // workgroups that have passed the team's barriers
+  union {
+    struct {                             // distance at most 4: rounds
+      unsigned long long acc[kCovWords]; // accepted in the current level
+      uint16_t queue[kCovWords];         // words with undecided candidates of the level
+      uint16_t diff[kCovDiffs];          // word-index differences, by weight
+      unsigned int cum[kCovMaxD + 1];    // differences of weight below j
+      uint8_t other[kCovTeam];           // differences of slice numbers, by weight
+      unsigned long long ball[kCovMaxD][64];  // ball[r][b]: bit indices within distance r of b
+      unsigned int cnt[kCovTeam];        // per slice: words it accepted in the last round
+      unsigned int total[kCovTeam];      // per slice: words it accepted in the level
+      uint32_t own[kCovOwn];             // the first words this slice accepted in the round
+      unsigned int qn, segn, seg_ok, left, accn, open;
+    };
+    struct {                             // larger distances: windows
+      uint16_t wdiff[kCovWords];         // word-index differences, by weight
+      unsigned int wcum[15];             // differences of weight below j
+      unsigned long long wball[8][64];   // as ball, radius -1 (none) .. 6 (every bit)
+      alignas(16) uint32_t cand[kCovWin];  // the window's candidates, in walk order
+      alignas(16) uint32_t took[kCovWin];  // those accepted
+      unsigned long long accm[kCovBlocks];   // accepted, by block of 64 candidates
+      uint3 run[kCovLevels * kCovTeam];  // per (level, slice): place in the window, length, place in its list
+      unsigned int size, done_levels, listed;  // the window's candidates; levels it takes whole, and at all
+    };
+  };
 };
 
 // Global memory of a cover team: every exchange is within one XCD (one L2).
 struct CoverWs {
-  unsigned long long active[(1u << (kCovMaxN - 6)) + 32];  // undecided candidates of the level; then zeros
+  union {
+    unsigned long long active[(1u << (kCovMaxN - 6)) + 32];  // undecided candidates of the level; then zeros
+    struct {                                                 // windows
+      uint32_t list[2][kCovTeam][kCovWin];                   // candidates a slice lists
+      unsigned int head[2][kCovTeam][16];                    // levels listed, cut short?, candidates of each level
+      unsigned long long adj[64 * kCovBlocks * (kCovBlocks + 1) / 2];  // earlier neighbours, 64 x 64 tiles
+    };
+  };
   uint32_t seg[2][kCovTeam][kCovSeg];                    // words accepted in a round, by slice
   unsigned long long slot[2][kCovTeam];                  // what a slice reports at a barrier
   unsigned int arrived;                                  // barrier: arrivals so far

@@ -1,6 +1,7 @@
 // cover_build.h -- graded codes (grlex, grevlex; constant weight, ranges and
 // prefixes too) of distance 2, 3 or 4 for n <= 24, from a bitmap of the whole
-// space instead of distance checks.  Included by greedy_code.hip.
+// space instead of distance checks.  Included by greedy_code.hip.  Larger
+// distances: cover_windows.h.
 //
 // An accepted word marks the ball of radius d - 1 around it (301 words at n =
 // 24, d = 3), so a candidate costs one bit and not a scan of the code.  The
@@ -506,12 +507,7 @@ __device__ __noinline__ void cover_team(CoverWs *ws, Ctl *ctl, unsigned int rank
     const unsigned int per = (words + kBlock - 1) / kBlock, w0 = tid * per;
     unsigned int mine = 0;
     for (unsigned int i = w0; i < w0 + per && i < words; ++i) mine += (unsigned int)__builtin_popcountll(C.acc[i]);
-    unsigned int incl = mine;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const unsigned int y = __shfl_up(incl, off);
-      if (lane >= off) incl += y;
-    }
+    const unsigned int incl = wave_scan(mine);
     if (lane == 63) C.wsum[wave] = incl;
     __syncthreads();
     base += incl - mine;
@@ -530,17 +526,25 @@ __device__ __noinline__ void cover_team(CoverWs *ws, Ctl *ctl, unsigned int rank
   }
 }
 
-// A graded code of small distance by cover marks.  The team's workgroups on
-// one XCD build it, while the others wait at the barrier that ends the job:
-// one workgroup up to 1024 words (n = 16: 368 us against 429 us with two),
-// then as many (a power of two) as give each 512 words or more (n = 20, d =
-// 3: 1.22 ms with 32 workgroups, 1.52 ms with 8, 2.22 ms with 2).  False
-// (alike in every workgroup) when the slices would not fit.
+#include "cover_windows.h"
+
+// A graded code by cover marks.  The team's workgroups on one XCD build it,
+// while the others wait at the barrier that ends the job.  Rounds: one
+// workgroup up to 1024 words (n = 16: 368 us against 429 us with two), then as
+// many (a power of two) as give each 512 words or more (n = 20, d = 3: 1.22
+// ms with 32 workgroups, 1.52 ms with 8, 2.22 ms with 2).  Windows share out
+// their conflict graphs, so workgroups pay from 8 words each (n = 16, d = 5:
+// 220 us with 32, 294 us with one).  False (alike in every workgroup) when
+// the slices would not fit.
 __device__ __forceinline__ bool build_cover(Lds &L, const Params &P, const TeamWs &W) {
-  const unsigned long long words = L.n > 6 ? 1ull << (L.n - 6) : 1ull;
+  const unsigned int words = L.n > 6 ? 1u << (L.n - 6) : 1u, most = umin(L.sub_size, (unsigned int)kCovTeam);
+  const unsigned int least = L.d > kCovMaxD ? 8u : words > 1024 ? 512u : 1024u;  // words of a slice
   unsigned int team = 1;
-  while (words > 1024 && 2 * team <= L.sub_size && 2 * team <= (unsigned int)kCovTeam && words / (2 * team) >= 512) team *= 2;
-  if (words / team > (unsigned long long)kCovWords) return false;
-  if (L.sub_rank < team) cover_team(W.cover, W.ctl, L.sub_rank, team, &P.dq->abort, P.spin_limit);
+  while (2 * team <= most && words / (2 * team) >= least) team *= 2;
+  if (words / team > (unsigned int)kCovWords) return false;
+  if (L.sub_rank < team) {
+    if (L.d <= kCovMaxD) cover_team(W.cover, W.ctl, L.sub_rank, team, &P.dq->abort, P.spin_limit);
+    else cover_window_team(W.cover, W.ctl, L.sub_rank, team, &P.dq->abort, P.spin_limit);
+  }
   return true;
 }

@@ -1,0 +1,331 @@
+// cover_windows.h -- graded codes of distance 5 and more for n <= 24 from the
+// same bitmap as cover_build.h (included by it), in windows.
+//
+// With a larger distance a level takes many short rounds, each a walk over
+// many neighbour words.  Here the team lists the first 1024 undecided
+// candidates in walk order, computes their
+// conflict graph from their distances (64 x 64 tiles, shared out to all
+// waves: three instructions a pair), and every workgroup finds the greedy's
+// choice among them for itself: a wave holds the conflicts of its block of 64
+// candidates in registers, and the blocks are decided in turn.  Each
+// workgroup then marks the balls of the accepted words in its slice, which
+// removes every candidate of the window.  Two XCD-local barriers a window.
+//
+// What bounds it: about 25 us a window at n = 22, d = 5 (listing 4, waiting
+// for the busiest slice 4, gathering 2.4, graph 2.5, choice 6.5, marks 4), and
+// from n = 24 on the LDS throughput of the marks, uneven over the slices: a
+// window's words are neighbours in the walk, so the slices near them mark
+// most (slices taken from lower bits, which share the marks evenly, need a
+// merge of the lists: n = 24, d = 6 2.35 ms against 2.53 ms, but n = 22, d = 5
+// 1.05 ms against 0.95 ms).
+
+// Bits 0 .. 63: which of the 64 words at `w` (broadcast reads) are closer than
+// d to x.  XOR, a population count that starts at -d, and its sign shifted
+// into the mask.
+__device__ __forceinline__ unsigned long long clash_mask(const uint32_t *w, uint32_t x, int d) {
+  unsigned int half[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    unsigned int m = 0;
+    const uint4 *v = reinterpret_cast<const uint4 *>(w + 32 * h);
+#pragma unroll
+    for (int q = 7; q >= 0; --q) {
+      const uint4 c = v[q];
+      m = __builtin_amdgcn_alignbit(m, (unsigned int)(__builtin_popcount(x ^ c.w) - d), 31);
+      m = __builtin_amdgcn_alignbit(m, (unsigned int)(__builtin_popcount(x ^ c.z) - d), 31);
+      m = __builtin_amdgcn_alignbit(m, (unsigned int)(__builtin_popcount(x ^ c.y) - d), 31);
+      m = __builtin_amdgcn_alignbit(m, (unsigned int)(__builtin_popcount(x ^ c.x) - d), 31);
+    }
+    half[h] = m;
+  }
+  return ((unsigned long long)half[1] << 32) | half[0];
+}
+
+__device__ __noinline__ void cover_window_team(CoverWs *ws, Ctl *ctl, unsigned int rank_v, unsigned int team_v,
+                                               int *abort_flag, unsigned int limit) {
+  Lds &L = g_lds;
+  CoverLds &C = g_lds.cover;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const unsigned int rank = __builtin_amdgcn_readfirstlane(rank_v), team = __builtin_amdgcn_readfirstlane(team_v);
+  const int n = __builtin_amdgcn_readfirstlane(L.n), d = __builtin_amdgcn_readfirstlane(L.d);
+  const bool rev = L.ord == GC_GREVLEX;
+  const int slice_bits = __builtin_ctz(team);
+  const unsigned int words = n > 6 ? 1u << (n - 6 - slice_bits) : 1u;
+  const int hbits = __builtin_ctz(words);
+  const unsigned int high = rank << hbits;
+  const unsigned long long valid = n < 6 ? (1ull << (1 << n)) - 1 : ~0ull;
+  uint32_t *code = L.code;
+  const unsigned long long capacity = L.capacity, start = L.p_start, stop = L.total;
+  unsigned long long m = L.m_start;
+
+  // Tables: differences of the word index by weight (C(hbits, j) of weight j),
+  // balls, level masks; the empty slice.
+  if (tid == 0) {
+    unsigned int at = 0, of = 1;
+    for (int j = 0; j < 15; ++j) {
+      C.wcum[j] = at;
+      at += of;
+      of = j < hbits ? of * (unsigned int)(hbits - j) / (unsigned int)(j + 1) : 0;
+    }
+    C.epoch = 0;
+  }
+  if (tid < 8 * 64) {
+    unsigned long long b = 0;
+    for (int x = 0; x < 64; ++x)
+      if (__builtin_popcount(x ^ (tid & 63)) < (tid >> 6)) b |= 1ull << x;
+    C.wball[tid >> 6][tid & 63] = b;
+  } else if (tid >= 512 && tid < 576) {
+    unsigned long long b = 0;
+    for (int x = 0; x < 64; ++x)
+      if (__builtin_popcount(x) == tid - 512 - 32) b |= 1ull << x;
+    C.level[tid - 512] = b;
+  }
+  __syncthreads();
+  for (unsigned int w = tid; w < words; w += kBlock) {
+    const int j = __builtin_popcount(w);
+    // Rank among the numbers of its weight: C(b, 1) + C(b', 2) + ...
+    unsigned int place = C.wcum[j], k = 1;
+    for (unsigned int b = w; b; b &= b - 1, ++k) {
+      const unsigned int p = __builtin_ctz(b);
+      if (p >= k) place += L.tab.binom[p][k];
+    }
+    C.wdiff[place] = (uint16_t)w;
+    C.dead[w] = ~valid;
+  }
+  __syncthreads();
+
+  // Marks the balls around four numbers (uniform), by one wave: a lane takes a
+  // difference of the word index for all of them.  Instructions bound this
+  // loop, so a mark is few of them: the slice's byte offset is one XOR, the
+  // ball's row one sum and one clamp (row 0, radius -1, is empty: differences
+  // of too much weight need no test).
+  auto mark4 = [&](const uint32_t (&c)[4], int have) {
+    int row[4];
+    unsigned int at[4], most = 0;
+    unsigned int bit[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = q < have ? d - 1 - __builtin_popcount((c[q] >> 6 >> hbits) ^ rank) : -1;
+      row[q] = 64 * (r + 1);
+      at[q] = (c[q] >> 6) & (words - 1);
+      bit[q] = c[q] & 63;
+      const unsigned int per = r < 0 ? 0u : (unsigned int)__builtin_amdgcn_readfirstlane((int)C.wcum[r + 1 < 14 ? r + 1 : 14]);
+      most = per > most ? per : most;
+    }
+    for (unsigned int e = lane; e < most; e += 64) {
+      const unsigned int diff = C.wdiff[e];
+      const int weight = 64 * __builtin_popcount(diff);
+      unsigned long long b[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        int o = row[q] - weight;
+        o = o < 0 ? 0 : o > 7 * 64 ? 7 * 64 : o;
+        b[q] = (&C.wball[0][0])[o + (int)bit[q]];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        __hip_atomic_fetch_or(&C.dead[at[q] ^ diff], b[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  };
+  // Words accepted before `start`: their first n bits, as on the matrix screens.
+  for (unsigned long long i = 4 * wave; i < m; i += 4 * kWaves) {
+    uint32_t c[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) c[q] = cover_number(code[i + q < m ? i + q : i] & ((1u << n) - 1u), n, rev);
+    mark4(c, m - i < 4 ? (int)(m - i) : 4);
+  }
+
+  // Walk levels with positions in [start, stop); candidates outside are none.
+  int first = n + 1, last = -1;
+  for (int w = 0; w <= n; ++w) {
+    const unsigned long long at = L.tab.off[w], end = L.tab.off[w + 1];
+    const unsigned long long lo = start > at ? start - at : 0, hi = stop < end ? (stop > at ? stop - at : 0) : end - at;
+    if (lo >= hi) continue;
+    if (first > n) first = w;
+    last = w;
+    if (lo == 0 && hi == end - at) continue;
+    const int k = rev ? n - w : w;
+    const unsigned long long from = lo > 0 ? unrank_weight(L.tab, lo, k, n) : 0;
+    const unsigned long long to = hi < end - at ? unrank_weight(L.tab, hi, k, n) : 1ull << n;
+    __syncthreads();  // the marks: a word's bits are set here without an atomic
+    for (unsigned int i = tid; i < words; i += kBlock) {
+      const unsigned long long base = 64ull * (high + i);
+      unsigned long long in = ~0ull;
+      if (base < from) in = from - base >= 64 ? 0ull : ~0ull << (from - base);
+      if (base + 64 > to) in &= to <= base ? 0ull : ~0ull >> (64 - (to - base));
+      C.dead[i] |= C.level[32 + k - __builtin_popcount(high + i)] & ~in;
+    }
+  }
+  __syncthreads();
+
+  const unsigned int per = (words + kBlock - 1) / kBlock, w0 = tid * per;
+  // A slice stops listing further levels once it has more than its share of a
+  // window (a window takes a level only if every slice has listed it).
+  const unsigned int share = umin(kCovWin, 2 * kCovWin / team);
+  unsigned int windows = 0, par = 0;
+  int level = first;
+  while (level <= last) {
+    // This slice's first undecided candidates, level by level.
+    unsigned int listed = 0, levels = 0;
+    bool cut = false;
+    for (; levels < (unsigned int)kCovLevels && level + (int)levels <= last && listed < share && !cut; ++levels) {
+      const int w = level + (int)levels, k = 32 + (rev ? n - w : w);
+      unsigned int mine = 0;
+      if (L.tab.off[w + 1] > L.tab.off[w])  // (a weight: the other levels have no candidates)
+        for (unsigned int i = w0; i < w0 + per && i < words; ++i)
+          mine += (unsigned int)__builtin_popcountll(C.level[k - __builtin_popcount(high + i)] & ~C.dead[i]);
+      unsigned int at = wave_scan(mine), all = 0;
+      if (lane == 63) C.wsum[16 * (levels & 1) + wave] = at;
+      __syncthreads();
+      at += listed - mine;
+#pragma unroll
+      for (int wv = 0; wv < kWaves; ++wv) {
+        const unsigned int sum = C.wsum[16 * (levels & 1) + wv];
+        if (wv < wave) at += sum;
+        all += sum;
+      }
+      if (mine)
+        for (unsigned int i = w0; i < w0 + per && i < words; ++i)
+          for (unsigned long long f = C.level[k - __builtin_popcount(high + i)] & ~C.dead[i];
+               f && at < (unsigned int)kCovWin; f &= f - 1, ++at)
+            as_global(ws->list[par][rank])[at] = 64u * (high + i) + __builtin_ctzll(f);
+      if (listed + all > (unsigned int)kCovWin) {
+        all = kCovWin - listed;
+        cut = true;
+      }
+      if (tid == 0) as_global(ws->head[par][rank])[2 + levels] = all;
+      listed += all;
+    }
+    if (tid == 0) {
+      as_global(ws->head[par][rank])[0] = levels;
+      as_global(ws->head[par][rank])[1] = cut;
+    }
+    cover_barrier(ws, team, abort_flag, limit);
+    if (L.abort) return;
+    if (wave == 0) {
+      // Candidates of every (level, slice) in walk order; a list cut short
+      // ends the window, and so does a level that a slice has not listed.
+      const bool in = (unsigned int)lane < team;
+      const unsigned int have = in ? cover_ld(&ws->head[par][lane][0]) : (unsigned int)kCovLevels;
+      const bool was_cut = in && cover_ld(&ws->head[par][lane][1]) != 0;
+      unsigned int num[kCovLevels];
+#pragma unroll
+      for (int l = 0; l < kCovLevels; ++l) num[l] = in ? cover_ld(&ws->head[par][lane][2 + l]) : 0u;
+      unsigned int before = 0, full = 0, from = 0;
+      int l = 0;
+#pragma unroll
+      for (; l < kCovLevels; ++l) {
+        if (ballot((int)have <= l)) break;  // a slice has not listed level l
+        unsigned int own = num[l];
+        // Slices after one whose list was cut in this level do not count.
+        const unsigned long long cuts = ballot(was_cut && (int)have == l + 1);
+        if (cuts && lane > (int)__builtin_ctzll(cuts)) own = 0;
+        const unsigned int at = wave_scan(own);
+        if (in) {
+          C.run[l * kCovTeam + lane] = make_uint3(before + at - own, own, from);
+          from += own;
+        }
+        before += (unsigned int)__builtin_amdgcn_readlane((int)at, 63);
+        if (!cuts && before <= (unsigned int)kCovWin) full = (unsigned int)l + 1;
+        if (cuts || before >= (unsigned int)kCovWin) {
+          ++l;
+          break;
+        }
+      }
+      if (lane == 0) {
+        C.size = before < (unsigned int)kCovWin ? before : (unsigned int)kCovWin;
+        C.done_levels = full;
+        C.listed = (unsigned int)l;
+      }
+    }
+    __syncthreads();
+    const unsigned int size = C.size, complete = C.done_levels;
+    // Copy: a wave takes a slice's run of a level at a time.
+    const unsigned int runs = C.listed * team;
+    for (unsigned int e = wave; e < runs; e += kWaves) {
+      const uint3 run = C.run[(e >> slice_bits) * kCovTeam + (e & (team - 1))];
+      for (unsigned int i = lane; i < run.y && run.x + i < (unsigned int)kCovWin; i += 64)
+        C.cand[run.x + i] = cover_ld(&ws->list[par][e & (team - 1)][run.z + i]);
+    }
+    __syncthreads();
+    // Conflict graph: earlier neighbours, 64 x 64 tiles.
+    const unsigned int blocks = (size + 63) / 64, tiles = blocks * (blocks + 1) / 2;
+    for (unsigned int t = (unsigned int)wave * team + rank; t < tiles; t += kWaves * team) {
+      unsigned int I = 0;
+      while ((I + 1) * (I + 2) / 2 <= t) ++I;
+      const unsigned int J = t - I * (I + 1) / 2, j = 64 * I + lane;
+      unsigned long long mask = clash_mask(&C.cand[64 * J], C.cand[j], d);
+      mask &= I == J ? lanemask_lt() : ~0ull;
+      if (j >= size) mask = 0;
+      as_global(ws->adj)[64 * t + lane] = mask;
+    }
+    cover_barrier(ws, team, abort_flag, limit);
+    if (L.abort) return;
+    // The greedy's choice.  A wave keeps the conflicts of its block; a block
+    // is decided once every earlier one is.
+    unsigned long long row[kCovBlocks];
+#pragma unroll
+    for (int J = 0; J < kCovBlocks; ++J)
+      row[J] = J <= wave && wave < (int)blocks ? cover_ld(&ws->adj[64 * (wave * (wave + 1) / 2 + J) + lane]) : 0ull;
+    bool killed = (unsigned int)tid >= size;
+#pragma unroll
+    for (int I = 0; I < kCovBlocks; ++I) {
+      if (I < (int)blocks) {
+        if (wave == I) {
+          // The first candidate left is accepted and takes its later
+          // neighbours with it (few words a block: synchronous rounds over
+          // all lanes measured slower, 954 us against 946 us at n = 22, d = 5).
+          unsigned long long acc = 0, und = ballot(!killed);
+          while (und) {
+            const int j = __builtin_ctzll(und);
+            const unsigned int part = j < 32 ? (unsigned int)row[I] : (unsigned int)(row[I] >> 32);
+            acc |= 1ull << j;
+            und &= ~((1ull << j) | ballot((part >> (j & 31)) & 1));
+          }
+          if (lane == 0) C.accm[I] = acc;
+        }
+        __syncthreads();
+        killed |= (row[I] & C.accm[I]) != 0;
+      }
+    }
+    // The accepted words, in order.
+    unsigned int before = 0, all = 0;
+    for (unsigned int I = 0; I < blocks; ++I) {
+      const unsigned int c = (unsigned int)__builtin_popcountll(C.accm[I]);
+      if (I < (unsigned int)wave) before += c;
+      all += c;
+    }
+    if ((unsigned int)wave < blocks && ((C.accm[wave] >> lane) & 1)) {
+      const unsigned int at = before + (unsigned int)__builtin_popcountll(C.accm[wave] & lanemask_lt());
+      const uint32_t c = C.cand[tid];
+      C.took[at] = c;
+      if (rank == 0 && m + at < capacity) as_global(code)[m + at] = cover_number(c, n, rev);
+    }
+    __syncthreads();
+    m += all;
+    if (m > capacity) break;
+    for (unsigned int i = 4 * wave; i < all; i += 4 * kWaves) {
+      const uint4 t = *reinterpret_cast<const uint4 *>(&C.took[i]);
+      const uint32_t c[4] = {(uint32_t)__builtin_amdgcn_readfirstlane((int)t.x), (uint32_t)__builtin_amdgcn_readfirstlane((int)t.y),
+                             (uint32_t)__builtin_amdgcn_readfirstlane((int)t.z), (uint32_t)__builtin_amdgcn_readfirstlane((int)t.w)};
+      mark4(c, all - i < 4 ? (int)(all - i) : 4);
+    }
+    __syncthreads();
+    level += (int)complete;
+    par ^= 1;
+    // Every window decides its candidates and passes levels without any: the
+    // limit is never met, and like every wait's it ends the launch.
+    if (++windows > kCovMaxRounds) {
+      if (tid == 0) {
+        __hip_atomic_store(abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        L.abort = 1;
+      }
+      return;
+    }
+  }
+  if (rank == 0 && tid == 0) {
+    if (m > capacity) set_status(ctl, GC_ECAPACITY);
+    ctl->m = m < capacity ? m : capacity;
+    ctl->stat_windows = windows;
+  }
+}

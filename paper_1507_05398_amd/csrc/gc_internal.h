@@ -133,7 +133,7 @@ void fill_job(Job *J, int n, int d, int ordering, uint32_t *words, uint64_t capa
 // Whether a job's code is linear and no tuning asks for the screens; its code
 // is then built from its generators.
 bool linear_job(const Job &J);
-// Whether a job's code may be built by cover marks (small distance, graded).
+// Whether a job's code may be built by cover marks (graded, n <= 24).
 bool cover_job(const Job &J);
 // Builds a linear single code on `stream` and waits for it: outputs into *J and
 // *built, kernel_ms (may be null) the device time.  `fixed`: a workspace of

@@ -290,6 +290,17 @@ __device__ __forceinline__ unsigned long long lanemask_lt() {
   return l ? (~0ull >> (64 - l)) : 0ull;
 }
 
+// Inclusive prefix sum over the wave (DPP moves: no LDS round trips).
+__device__ __forceinline__ unsigned int wave_scan(unsigned int x) {
+  x += (unsigned int)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);   // row_shr:1, 2, 4, 8
+  x += (unsigned int)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);
+  x += (unsigned int)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);
+  x += (unsigned int)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);
+  x += (unsigned int)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1, 3
+  x += (unsigned int)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2, 3
+  return x;
+}
+
 // A pointer into global memory.  Operations through it are global (not flat)
 // instructions, which count only on the vector-memory counter: an atomic in
 // flight does not hold up the waits for LDS reads.
@@ -499,11 +510,24 @@ __device__ __forceinline__ uint32_t position_word(const Tables &T, const Walk &K
   return __builtin_bitreverse32(~y & mask) >> (32 - n);
 }
 
+struct BinomTable {
+  uint32_t c[33 * 33];
+};
+constexpr BinomTable make_binom() {
+  BinomTable t{};
+  for (int a = 0; a <= 32; ++a)
+    for (int b = 0; b <= a; ++b)
+      t.c[33 * a + b] = b == 0 || b == a ? 1u : t.c[33 * (a - 1) + b - 1] + t.c[33 * (a - 1) + b];
+  return t;
+}
+__constant__ BinomTable kBinomials = make_binom();
+
 // Fill the tables of a walk (whole workgroup): binomials and the offsets of
 // the allowed weight classes (bit w of `classes`) for graded walks, the byte
-// tables of the basis for a B-ordering.
+// tables of the basis for a B-ordering, nothing for lex and Gray.
 __device__ void init_tables(Tables &T, const Walk &K, unsigned long long classes, const uint32_t *basis) {
   const int n = K.n;
+  if (K.ord == GC_LEX || K.ord == GC_GRAY) return;
   if (K.ord == GC_BORDER) {
     for (int i = threadIdx.x; i < 4 * 256; i += blockDim.x) {
       const int byte = i >> 8, v = i & 255;
@@ -515,16 +539,7 @@ __device__ void init_tables(Tables &T, const Walk &K, unsigned long long classes
     __syncthreads();
     return;
   }
-  for (int i = threadIdx.x; i < 33 * 33; i += blockDim.x) {
-    const int a = i / 33, b = i % 33;
-    // C(a, b) by the multiplicative formula, exact in 64 bits for a <= 32.
-    unsigned long long c = 0;
-    if (b <= a) {
-      c = 1;
-      for (int t = 1; t <= b; ++t) c = c * (unsigned long long)(a - b + t) / (unsigned long long)t;
-    }
-    T.binom[a][b] = (uint32_t)c;
-  }
+  for (int i = threadIdx.x; i < 33 * 33; i += blockDim.x) T.binom[i / 33][i % 33] = kBinomials.c[i];
   __syncthreads();
   if (threadIdx.x == 0) {
     unsigned long long acc = 0;
@@ -1253,12 +1268,7 @@ __device__ __forceinline__ void build_code(Lds &L, const Params &P, const TeamWs
         }
         cnt += __builtin_popcount(liveb[k]);
       }
-      unsigned int incl = cnt;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const unsigned int y = __shfl_up(incl, off);
-        if ((int)lane >= off) incl += y;
-      }
+      const unsigned int incl = wave_scan(cnt);
       if (lane == 63) L.wsum[tid >> 6] = incl;
       __syncthreads();
       unsigned int idx = incl - cnt;
@@ -1549,15 +1559,43 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
   // The claim wait (server) may last up to idle_limit polls.
   const unsigned int claim_limit = P.idle_limit + P.spin_limit;
 
+  bool screened = true;  // the window masks may hold the previous job's (or launch's) bits
   while (!L.abort) {
+    // The state of the job to come, before the barrier that starts it (every
+    // workgroup has left the previous job): the window masks and cursors
+    // clear, the team's control block from the claimed job.
     if (L.team_rank == 0 && tid == 0) {
       const int j = claim_job(P, L.team);
-      W.ctl->job = j;
+      Ctl *c = W.ctl;
+      c->job = j;
       if (j >= 0) {
         Job *J = &P.jobs[j];
         st_sys(&J->t_claim, (unsigned long long)wall_clock64());
+        c->m = ld_sys(&J->m_start);
+        c->p = ld_sys(&J->p_start);
+        c->w = kWMin;
+        c->status = 0;
+        c->action = ACT_NEXT;
+        c->ndeep = 0;
+        c->stat_windows = c->stat_rounds = c->stat_surv = 0;
+        c->stat_near = c->stat_deep = c->stat_pairs = 0;
+        c->ticks[0] = c->ticks[1] = c->ticks[2] = c->ticks[3] = 0;
       }
     }
+    if (screened) {
+      for (unsigned long long k = (unsigned long long)L.team_rank * kBlock + tid; k < kWMax / 32;
+           k += (unsigned long long)L.team_size * kBlock) {
+        W.win_dead[0][k] = 0;
+        W.win_dead[1][k] = 0;
+      }
+      for (unsigned long long k = (unsigned long long)L.team_rank * kBlock + tid; k < kCursors;
+           k += (unsigned long long)L.team_size * kBlock)
+        W.cur[k] = 0;
+      if (L.team_rank == 0 && tid < kSMax / 32) W.deep_fail[tid] = 0;
+      screened = false;
+    }
+    if (L.sub_rank == 0 && tid == 0)
+      __hip_atomic_store(&W.cover->arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     team_barrier(L, P, claim_limit);
     if (tid == 0) L.job = ld_relaxed(&W.ctl->job);
     __syncthreads();
@@ -1611,34 +1649,11 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
       if (L.total == 0 || L.total > len) L.total = len;
     }
     __syncthreads();
-    if (L.team_rank == 0 && tid == 0) {
-      Ctl *c = W.ctl;
-      c->m = L.m_start;
-      c->p = L.p_start;
-      c->w = kWMin;
-      c->status = 0;
-      c->action = ACT_NEXT;
-      c->ndeep = 0;
-      c->stat_windows = c->stat_rounds = c->stat_surv = 0;
-      c->stat_near = c->stat_deep = c->stat_pairs = 0;
-      c->ticks[0] = c->ticks[1] = c->ticks[2] = c->ticks[3] = 0;
-    }
-    for (unsigned long long k = (unsigned long long)L.team_rank * kBlock + tid; k < kWMax / 32;
-         k += (unsigned long long)L.team_size * kBlock) {
-      W.win_dead[0][k] = 0;
-      W.win_dead[1][k] = 0;
-    }
-    for (unsigned long long k = (unsigned long long)L.team_rank * kBlock + tid; k < kCursors;
-         k += (unsigned long long)L.team_size * kBlock)
-      W.cur[k] = 0;
-    if (L.team_rank == 0 && tid < kSMax / 32) W.deep_fail[tid] = 0;
-    if (L.sub_rank == 0 && tid == 0)
-      __hip_atomic_store(&W.cover->arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    team_barrier(L, P, P.spin_limit);
-
     if (L.d <= 1 && !L.walk.so) emit_ordering(L, W);
-    else if ((!kLinear || !L.linear || !build_linear(L, P, W)) && (SO || !L.by_cover || !build_cover(L, P, W)))
+    else if ((!kLinear || !L.linear || !build_linear(L, P, W)) && (SO || !L.by_cover || !build_cover(L, P, W))) {
       build_code<SO>(L, P, W);
+      screened = true;
+    }
 
     __syncthreads();
     if (tid == 0) {
@@ -1690,9 +1705,12 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
       st_sys(&J->ticks_deep, ld_relaxed(&c->ticks[3]));
       st_sys(&J->status, ld_relaxed(&c->status));
       st_sys(&J->t_done, (unsigned long long)wall_clock64());
-      __hip_atomic_store(&J->done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+      // (A batch's host reads after the launch, which writes everything back.)
+      if (P.njobs_fixed >= 0) st_sys(&J->done, 1u);
+      else __hip_atomic_store(&J->done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
       __hip_atomic_fetch_add(&P.dq->completed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    if (P.njobs_fixed == 1 && P.nteams == 1) break;  // a single code: no further claim
   }
 }
 
@@ -2070,7 +2088,7 @@ void fill_job(Job *J, int n, int d, int ordering, uint32_t *words, uint64_t capa
 }
 
 bool cover_job(const Job &J) {
-  return (J.ord == GC_GRLEX || J.ord == GC_GREVLEX) && !J.so && J.n <= kCovMaxN && J.d >= 2 && J.d <= kCovMaxD &&
+  return (J.ord == GC_GRLEX || J.ord == GC_GREVLEX) && !J.so && J.n <= kCovMaxN && J.d >= 2 &&
          J.near_depth == 0 && J.target == 0 && J.mode == 0 && J.deep_tile == 0 && J.valu_screen == 0;
 }
 

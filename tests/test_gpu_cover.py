@@ -1,6 +1,7 @@
-"""Graded codes of distance 2 to 4 built by cover marks against the screens:
-one word, one and several workgroups, every slice count, the limit of words a
-slice accepts in a round, constant weights, ranges, prefixes, capacities.
+"""Graded codes built by cover marks (distance up to 4 by rounds, larger ones
+by windows) against the screens: one word, one and several workgroups, every
+slice count, the limits of words a slice accepts in a round or lists for a
+window, constant weights, ranges, prefixes, capacities.
 
 The screens build the same code when a tuning asks for them (target_survivors
 here), and are checked against the oracle elsewhere; results are words, so
@@ -47,8 +48,21 @@ def test_walks(n, d, o):
     assert np.array_equal(got, ref)
 
 
+# Windows: n = 9 and 10: one workgroup, then two; 14 and 15: 16, then 32.  At
+# n = 16, d = 16 a window lists many levels; at n = 19, d = 12 and 22, d = 9 a
+# slice alone has more candidates of a level than a window takes.
+@pytest.mark.parametrize("o", ["grlex", "grevlex"])
+@pytest.mark.parametrize("n,d", [(1, 5), (3, 9), (5, 5), (6, 6), (7, 5), (9, 5), (10, 6), (11, 5), (13, 7), (14, 5),
+                                 (15, 6), (16, 5), (16, 16), (16, 17), (17, 8), (19, 12), (20, 5), (22, 9), (23, 14)])
+def test_walks_of_larger_distance(n, d, o):
+    log(f"[cover] n={n} d={d} {o}")
+    got, ref = both(gc.problem(n, d, o))
+    assert np.array_equal(got, ref)
+
+
 @pytest.mark.parametrize("o", ["lex", "grlex", "grevlex"])
-@pytest.mark.parametrize("n,w,d", [(5, 0, 3), (6, 6, 4), (9, 1, 2), (13, 6, 4), (17, 8, 3), (20, 10, 2), (22, 3, 4)])
+@pytest.mark.parametrize("n,w,d", [(5, 0, 3), (6, 6, 4), (9, 1, 2), (13, 6, 4), (17, 8, 3), (20, 10, 2), (22, 3, 4),
+                                   (6, 3, 5), (12, 6, 6), (18, 9, 5), (21, 4, 6), (22, 11, 8)])
 def test_constant_weight(n, w, d, o):
     log(f"[cover] n={n} w={w} d={d} {o}")
     got, ref = both(gc.problem(n, d, o, weight=w))
@@ -56,7 +70,9 @@ def test_constant_weight(n, w, d, o):
 
 
 @pytest.mark.parametrize("n,d,o,w", [(11, 3, "grlex", -1), (17, 4, "grevlex", -1), (17, 3, "grlex", 7),
-                                     (15, 4, "grevlex", 6)])
+                                     (15, 4, "grevlex", 6),
+                                     (12, 5, "grevlex", -1), (17, 6, "grlex", -1), (16, 5, "grevlex", 8),
+                                     (14, 6, "grlex", 6)])
 def test_ranges_and_prefixes(n, d, o, w):
     total = gc.problem_positions(gc.problem(n, d, o, weight=w))
     full, _ = both(gc.problem(n, d, o, weight=w))
@@ -72,13 +88,14 @@ def test_ranges_and_prefixes(n, d, o, w):
         assert np.array_equal(got, ref)
 
 
-def test_capacity_keeps_the_beginning_and_nothing_past_it(cuda):
-    full, _ = both(gc.problem(17, 3, "grlex"))
-    for cap in (1, 2, 1001, len(full) - 1):
+@pytest.mark.parametrize("d", [3, 5])
+def test_capacity_keeps_the_beginning_and_nothing_past_it(cuda, d):
+    full, _ = both(gc.problem(17, d, "grlex"))
+    for cap in (1, 2, 101, len(full) - 1):
         words = cuda.full((cap + 8,), -1, dtype=cuda.int32, device="cuda")
         count = cuda.zeros(1, dtype=cuda.int64, device="cuda")
         with pytest.raises(gc.GreedyCodeError) as e:
-            gc.greedy_code_device(17, 3, "grlex", words[:cap], count)
+            gc.greedy_code_device(17, d, "grlex", words[:cap], count)
         assert e.value.rc == gc.GC_ECAPACITY and int(count.item()) == cap
         got = words.cpu().numpy().view(np.uint32)
         assert np.array_equal(got[:cap], full[:cap]) and (got[cap:] == 0xFFFFFFFF).all()
@@ -86,7 +103,7 @@ def test_capacity_keeps_the_beginning_and_nothing_past_it(cuda):
 
 @pytest.mark.parametrize("teams", [1, 2, 4, 8])
 def test_batch(teams):
-    jobs = [(n, d, o) for o in ("grlex", "grevlex") for n, d in [(3, 2), (9, 3), (16, 4), (17, 3), (20, 4)]]
+    jobs = [(n, d, o) for o in ("grlex", "grevlex") for n, d in [(3, 2), (9, 3), (16, 4), (17, 3), (20, 4), (8, 5), (15, 6), (18, 5)]]
     log(f"[cover] batch teams={teams}")
     words, _, _ = gc.greedy_code_batch(jobs, teams=teams)
     for (n, d, o), w in zip(jobs, words):
