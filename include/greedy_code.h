@@ -84,8 +84,8 @@ typedef struct gc_stats {
 /* Tuning knobs (optional input; zero fields take the built-in defaults).
  * The greedy codes of GC_LEX, GC_GRAY and GC_BORDER walks (self-orthogonal
  * ones included, a weight not) are linear; with every field zero they are
- * built from their generators.  GC_GRLEX and GC_GREVLEX codes (a weight too,
- * not self-orthogonal) of n <= 24 are built by marking the ball of each
+ * built from their generators.  GC_GRLEX and GC_GREVLEX codes (a weight and
+ * self-orthogonal ones too) of n <= 24 are built by marking the ball of each
  * accepted word in a bitmap of the space.  Any field set asks
  * for the windowed screens, which build the same code. */
 typedef struct gc_tuning {
@@ -315,13 +315,16 @@ int greedy_code_batch_tune(gc_job *jobs, int njobs, void *hip_stream, int *best_
  * for its worst-case code (greedy_code_capacity(n, d) words); admitted jobs
  * go to a queue in pinned host memory that the running kernel's teams pull
  * from, so a job arriving while others build starts as soon as a team frees
- * up.  With teams 2 or 4, a job whose exhaustive work bound
- * 2^n * greedy_code_capacity(n, d) is at least 2^38 ("wide") goes to a wide
- * queue, served by one team spanning 8 - teams of the eight XCDs; the other
- * jobs go to a narrow queue, served by `teams` teams of one XCD each and by
- * the wide team whenever no wide job waits.  Each queue runs in arrival
- * order; narrow jobs never wait behind a wide one, and may be admitted past a
- * wide job that waits for arena space until it has waited 1 s.  Finished
+ * up.  With teams 2 or 4, every XCD is a team of its own while no "wide" job
+ * is open: one that the windowed screens build (see gc_tuning) and whose
+ * exhaustive work bound 2^n * greedy_code_capacity(n, d) is at least 2^38.
+ * Wide jobs go to a wide queue; while one is open, one team spanning 8 - teams
+ * of the eight XCDs serves it, and the other jobs, in a narrow queue, are
+ * served by `teams` teams of one XCD each and by the wide team whenever no
+ * wide job waits (to change teams the kernel finishes the jobs it is building
+ * and is launched again).  Each queue runs in arrival order; narrow jobs never
+ * wait behind a wide one, and may be admitted past a wide job that waits for
+ * arena space until it has waited 1 s.  Finished
  * codes stay resident in the arena until released.  The kernel
  * exits after about 0.1 s without work and is relaunched on demand.  If a
  * bounded device-side wait expires, every unfinished job fails with
@@ -334,8 +337,9 @@ typedef struct gc_server gc_server;
  * as much pinned host memory: each finished code is written there by the
  * kernel itself, so fetching a result needs no device copy while the kernel
  * holds the GPU); teams: 1 (one team spanning the GPU) or 8 (one team per
- * XCD): every job in one queue, in arrival order; 2 or 4: the wide team of
- * 8 - teams XCDs plus `teams` narrow teams of one XCD. */
+ * XCD): every job in one queue, in arrival order; 2 or 4: one team per XCD,
+ * or while a wide job is open the wide team of 8 - teams XCDs plus `teams`
+ * narrow teams of one XCD. */
 int gc_server_create(size_t arena_bytes, int teams, gc_server **out);
 /* Queue a job; *ticket identifies it.  GC_ENOMEM if its worst-case code can
  * never fit the arena. */

@@ -46,6 +46,8 @@ struct CoverLds {
       alignas(16) uint32_t took[kCovWin];  // those accepted
       unsigned long long accm[kCovBlocks];   // accepted, by block of 64 candidates
       uint3 run[kCovLevels * kCovTeam];  // per (level, slice): place in the window, length, place in its list
+      uint32_t basis[32], pick;          // self-orthogonal: a basis of the code's span
+      int dim;
       unsigned int size, done_levels, listed;  // the window's candidates; levels it takes whole, and at all
     };
   };

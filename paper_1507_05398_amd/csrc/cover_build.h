@@ -123,8 +123,12 @@ __device__ __forceinline__ void cover_mark(CoverLds &C, const unsigned int (&w)[
 // Builds the job's code with the first `team` workgroups of the XCD (this one
 // is number `rank`); writes the words and the count.  Not inlined: the
 // screens' registers are not affected.
-__device__ __noinline__ void cover_team(CoverWs *ws, Ctl *ctl, unsigned int rank_v, unsigned int team_v, int *abort_flag,
+__device__ __noinline__ void cover_team(CoverWs *ws_v, Ctl *ctl_v, unsigned int rank_v, unsigned int team_v, int *abort_v,
                                         unsigned int limit) {
+  // Arguments are the same for every lane: pointers in scalar registers.
+  CoverWs *const ws = uniform_ptr(ws_v);
+  Ctl *const ctl = uniform_ptr(ctl_v);
+  int *const abort_flag = uniform_ptr(abort_v);
   Lds &L = g_lds;
   CoverLds &C = g_lds.cover;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -136,9 +140,9 @@ __device__ __noinline__ void cover_team(CoverWs *ws, Ctl *ctl, unsigned int rank
   const int hbits = __builtin_ctz(words);                              // word-index bits of a slice
   const unsigned int high = rank << hbits;
   const unsigned long long valid = n < 6 ? (1ull << (1 << n)) - 1 : ~0ull;
-  uint32_t *code = L.code;
-  const unsigned long long capacity = L.capacity, start = L.p_start, stop = L.total;
-  unsigned long long m = L.m_start;
+  uint32_t *const code = uniform_ptr(L.code);
+  const unsigned long long capacity = uniform64(L.capacity), start = uniform64(L.p_start), stop = uniform64(L.total);
+  unsigned long long m = uniform64(L.m_start);
   unsigned int rounds = 0;
 
   // Tables, and the empty slice.
@@ -536,15 +540,16 @@ __device__ __noinline__ void cover_team(CoverWs *ws, Ctl *ctl, unsigned int rank
 // their conflict graphs, so workgroups pay from 8 words each (n = 16, d = 5:
 // 220 us with 32, 294 us with one).  False (alike in every workgroup) when
 // the slices would not fit.
+template <bool kSelf>
 __device__ __forceinline__ bool build_cover(Lds &L, const Params &P, const TeamWs &W) {
   const unsigned int words = L.n > 6 ? 1u << (L.n - 6) : 1u, most = umin(L.sub_size, (unsigned int)kCovTeam);
-  const unsigned int least = L.d > kCovMaxD ? 8u : words > 1024 ? 512u : 1024u;  // words of a slice
+  const unsigned int least = kSelf || L.d > kCovMaxD ? 8u : words > 1024 ? 512u : 1024u;  // words of a slice
   unsigned int team = 1;
   while (2 * team <= most && words / (2 * team) >= least) team *= 2;
   if (words / team > (unsigned int)kCovWords) return false;
   if (L.sub_rank < team) {
-    if (L.d <= kCovMaxD) cover_team(W.cover, W.ctl, L.sub_rank, team, &P.dq->abort, P.spin_limit);
-    else cover_window_team(W.cover, W.ctl, L.sub_rank, team, &P.dq->abort, P.spin_limit);
+    if (!kSelf && L.d <= kCovMaxD) cover_team(W.cover, W.ctl, L.sub_rank, team, &P.dq->abort, P.spin_limit);
+    else cover_window_team<kSelf>(W.cover, W.ctl, L.sub_rank, team, &P.dq->abort, P.spin_limit);
   }
   return true;
 }

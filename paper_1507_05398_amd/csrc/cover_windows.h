@@ -11,6 +11,11 @@
 // workgroup then marks the balls of the accepted words in its slice, which
 // removes every candidate of the window.  Two XCD-local barriers a window.
 //
+// Self-orthogonal codes (kSelf; every distance): a pair clashes also when its
+// overlap is odd, and of the words accepted so far a basis is kept.  A new
+// basis word (at most n / 2 times) removes the candidates it overlaps oddly
+// from the bitmap, a word of 64 at a time.
+//
 // What bounds it: about 25 us a window at n = 22, d = 5 (listing 4, waiting
 // for the busiest slice 4, gathering 2.4, graph 2.5, choice 6.5, marks 4), and
 // from n = 24 on the LDS throughput of the marks, uneven over the slices: a
@@ -21,8 +26,13 @@
 
 // Bits 0 .. 63: which of the 64 words at `w` (broadcast reads) are closer than
 // d to x.  XOR, a population count that starts at -d, and its sign shifted
-// into the mask.
-__device__ __forceinline__ unsigned long long clash_mask(const uint32_t *w, uint32_t x, int d) {
+// into the mask.  kSelf: or have an odd overlap with it, counted from `odd`.
+template <bool kSelf>
+__device__ __forceinline__ unsigned long long clash_mask(const uint32_t *w, uint32_t x, int d, unsigned int odd) {
+  auto sign = [&](uint32_t y) {
+    const unsigned int t = (unsigned int)(__builtin_popcount(x ^ y) - d);
+    return kSelf ? t | ((__builtin_popcount(x & y) + odd) << 31) : t;
+  };
   unsigned int half[2];
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
@@ -31,18 +41,23 @@ __device__ __forceinline__ unsigned long long clash_mask(const uint32_t *w, uint
 #pragma unroll
     for (int q = 7; q >= 0; --q) {
       const uint4 c = v[q];
-      m = __builtin_amdgcn_alignbit(m, (unsigned int)(__builtin_popcount(x ^ c.w) - d), 31);
-      m = __builtin_amdgcn_alignbit(m, (unsigned int)(__builtin_popcount(x ^ c.z) - d), 31);
-      m = __builtin_amdgcn_alignbit(m, (unsigned int)(__builtin_popcount(x ^ c.y) - d), 31);
-      m = __builtin_amdgcn_alignbit(m, (unsigned int)(__builtin_popcount(x ^ c.x) - d), 31);
+      m = __builtin_amdgcn_alignbit(m, sign(c.w), 31);
+      m = __builtin_amdgcn_alignbit(m, sign(c.z), 31);
+      m = __builtin_amdgcn_alignbit(m, sign(c.y), 31);
+      m = __builtin_amdgcn_alignbit(m, sign(c.x), 31);
     }
     half[h] = m;
   }
   return ((unsigned long long)half[1] << 32) | half[0];
 }
 
-__device__ __noinline__ void cover_window_team(CoverWs *ws, Ctl *ctl, unsigned int rank_v, unsigned int team_v,
-                                               int *abort_flag, unsigned int limit) {
+template <bool kSelf>
+__device__ __noinline__ void cover_window_team(CoverWs *ws_v, Ctl *ctl_v, unsigned int rank_v, unsigned int team_v,
+                                               int *abort_v, unsigned int limit) {
+  // Arguments are the same for every lane: pointers in scalar registers.
+  CoverWs *const ws = uniform_ptr(ws_v);
+  Ctl *const ctl = uniform_ptr(ctl_v);
+  int *const abort_flag = uniform_ptr(abort_v);
   Lds &L = g_lds;
   CoverLds &C = g_lds.cover;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -54,9 +69,12 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws, Ctl *ctl, unsigned i
   const int hbits = __builtin_ctz(words);
   const unsigned int high = rank << hbits;
   const unsigned long long valid = n < 6 ? (1ull << (1 << n)) - 1 : ~0ull;
-  uint32_t *code = L.code;
-  const unsigned long long capacity = L.capacity, start = L.p_start, stop = L.total;
-  unsigned long long m = L.m_start;
+  uint32_t *const code = uniform_ptr(L.code);
+  const unsigned long long capacity = uniform64(L.capacity), start = uniform64(L.p_start), stop = uniform64(L.total);
+  unsigned long long m = uniform64(L.m_start);
+  // Overlap of two even words by their numbers: the bits both have, plus n
+  // for complemented ones.
+  const unsigned int odd = rev ? (unsigned int)n & 1u : 0u, all_bits = (1u << n) - 1u;
 
   // Tables: differences of the word index by weight (C(hbits, j) of weight j),
   // balls, level masks; the empty slice.
@@ -68,6 +86,7 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws, Ctl *ctl, unsigned i
       of = j < hbits ? of * (unsigned int)(hbits - j) / (unsigned int)(j + 1) : 0;
     }
     C.epoch = 0;
+    C.dim = C.pick = 0;
   }
   if (tid < 8 * 64) {
     unsigned long long b = 0;
@@ -94,18 +113,19 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws, Ctl *ctl, unsigned i
   }
   __syncthreads();
 
-  // Marks the balls around four numbers (uniform), by one wave: a lane takes a
-  // difference of the word index for all of them.  Instructions bound this
+  // Marks the balls around four numbers (uniform; `past`: distance that lies
+  // past the n bits), by one wave: a lane takes a difference of the word index
+  // for all of them.  Instructions bound this
   // loop, so a mark is few of them: the slice's byte offset is one XOR, the
   // ball's row one sum and one clamp (row 0, radius -1, is empty: differences
   // of too much weight need no test).
-  auto mark4 = [&](const uint32_t (&c)[4], int have) {
+  auto mark4 = [&](const uint32_t (&c)[4], int have, const int (&past)[4]) {
     int row[4];
     unsigned int at[4], most = 0;
     unsigned int bit[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int r = q < have ? d - 1 - __builtin_popcount((c[q] >> 6 >> hbits) ^ rank) : -1;
+      const int left = d - 1 - past[q] - __builtin_popcount((c[q] >> 6 >> hbits) ^ rank), r = q < have && left >= 0 ? left : -1;
       row[q] = 64 * (r + 1);
       at[q] = (c[q] >> 6) & (words - 1);
       bit[q] = c[q] & 63;
@@ -127,24 +147,68 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws, Ctl *ctl, unsigned i
         __hip_atomic_fetch_or(&C.dead[at[q] ^ diff], b[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
   };
-  // Words accepted before `start`: their first n bits, as on the matrix screens.
+  // kSelf: candidates with an odd overlap with one of the words whose reversed
+  // (grevlex) or plain bits are `b` (one a thread, 0: none) leave the bitmap;
+  // the bitmap is not marked meanwhile.  The words' span is kept as a basis,
+  // each vector without the top bits of those before it.
+  auto keep_orthogonal = [&](uint32_t b) {
+    for (;;) {
+      const int dim = C.dim;
+      for (int i = 0; i < dim; ++i)
+        if ((b >> (31 - __builtin_clz(C.basis[i]))) & 1) b ^= C.basis[i];
+      if (b) atomicMax(&C.pick, b);
+      __syncthreads();
+      const uint32_t pick = C.pick;
+      if (pick == 0) break;
+      __syncthreads();
+      if (tid == 0) {
+        C.basis[dim] = pick;
+        C.dim = dim + 1;
+        C.pick = 0;
+      }
+      constexpr unsigned long long in[6] = {0xaaaaaaaaaaaaaaaaull, 0xccccccccccccccccull, 0xf0f0f0f0f0f0f0f0ull,
+                                            0xff00ff00ff00ff00ull, 0xffff0000ffff0000ull, 0xffffffff00000000ull};
+      unsigned long long low = rev && (__builtin_popcount(pick) & 1) ? ~0ull : 0ull;
+#pragma unroll
+      for (int j = 0; j < 6; ++j) low ^= (pick >> j) & 1 ? in[j] : 0ull;
+      for (unsigned int i = tid; i < words; i += kBlock)
+        C.dead[i] |= __builtin_popcount((high + i) & (pick >> 6)) & 1 ? ~low : low;
+      __syncthreads();
+    }
+  };
+  // Words accepted before `start`: their first n bits as on the matrix
+  // screens; self-orthogonal codes count the others in the distance, as the
+  // screens of the vector ALU do.
   for (unsigned long long i = 4 * wave; i < m; i += 4 * kWaves) {
     uint32_t c[4];
+    int past[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) c[q] = cover_number(code[i + q < m ? i + q : i] & ((1u << n) - 1u), n, rev);
-    mark4(c, m - i < 4 ? (int)(m - i) : 4);
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t x = code[i + q < m ? i + q : i];
+      c[q] = cover_number(x & all_bits, n, rev);
+      past[q] = kSelf ? __builtin_popcount(x >> n) : 0;
+    }
+    mark4(c, m - i < 4 ? (int)(m - i) : 4, past);
   }
+  __syncthreads();
+  if (kSelf)
+    for (unsigned long long i = 0; i < m; i += kBlock) {
+      const uint32_t x = i + tid < m ? code[i + tid] & all_bits : 0u;
+      keep_orthogonal(rev ? __builtin_bitreverse32(x) >> (32 - n) : x);
+    }
 
   // Walk levels with positions in [start, stop); candidates outside are none.
   int first = n + 1, last = -1;
+  unsigned int walked = 0;  // levels with candidates, by the weight of their numbers
   for (int w = 0; w <= n; ++w) {
     const unsigned long long at = L.tab.off[w], end = L.tab.off[w + 1];
     const unsigned long long lo = start > at ? start - at : 0, hi = stop < end ? (stop > at ? stop - at : 0) : end - at;
     if (lo >= hi) continue;
     if (first > n) first = w;
     last = w;
-    if (lo == 0 && hi == end - at) continue;
     const int k = rev ? n - w : w;
+    walked |= 1u << k;
+    if (lo == 0 && hi == end - at) continue;
     const unsigned long long from = lo > 0 ? unrank_weight(L.tab, lo, k, n) : 0;
     const unsigned long long to = hi < end - at ? unrank_weight(L.tab, hi, k, n) : 1ull << n;
     __syncthreads();  // the marks: a word's bits are set here without an atomic
@@ -158,6 +222,21 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws, Ctl *ctl, unsigned i
   }
   __syncthreads();
 
+  if (walked != (2u << n) - 1u) {
+    for (unsigned int i = tid; i < words; i += kBlock) {
+      unsigned long long none = 0;
+      for (int j = 0; j <= 6; ++j)
+        if (!((walked >> (__builtin_popcount(high + i) + j)) & 1)) none |= C.level[32 + j];
+      C.dead[i] |= none;
+    }
+    __syncthreads();
+  }
+  // Clock cycles of an accepted word's marks (a third of a cycle each, the
+  // ball's words even over the slices), of one comparison of 1024 candidates
+  // with a word, and of listing 1024 candidates.
+  unsigned int near_words = 0;
+  for (int j = 0; j < d && j <= n - 6; ++j) near_words += L.tab.binom[n - 6][j];
+  const unsigned int mark_cost = near_words / (3u * team), compare_cost = 48, list_cost = 8000;
   const unsigned int per = (words + kBlock - 1) / kBlock, w0 = tid * per;
   // A slice stops listing further levels once it has more than its share of a
   // window (a window takes a level only if every slice has listed it).
@@ -254,7 +333,7 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws, Ctl *ctl, unsigned i
       unsigned int I = 0;
       while ((I + 1) * (I + 2) / 2 <= t) ++I;
       const unsigned int J = t - I * (I + 1) / 2, j = 64 * I + lane;
-      unsigned long long mask = clash_mask(&C.cand[64 * J], C.cand[j], d);
+      unsigned long long mask = clash_mask<kSelf>(&C.cand[64 * J], C.cand[j], d, odd);
       mask &= I == J ? lanemask_lt() : ~0ull;
       if (j >= size) mask = 0;
       as_global(ws->adj)[64 * t + lane] = mask;
@@ -304,13 +383,61 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws, Ctl *ctl, unsigned i
     __syncthreads();
     m += all;
     if (m > capacity) break;
-    for (unsigned int i = 4 * wave; i < all; i += 4 * kWaves) {
-      const uint4 t = *reinterpret_cast<const uint4 *>(&C.took[i]);
-      const uint32_t c[4] = {(uint32_t)__builtin_amdgcn_readfirstlane((int)t.x), (uint32_t)__builtin_amdgcn_readfirstlane((int)t.y),
-                             (uint32_t)__builtin_amdgcn_readfirstlane((int)t.z), (uint32_t)__builtin_amdgcn_readfirstlane((int)t.w)};
-      mark4(c, all - i < 4 ? (int)(all - i) : 4);
+    // With few candidates left in the slice their distances to the accepted
+    // words cost less than the marks (n = 24, d = 8, self-orthogonal: 0.70 ms
+    // against 2.0 ms with marks alone).
+    unsigned int undecided = 0, mine_at = 0;
+    bool compare = false;
+    if (all * mark_cost > list_cost + all * compare_cost) {
+      unsigned int mine = 0;
+      for (unsigned int i = w0; i < w0 + per && i < words; ++i) mine += (unsigned int)__builtin_popcountll(~C.dead[i]);
+      const unsigned int at = wave_scan(mine);
+      if (lane == 63) C.wsum[wave] = at;
+      __syncthreads();
+      mine_at = at - mine;
+#pragma unroll
+      for (int wv = 0; wv < kWaves; ++wv) {
+        if (wv < wave) mine_at += C.wsum[wv];
+        undecided += C.wsum[wv];
+      }
+      const unsigned int passes = undecided / kCovWin + 1;
+      compare = all * mark_cost > passes * (list_cost + all * compare_cost);
+    }
+    if (compare) {
+      if (tid < 4 && all + tid < ((all + 3) & ~3u)) C.took[all + tid] = C.took[all - 1];
+      // 1024 at a time, the last ones first: what they lose does not move the
+      // places of those before them.
+      for (unsigned int c1 = (undecided + kCovWin - 1) / kCovWin; c1 > 0; --c1) {
+        const unsigned int c0 = (c1 - 1) * kCovWin;
+        __syncthreads();
+        unsigned int at = mine_at;
+        for (unsigned int i = w0; i < w0 + per && i < words; ++i)
+          for (unsigned long long f = ~C.dead[i]; f; f &= f - 1, ++at)
+            if (at - c0 < (unsigned int)kCovWin) C.cand[at - c0] = 64u * (high + i) + __builtin_ctzll(f);
+        __syncthreads();
+        if (c0 + tid < undecided) {
+          const uint32_t x = C.cand[tid];
+          unsigned int least = ~0u;
+          for (unsigned int i = 0; i < all; i += 4) {
+            const uint4 t = *reinterpret_cast<const uint4 *>(&C.took[i]);
+            least = umin3(least, dist(x, t.x), dist(x, t.y));
+            least = umin3(least, dist(x, t.z), dist(x, t.w));
+          }
+          if (least < (unsigned int)d)
+            __hip_atomic_fetch_or(&C.dead[(x >> 6) & (words - 1)], 1ull << (x & 63), __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+      }
+    } else {
+      for (unsigned int i = 4 * wave; i < all; i += 4 * kWaves) {
+        const uint4 t = *reinterpret_cast<const uint4 *>(&C.took[i]);
+        const uint32_t c[4] = {(uint32_t)__builtin_amdgcn_readfirstlane((int)t.x), (uint32_t)__builtin_amdgcn_readfirstlane((int)t.y),
+                               (uint32_t)__builtin_amdgcn_readfirstlane((int)t.z), (uint32_t)__builtin_amdgcn_readfirstlane((int)t.w)};
+        mark4(c, all - i < 4 ? (int)(all - i) : 4, {0, 0, 0, 0});
+      }
     }
     __syncthreads();
+    if (kSelf) keep_orthogonal((unsigned int)tid < all ? (rev ? ~C.took[tid] & all_bits : C.took[tid]) : 0u);
     level += (int)complete;
     par ^= 1;
     // Every window decides its candidates and passes levels without any: the

@@ -4,6 +4,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <string>
@@ -33,6 +34,8 @@ struct Job {
                                   // before `done` is set (may be null)
   int wclass;                     // 0: every weight is a candidate; w + 1: only weight w
   int so;                         // 1: self-orthogonal (even weights, even common ones)
+  int linear;                     // 1 if the code may be built from its generators
+  int cover;                      // 1 if it may be built by cover marks
   unsigned long long p_start;     // first position screened
   unsigned long long p_stop;      // end of the screened positions (0: the walk's end)
   unsigned long long m_start;     // words already in `code` (accepted before p_start)
@@ -45,9 +48,9 @@ struct Job {
   int status;
   unsigned int done;              // 0 pending, 1 finished (written last)
   int wide;                       // server: queued on the wide ring
-  int linear;                     // input: 1 if the code may be built from its generators
-  int cover;                      // input: 1 if it may be built by cover marks
 };
+constexpr int kJobInputWords = 64;  // the inputs, in 32-bit words (at most)
+static_assert(offsetof(Job, out_count) <= 4 * kJobInputWords, "job inputs outgrow their copy");
 
 // Job queue.  `submitted` and `shutdown` may live in host memory (server);
 // `claimed` and `abort` always live in device memory.
@@ -55,7 +58,8 @@ struct HostQueue {
   unsigned int submitted;   // batch: jobs visible to the device; server: entries of the narrow ring
   unsigned int shutdown;    // host sets 1: the kernel exits when idle
   unsigned int submitted_wide;  // server: entries of the wide ring
-  unsigned int pad[61];
+  unsigned int layout;      // server: a launch whose Params::layout differs exits before its next job
+  unsigned int pad[60];
 };
 
 struct DevQueue {
@@ -82,14 +86,12 @@ struct Ctl {
   unsigned int pad[23];
 };
 
-// Barrier state: per XCD a counter, a generation and the member count (each
-// on its own 256-byte line); per team a counter and generation for the XCD
-// leaders; a one-time join count.
+// Barrier state, cleared before a launch: per XCD a counter and the member
+// count (each XCD on its own 256-byte line); per team a counter for the XCD
+// leaders and the generation.
 struct Bar {
-  unsigned int join_count;
-  unsigned int pad0[63];
-  unsigned int xcd[kMaxXcd][64];     // [0] count, [1] generation, [2] members
-  unsigned int team[kMaxTeams][64];  // [0] count, [1] generation, [2] members, [3] xcds
+  unsigned int xcd[kMaxXcd][64];     // [0] arrivals, [2] members
+  unsigned int team[kMaxTeams][64];  // [0] XCD arrivals, [1] generation
 };
 
 struct Params {
@@ -105,6 +107,7 @@ struct Params {
   // 0: teams are XCD id mod nteams and claim one queue (batch, or a one-team
   // server).
   int split;
+  unsigned int layout;           // server: HostQueue::layout at the launch
   unsigned int *ring;            // server: job indices in publication order (narrow jobs)
   unsigned int *ring_wide;       // server: job indices of the wide jobs
   unsigned int spin_limit;       // bounded waits inside a job

@@ -112,6 +112,7 @@ struct TeamWs {
   uint32_t *deep_word;       // kSMax
   uint32_t *deep_idx;        // kSMax
   uint32_t *deep_fail;       // kSMax / 32
+  uint32_t *job;             // inputs of the job being built
   LinResult *lin;            // linear codes: the generators
   unsigned long long *lin_bits;  // kLinTeamWords: label bitmaps past LDS
   CoverWs *cover;            // graded codes of small distance
@@ -140,7 +141,8 @@ constexpr size_t kOffDfail = kOffDidx + align256(kSMax * sizeof(uint32_t));
 // needs more leaves its code to the screens).
 constexpr int kLinLdsWords = 2048;
 constexpr unsigned int kLinTeamWords = 49152;
-constexpr size_t kOffLin = kOffDfail + align256(kSMax / 32 * sizeof(uint32_t));
+constexpr size_t kOffJob = kOffDfail + align256(kSMax / 32 * sizeof(uint32_t));
+constexpr size_t kOffLin = kOffJob + align256(kJobInputWords * sizeof(uint32_t));
 constexpr size_t kOffLinBits = kOffLin + align256(sizeof(LinResult));
 constexpr size_t kOffCover = kOffLinBits + align256(kLinTeamWords * sizeof(unsigned long long));
 constexpr size_t kTeamWsBytes = kOffCover + align256(sizeof(CoverWs));
@@ -155,6 +157,7 @@ __host__ __device__ inline TeamWs team_ws(char *base) {
   w.deep_word = reinterpret_cast<uint32_t *>(base + kOffDword);
   w.deep_idx = reinterpret_cast<uint32_t *>(base + kOffDidx);
   w.deep_fail = reinterpret_cast<uint32_t *>(base + kOffDfail);
+  w.job = reinterpret_cast<uint32_t *>(base + kOffJob);
   w.lin = reinterpret_cast<LinResult *>(base + kOffLin);
   w.lin_bits = reinterpret_cast<unsigned long long *>(base + kOffLinBits);
   w.cover = reinterpret_cast<CoverWs *>(base + kOffCover);
@@ -212,9 +215,9 @@ struct Lds {
   Tables tab;
   Walk walk;
   // job
+  alignas(8) uint32_t in[kJobInputWords];  // its inputs (the beginning of a Job)
   int job, n, d, ord, mode;
   uint32_t *code;
-  uint32_t *host_copy;                 // server: pinned host copy of the words (or null)
   unsigned long long capacity, total, near_depth;
   unsigned long long p_start, m_start, classes;
   unsigned int target, deep_tile;
@@ -283,6 +286,11 @@ __device__ __forceinline__ unsigned long long uniform64(unsigned long long x) {
   const unsigned int lo = __builtin_amdgcn_readfirstlane((unsigned int)x);
   const unsigned int hi = __builtin_amdgcn_readfirstlane((unsigned int)(x >> 32));
   return ((unsigned long long)hi << 32) | lo;
+}
+
+template <typename T>
+__device__ __forceinline__ T *uniform_ptr(T *p) {
+  return reinterpret_cast<T *>(uniform64(reinterpret_cast<unsigned long long>(p)));
 }
 
 __device__ __forceinline__ unsigned long long lanemask_lt() {
@@ -365,53 +373,59 @@ __device__ __forceinline__ unsigned int team_of(const Params &P, unsigned int x)
   return r < w ? 0u : 1u + (r - w) % (unsigned int)(P.nteams - 1);
 }
 
-// One-time registration: every workgroup counts itself on its XCD and takes a
-// rank in its team, then all wait until the whole grid has registered.  No
-// assumption is made about the block -> XCD mapping.
+// One-time registration: every workgroup counts itself on its XCD, then all
+// wait until the XCDs' counts add up to the grid.  No assumption is made about
+// the block -> XCD mapping.  A workgroup's rank in its team follows from the
+// counts of the team's lower XCDs: one atomic a workgroup, at most 32 on one
+// address (with a team counter and a join counter besides, 256 workgroups each
+// on one address, a launch of one code took 18 us more).
 __device__ __forceinline__ void team_join(Lds &L, const Params &P) {
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 64) {
     Bar *B = P.bar;
-    const unsigned int x = xcc_id();
-    const unsigned int t = team_of(P, x);
-    const unsigned int xcd_rank =
-        __hip_atomic_fetch_add(&B->xcd[x][2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned int rank =
-        __hip_atomic_fetch_add(&B->team[t][2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_fetch_add(&B->join_count, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    unsigned int spins = 0;
-    while (ld_relaxed(&B->join_count) < gridDim.x) {
+    const unsigned int lane = threadIdx.x;
+    const unsigned int x = xcc_id(), t = team_of(P, x);
+    unsigned int xcd_rank = 0;
+    if (lane == 0)
+      xcd_rank = __hip_atomic_fetch_add(&B->xcd[x][2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned int members = 0, all = 0, spins = 0;
+    for (;;) {
+      members = lane < (unsigned int)kMaxXcd ? ld_relaxed(&B->xcd[lane][2]) : 0u;
+      all = (unsigned int)__builtin_amdgcn_readlane((int)wave_scan(members), 63);
+      if (all >= gridDim.x) break;
       __builtin_amdgcn_s_sleep(1);
       if (++spins > P.spin_limit) {
-        set_abort(P);
+        if (lane == 0) set_abort(P);
         break;
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     // The team's XCDs, and the one with the most members (the lowest of
     // several), where jobs that want one L2 are built.
-    unsigned int nx = 0, sub = 0, sub_size = 0;
-    for (int i = 0; i < kMaxXcd; ++i)
-      if (team_of(P, (unsigned int)i) == t) {
-        const unsigned int members = ld_relaxed(&B->xcd[i][2]);
-        nx += members > 0;
-        if (members > sub_size) {
-          sub = (unsigned int)i;
-          sub_size = members;
-        }
+    const bool ours = members > 0 && team_of(P, lane) == t;
+    const unsigned int mine = ours ? members : 0u, upto = wave_scan(mine);
+    unsigned int sub = 0, sub_size = 0;
+    for (unsigned int i = 0; i < (unsigned int)kMaxXcd; ++i) {
+      const unsigned int m = (unsigned int)__builtin_amdgcn_readlane((int)mine, (int)i);
+      if (m > sub_size) {
+        sub = i;
+        sub_size = m;
       }
-    L.sub_size = sub_size;
-    L.sub_rank = x == sub ? xcd_rank : ~0u;
-    L.xcd = x;
-    L.xcd_members = ld_relaxed(&B->xcd[x][2]);
-    L.team = t;
-    L.team_rank = rank;
-    L.team_size = ld_relaxed(&B->team[t][2]);
-    L.team_xcds = nx;
-    // No team barrier of this launch can complete before every member has
-    // joined, so all members read the same generation here and then count
-    // the barriers they pass.
-    L.tgen = ld_relaxed(&B->team[t][1]);
-    L.abort = ld_relaxed(&P.dq->abort);
+    }
+    const unsigned int before = (unsigned int)__builtin_amdgcn_readlane((int)(upto - mine), (int)x);
+    const unsigned int here = (unsigned int)__builtin_amdgcn_readlane((int)mine, (int)x);
+    const unsigned int xcds = (unsigned int)__builtin_popcountll(ballot(ours));
+    const unsigned int size = (unsigned int)__builtin_amdgcn_readlane((int)upto, 63);
+    if (lane == 0) {
+      L.xcd = x;
+      L.xcd_members = here;
+      L.team = t;
+      L.team_rank = before + xcd_rank;
+      L.team_size = size;
+      L.team_xcds = xcds;
+      L.sub_size = sub_size;
+      L.sub_rank = x == sub ? xcd_rank : ~0u;
+      L.tgen = 0;  // the launch starts with the barrier block cleared
+      L.abort = ld_relaxed(&P.dq->abort);
+    }
   }
   __syncthreads();
 }
@@ -421,13 +435,16 @@ __device__ __forceinline__ void team_join(Lds &L, const Params &P) {
 // writes visible device-wide (release) and counts the XCD on the team
 // counter; the last XCD leader bumps the team's generation.  Every workgroup
 // waits for that generation to change and then acquires at agent scope
-// before it reads data written elsewhere.  The generation a workgroup waits
-// on is its own count of the barriers it has passed (every member passes
-// every barrier, and none completes before all have arrived), so no load
-// precedes the arrival.  The kernel-wide abort flag is read on arrival, so
-// its round trip overlaps the wait (an abort raised meanwhile is seen at the
-// next wait, where the workgroups still running time out anyway); a wait
-// that expires aborts by itself.  Waits are bounded by `limit` polls.
+// before it reads data written elsewhere.  The counters only grow: the last
+// arrival is the one that brings a count to (barriers passed + 1) x members
+// (resetting them put two more round trips on the last arriver's path), and
+// the generation a workgroup waits for is its own count of the barriers it
+// has passed (every member passes every barrier, and none completes before
+// all have arrived), so no load precedes the arrival.  The kernel-wide abort
+// flag is read on arrival, so its round trip overlaps the wait (an abort
+// raised meanwhile is seen at the next wait, where the workgroups still
+// running time out anyway); a wait that expires aborts by itself.  Waits are
+// bounded by `limit` polls.
 __device__ __forceinline__ void team_barrier(Lds &L, const Params &P, unsigned int limit) {
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
@@ -439,12 +456,13 @@ __device__ __forceinline__ void team_barrier(Lds &L, const Params &P, unsigned i
     const unsigned int tg = L.tgen;
     const int aborted = ld_relaxed(&P.dq->abort);
     const unsigned int a = __hip_atomic_fetch_add(xc, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (a + 1 == L.xcd_members) {
-      __hip_atomic_store(xc, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned int b = __hip_atomic_fetch_add(tc, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-      if (b + 1 == L.team_xcds) {
-        __hip_atomic_store(tc, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (a + 1 == (tg + 1) * L.xcd_members) {
+      if (L.team_xcds == 1) {
         __hip_atomic_fetch_add(tgp, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      } else {
+        const unsigned int b = __hip_atomic_fetch_add(tc, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        if (b + 1 == (tg + 1) * L.team_xcds)
+          __hip_atomic_fetch_add(tgp, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
     const bool passed = wait_change(tgp, tg, P, limit);
@@ -1535,6 +1553,7 @@ __device__ int claim_job(const Params &P, unsigned int team) {
   for (;;) {
     if (ld_relaxed(&P.dq->abort)) return -1;
     if (ld_sys(&P.hq->shutdown)) return -1;  // outstanding jobs are abandoned
+    if (ld_sys(&P.hq->layout) != P.layout) return -1;  // the host wants other teams: it launches again
     int j = -1;
     if (P.split && team == 0 && take(&P.hq->submitted_wide, &P.dq->claimed_wide, P.ring_wide, &j)) return j;
     if (take(&P.hq->submitted, &P.dq->claimed, P.ring, &j)) return j;
@@ -1562,24 +1581,36 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
   bool screened = true;  // the window masks may hold the previous job's (or launch's) bits
   while (!L.abort) {
     // The state of the job to come, before the barrier that starts it (every
-    // workgroup has left the previous job): the window masks and cursors
-    // clear, the team's control block from the claimed job.
-    if (L.team_rank == 0 && tid == 0) {
-      const int j = claim_job(P, L.team);
-      Ctl *c = W.ctl;
-      c->job = j;
+    // workgroup has left the previous job): the team's first workgroup claims
+    // it and copies its inputs to the team's workspace, all words at once (the
+    // job may be in host memory, where a field by field read by every
+    // workgroup costs a round trip each); the window masks and cursors clear.
+    if (L.team_rank == 0 && tid < 64) {
+      int j = -1;
+      if (tid == 0) j = claim_job(P, L.team);
+      j = __builtin_amdgcn_readfirstlane(j);
       if (j >= 0) {
-        Job *J = &P.jobs[j];
-        st_sys(&J->t_claim, (unsigned long long)wall_clock64());
-        c->m = ld_sys(&J->m_start);
-        c->p = ld_sys(&J->p_start);
-        c->w = kWMin;
-        c->status = 0;
-        c->action = ACT_NEXT;
-        c->ndeep = 0;
-        c->stat_windows = c->stat_rounds = c->stat_surv = 0;
-        c->stat_near = c->stat_deep = c->stat_pairs = 0;
-        c->ticks[0] = c->ticks[1] = c->ticks[2] = c->ticks[3] = 0;
+        const uint32_t v = ld_sys(reinterpret_cast<uint32_t *>(&P.jobs[j]) + tid);
+        W.job[tid] = v;
+        L.in[tid] = v;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      }
+      if (tid == 0) {
+        Ctl *c = W.ctl;
+        c->job = j;
+        if (j >= 0) {
+          const Job &J = *reinterpret_cast<const Job *>(L.in);
+          st_sys(&P.jobs[j].t_claim, (unsigned long long)wall_clock64());
+          c->m = J.m_start;
+          c->p = J.p_start;
+          c->w = kWMin;
+          c->status = 0;
+          c->action = ACT_NEXT;
+          c->ndeep = 0;
+          c->stat_windows = c->stat_rounds = c->stat_surv = 0;
+          c->stat_near = c->stat_deep = c->stat_pairs = 0;
+          c->ticks[0] = c->ticks[1] = c->ticks[2] = c->ticks[3] = 0;
+        }
       }
     }
     if (screened) {
@@ -1597,50 +1628,50 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
     if (L.sub_rank == 0 && tid == 0)
       __hip_atomic_store(&W.cover->arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     team_barrier(L, P, claim_limit);
+    if (tid < kJobInputWords) L.in[tid] = ld_relaxed(&W.job[tid]);
     if (tid == 0) L.job = ld_relaxed(&W.ctl->job);
     __syncthreads();
     if (L.job < 0 || L.abort) break;
 
-    // Load the job (system-scope loads: the array may live in host memory).
+    const Job &J = *reinterpret_cast<const Job *>(L.in);
     if (tid == 0) {
-      Job *J = &P.jobs[L.job];
-      L.n = ld_sys(&J->n);
-      L.d = ld_sys(&J->d);
-      L.ord = ld_sys(&J->ord);
+      L.n = J.n;
+      L.d = J.d;
+      L.ord = J.ord;
       // Defaults by ordering (measured on the n=24..28 screens): graded
       // orders reject many candidates deep in the code, so they screen the
       // whole code up front; lex screens the newest 16K words and Gray the
       // newest 8K (where almost every rejected candidate meets its killer),
       // and both then deep-scan every survivor once.
       const bool graded = L.ord == GC_GRLEX || L.ord == GC_GREVLEX;
-      const int mode = ld_sys(&J->mode);
+      const int mode = J.mode;
       L.mode = mode ? mode : MODE_DEEP_ALL;
-      const unsigned long long nd = ld_sys(&J->near_depth);
+      const unsigned long long nd = J.near_depth;
       L.near_depth = nd ? nd : (graded ? ~0ull : (L.ord == GC_GRAY ? kDefaultNearGray : kDefaultNear));
-      const unsigned int tg = ld_sys(&J->target);
+      const unsigned int tg = J.target;
       L.target = tg ? (tg > (unsigned int)kSMax ? (unsigned int)kSMax : (tg < 16 ? 16 : tg))
                     : (graded ? kDefaultTarget : kDefaultTargetLinear);
-      L.code = ld_sys(&J->code);
-      L.capacity = ld_sys(&J->capacity);
-      const unsigned int dt = ld_sys(&J->deep_tile);
+      L.code = J.code;
+      L.capacity = J.capacity;
+      const unsigned int dt = J.deep_tile;
       L.deep_tile = dt ? dt : (unsigned int)kTile;
-      L.mfma = ld_sys(&J->valu_screen) == 0;
-      L.linear = ld_sys(&J->linear);
-      L.by_cover = ld_sys(&J->cover);
-      const int wclass = ld_sys(&J->wclass);
+      L.mfma = J.valu_screen == 0;
+      L.linear = J.linear;
+      L.by_cover = J.cover;
+      const int wclass = J.wclass;
       L.walk.n = L.n;
       L.walk.ord = L.ord;
-      L.walk.so = ld_sys(&J->so);
+      L.walk.so = J.so;
       // Allowed weight classes of a graded walk: one class (constant
       // weight), the even ones (self-orthogonal) or all of them.
       L.classes = wclass > 0 ? 1ull << (wclass - 1) : (L.walk.so ? 0x5555555555555555ull : ~0ull);
-      L.p_start = ld_sys(&J->p_start);
-      L.m_start = ld_sys(&J->m_start);
-      L.total = ld_sys(&J->p_stop);
+      L.p_start = J.p_start;
+      L.m_start = J.m_start;
+      L.total = J.p_stop;
       L.cnt_near = L.cnt_deep = L.cnt_pairs = 0;
     }
     __syncthreads();
-    init_tables(L.tab, L.walk, L.classes, P.jobs[L.job].basis);
+    init_tables(L.tab, L.walk, L.classes, J.basis);
     if (tid == 0) {
       // The walk's length: 2^n positions (2^(n-1) self-orthogonal) for the
       // positional walks, the sizes of the allowed classes for graded ones.
@@ -1650,13 +1681,13 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
     }
     __syncthreads();
     if (L.d <= 1 && !L.walk.so) emit_ordering(L, W);
-    else if ((!kLinear || !L.linear || !build_linear(L, P, W)) && (SO || !L.by_cover || !build_cover(L, P, W))) {
+    else if ((!kLinear || !L.linear || !build_linear(L, P, W)) && (!L.by_cover || !build_cover<SO>(L, P, W))) {
       build_code<SO>(L, P, W);
       screened = true;
     }
 
     __syncthreads();
-    if (tid == 0) {
+    if (tid == 0 && (L.cnt_near | L.cnt_deep | L.cnt_pairs) != 0) {  // (screens only: every workgroup on one address)
       __hip_atomic_fetch_add(&W.ctl->stat_near, L.cnt_near, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_fetch_add(&W.ctl->stat_deep, L.cnt_deep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_fetch_add(&W.ctl->stat_pairs, L.cnt_pairs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1668,18 +1699,20 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
     // them over the fabric (no copy engine or extra kernel is needed while this
     // kernel holds the GPU), then releases them at system scope before the
     // barrier that precedes `done`.
-    if (tid == 0) L.host_copy = ld_sys(&P.jobs[L.job].host_copy);
-    __syncthreads();
-    if (L.host_copy != nullptr && ld_relaxed(&W.ctl->status) == 0) {
+    if (J.host_copy != nullptr && ld_relaxed(&W.ctl->status) == 0) {
       const unsigned long long m = ld_relaxed(&W.ctl->m);
       const uint4 *src = reinterpret_cast<const uint4 *>(L.code);
-      uint4 *dst = reinterpret_cast<uint4 *>(L.host_copy);
+      uint4 *dst = reinterpret_cast<uint4 *>(J.host_copy);
       const unsigned long long stride = (unsigned long long)L.team_size * kBlock;
       for (unsigned long long k = (unsigned long long)L.team_rank * kBlock + tid; k < m / 4; k += stride)
         dst[k] = src[k];
       for (unsigned long long k = m / 4 * 4 + (unsigned long long)L.team_rank * kBlock + tid; k < m; k += stride)
-        L.host_copy[k] = L.code[k];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+        J.host_copy[k] = L.code[k];
+      // Released once per workgroup, after all of its waves' stores are done
+      // (by every wave it took some 20 us), and only where words were written.
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      if (tid == 0 && (unsigned long long)L.team_rank * kBlock < m / 4 + 4) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
       team_barrier(L, P, P.spin_limit);
       if (L.abort) break;
     }
@@ -1687,27 +1720,32 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
     // Completion: outputs first, then `done` with system-scope release, so a
     // host that sees done=1 also sees the words and the count.
     if (L.team_rank == 0 && tid == 0) {
-      Job *J = &P.jobs[L.job];
+      Job *out = &P.jobs[L.job];
       Ctl *c = W.ctl;
-      const unsigned long long m = ld_relaxed(&c->m);
-      unsigned long long *cnt = ld_sys(&J->count);
-      if (cnt) *cnt = m;
-      st_sys(&J->out_count, m);
-      st_sys(&J->windows, ld_relaxed(&c->stat_windows));
-      st_sys(&J->rounds, ld_relaxed(&c->stat_rounds));
-      st_sys(&J->survivors, ld_relaxed(&c->stat_surv));
-      st_sys(&J->chk_near, ld_relaxed(&c->stat_near));
-      st_sys(&J->chk_deep, ld_relaxed(&c->stat_deep));
-      st_sys(&J->chk_pairs, ld_relaxed(&c->stat_pairs));
-      st_sys(&J->ticks_near, ld_relaxed(&c->ticks[0]));
-      st_sys(&J->ticks_surv, ld_relaxed(&c->ticks[1]));
-      st_sys(&J->ticks_resolve, ld_relaxed(&c->ticks[2]));
-      st_sys(&J->ticks_deep, ld_relaxed(&c->ticks[3]));
-      st_sys(&J->status, ld_relaxed(&c->status));
-      st_sys(&J->t_done, (unsigned long long)wall_clock64());
+      // All reads first: one round trip.
+      const unsigned long long m = ld_relaxed(&c->m), windows = ld_relaxed(&c->stat_windows),
+                               rounds = ld_relaxed(&c->stat_rounds), survivors = ld_relaxed(&c->stat_surv),
+                               near = ld_relaxed(&c->stat_near), deep = ld_relaxed(&c->stat_deep),
+                               pairs = ld_relaxed(&c->stat_pairs), t0 = ld_relaxed(&c->ticks[0]),
+                               t1 = ld_relaxed(&c->ticks[1]), t2 = ld_relaxed(&c->ticks[2]), t3 = ld_relaxed(&c->ticks[3]);
+      const int status = ld_relaxed(&c->status);
+      if (J.count) *J.count = m;
+      st_sys(&out->out_count, m);
+      st_sys(&out->windows, windows);
+      st_sys(&out->rounds, rounds);
+      st_sys(&out->survivors, survivors);
+      st_sys(&out->chk_near, near);
+      st_sys(&out->chk_deep, deep);
+      st_sys(&out->chk_pairs, pairs);
+      st_sys(&out->ticks_near, t0);
+      st_sys(&out->ticks_surv, t1);
+      st_sys(&out->ticks_resolve, t2);
+      st_sys(&out->ticks_deep, t3);
+      st_sys(&out->status, status);
+      st_sys(&out->t_done, (unsigned long long)wall_clock64());
       // (A batch's host reads after the launch, which writes everything back.)
-      if (P.njobs_fixed >= 0) st_sys(&J->done, 1u);
-      else __hip_atomic_store(&J->done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+      if (P.njobs_fixed >= 0) st_sys(&out->done, 1u);
+      else __hip_atomic_store(&out->done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
       __hip_atomic_fetch_add(&P.dq->completed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (P.njobs_fixed == 1 && P.nteams == 1) break;  // a single code: no further claim
@@ -2088,7 +2126,7 @@ void fill_job(Job *J, int n, int d, int ordering, uint32_t *words, uint64_t capa
 }
 
 bool cover_job(const Job &J) {
-  return (J.ord == GC_GRLEX || J.ord == GC_GREVLEX) && !J.so && J.n <= kCovMaxN && J.d >= 2 &&
+  return (J.ord == GC_GRLEX || J.ord == GC_GREVLEX) && J.n <= kCovMaxN && (J.d >= 2 || J.so) &&
          J.near_depth == 0 && J.target == 0 && J.mode == 0 && J.deep_tile == 0 && J.valu_screen == 0;
 }
 

@@ -33,11 +33,14 @@ namespace gcimpl {
 
 constexpr unsigned int kServerSlots = 1u << 16;   // jobs over the life of one server
 constexpr unsigned int kServerIdlePolls = 50000;  // about 0.1 s of empty queue before the kernel exits
-// A job whose exhaustive work bound 2^n * capacity(n, d) reaches this is
-// "wide": it goes to the wide ring, which the team spanning half of the XCDs
-// serves first (on one XCD's team it would take up to eight times longer and
-// stretch the makespan); the other jobs go to the narrow ring, served by the
-// teams of the other half and, when no wide job waits, by the wide team too.
+// A job that the screens build and whose exhaustive work bound 2^n *
+// capacity(n, d) reaches this is "wide": it goes to the wide ring, which the
+// team spanning several XCDs serves first (on one XCD's team it would take up
+// to eight times longer and stretch the makespan); the other jobs go to the
+// narrow ring, served by the teams of one XCD and, when no wide job waits, by
+// the wide team too.  Linear and cover jobs use one XCD at most: while no wide
+// job is open, every XCD is a team of its own (a burst of 200 jobs, n = 10 ..
+// 20: 15.4 ms with a wide team and two narrow ones).
 constexpr double kWideWork = 274877906944.0;  // 2^38
 // Narrow jobs may be admitted past a wide job that waits for arena space,
 // until that wide job has waited this long; then admission stops behind it
@@ -59,7 +62,10 @@ struct Ticket {
 struct gc_server {
   std::mutex mu;
   int teams = 8;            // as passed to gc_server_create
-  int launch_teams = 1;     // teams of a launch: `teams`, or 1 wide + `teams` narrow (one XCD each)
+  int launch_teams = 1;     // teams of a launch, at most
+  bool split = false;       // the last launch has a wide team and `teams` narrow ones
+  unsigned int layout_launched = 0;  // HostQueue::layout of the last launch
+  unsigned int wide_open = 0;  // wide jobs published and not yet seen finished
   bool stopped = false;     // a bounded device-side wait expired: no further launches
   unsigned int grid = 0;
   hipStream_t stream = nullptr;
@@ -131,13 +137,33 @@ bool kernel_running(gc_server *s) {
   return hipEventQuery(s->kernel_done) == hipErrorNotReady;
 }
 
-// Wide XCDs of a server: teams 2 and 4 split the 8 XCDs into one wide team
-// of 8 - teams XCDs and `teams` narrow teams of one XCD; teams 1 and 8 have
-// equal teams (one team spanning the GPU, or one per XCD) and one queue.
+// Wide XCDs of a server: with teams 2 and 4, while a wide job is open, the 8
+// XCDs are one wide team of 8 - teams XCDs and `teams` narrow teams of one XCD;
+// teams 1 and 8 have equal teams (one team spanning the GPU, or one per XCD)
+// and one queue.
 int wide_xcds(int teams) { return teams == 2 || teams == 4 ? 8 - teams : 0; }
 
-bool is_wide(const gc_server *s, int n, int d) {
-  return wide_xcds(s->teams) > 0 && std::ldexp((double)greedy_code_capacity(n, d), n) >= kWideWork;
+// The job's inputs, with the tuning remembered for it.
+void fill_server_job(Job *J, int n, int d, int ord) {
+  memset(J, 0, sizeof(*J));
+  J->n = n;
+  J->d = d;
+  J->ord = ord;
+  gc_tuning tu;
+  if (tuned_for(n, d, ord, &tu)) {
+    J->near_depth = tu.near_depth;
+    J->target = tu.target_survivors;
+    J->mode = (int)tu.resolve_mode;
+    J->deep_tile = tu.deep_tile;
+    J->valu_screen = tu.valu_screen;
+  }
+  J->linear = linear_job(*J);
+  J->cover = cover_job(*J);
+}
+
+bool is_wide(const gc_server *s, const Job &J) {
+  return wide_xcds(s->teams) > 0 && !J.linear && !J.cover &&
+         std::ldexp((double)greedy_code_capacity(J.n, J.d), J.n) >= kWideWork;
 }
 
 int launch_server_kernel(gc_server *s) {
@@ -148,8 +174,10 @@ int launch_server_kernel(gc_server *s) {
   P.dq = s->dq;
   P.bar = s->bar;
   P.njobs_fixed = -1;
-  P.nteams = s->launch_teams;
-  P.split = wide_xcds(s->teams);
+  s->split = s->wide_open > 0;
+  P.nteams = s->split ? 1 + s->teams : wide_xcds(s->teams) ? 8 : s->teams;
+  P.split = s->split ? wide_xcds(s->teams) : 0;
+  P.layout = s->layout_launched = s->hq->layout;
   P.ring = s->ring_dev;
   P.ring_wide = s->ring_wide_dev;
   P.spin_limit = 1u << 25;
@@ -203,7 +231,9 @@ int pump(gc_server *s) {
   for (auto it = s->waiting.begin(); it != s->waiting.end();) {
     const uint64_t id = *it;
     Ticket &t = s->tickets[id];
-    const bool wide = is_wide(s, t.n, t.d);
+    Job inputs;
+    fill_server_job(&inputs, t.n, t.d, t.ord);
+    const bool wide = is_wide(s, inputs);
     if (!wide && blocked_wide) break;
     size_t off = 0;
     if (!arena_alloc(s, t.bytes, &off)) {
@@ -223,27 +253,15 @@ int pump(gc_server *s) {
     t.slot = (int)s->published;
     t.state = GC_JOB_ADMITTED;
     Job *J = &s->jobs[t.slot];
-    memset(J, 0, sizeof(*J));
-    J->n = t.n;
-    J->d = t.d;
-    J->ord = t.ord;
+    *J = inputs;
     J->code = reinterpret_cast<uint32_t *>(s->arena + off);
     J->capacity = greedy_code_capacity(t.n, t.d);
     J->count = nullptr;
     J->host_copy = reinterpret_cast<uint32_t *>(s->mirror_dev + off);
     J->wide = wide ? 1 : 0;
+    if (wide) ++s->wide_open;
     if (J->wide) s->ring_wide[s->published_wide++] = (unsigned int)t.slot;
     else s->ring[s->published_narrow++] = (unsigned int)t.slot;
-    gc_tuning tu;
-    if (tuned_for(t.n, t.d, t.ord, &tu)) {
-      J->near_depth = tu.near_depth;
-      J->target = tu.target_survivors;
-      J->mode = (int)tu.resolve_mode;
-      J->deep_tile = tu.deep_tile;
-      J->valu_screen = tu.valu_screen;
-    }
-    J->linear = linear_job(*J);
-    J->cover = cover_job(*J);
     s->slot_ticket[t.slot] = id;
     s->inflight.insert(id);
     ++s->published;
@@ -254,6 +272,10 @@ int pump(gc_server *s) {
     __atomic_store_n(&s->hq->submitted_wide, s->published_wide, __ATOMIC_RELEASE);
     __atomic_store_n(&s->hq->submitted, s->published_narrow, __ATOMIC_RELEASE);
   }
+  // Other teams are wanted than those of the running launch: its teams finish
+  // the jobs they have, and the launch that follows takes up the rest.
+  if (wide_xcds(s->teams) && s->launched && s->split != (s->wide_open > 0) && s->hq->layout == s->layout_launched)
+    __atomic_store_n(&s->hq->layout, s->layout_launched + 1, __ATOMIC_RELEASE);
   // Relaunch if published jobs are unfinished and no kernel is running (the
   // previous one may have gone idle just before the publication, stopped at
   // a job of the other kind, or given up on a bounded wait).
@@ -290,7 +312,7 @@ void refresh(gc_server *s, uint64_t id, Ticket &t) {
   if (t.state == GC_JOB_ADMITTED && __atomic_load_n(&s->jobs[t.slot].done, __ATOMIC_ACQUIRE)) {
     t.status = s->jobs[t.slot].status;
     t.state = t.status == 0 ? GC_JOB_DONE : GC_JOB_FAILED;
-    s->inflight.erase(id);
+    if (s->inflight.erase(id) && s->jobs[t.slot].wide) --s->wide_open;
   }
 }
 
@@ -315,7 +337,7 @@ int gc_server_create(size_t arena_bytes, int teams, gc_server **out) {
   if (!coop || bpc < 1) return fail(GC_EDEVICE, "cooperative persistent kernel unavailable");
   gc_server *s = new gc_server();
   s->teams = teams;
-  s->launch_teams = wide_xcds(teams) ? 1 + teams : teams;
+  s->launch_teams = teams == 1 ? 1 : 8;
   s->grid = (unsigned int)cus;
   s->arena_bytes = round256(arena_bytes);
   const size_t off_dq = round256(sizeof(Bar));
@@ -323,7 +345,7 @@ int gc_server_create(size_t arena_bytes, int teams, gc_server **out) {
   const size_t ws_bytes = off_ws + team_workspace_bytes() * (size_t)s->launch_teams;
   hipError_t e = hipMalloc((void **)&s->dev, ws_bytes);
   if (e == hipSuccess) e = hipMalloc((void **)&s->arena, s->arena_bytes);
-  if (e == hipSuccess) e = hipMemset(s->dev, 0, ws_bytes);
+  if (e == hipSuccess) e = hipMemset(s->dev, 0, off_ws);  // barrier block and queue; kernels clear the rest
   if (e == hipSuccess)
     e = hipHostMalloc((void **)&s->hq, sizeof(HostQueue), hipHostMallocCoherent | hipHostMallocMapped);
   if (e == hipSuccess)

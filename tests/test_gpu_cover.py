@@ -88,6 +88,35 @@ def test_ranges_and_prefixes(n, d, o, w):
         assert np.array_equal(got, ref)
 
 
+# d = 8 at n = 23, 24: few candidates are left and are compared with the
+# accepted words instead of marked.
+@pytest.mark.parametrize("o", ["grlex", "grevlex"])
+@pytest.mark.parametrize("n,d", [(1, 1), (2, 2), (5, 3), (6, 1), (7, 2), (10, 4), (13, 1), (16, 4), (17, 6), (21, 2),
+                                 (23, 8), (24, 8)])
+def test_self_orthogonal(n, d, o):
+    log(f"[cover] self-orthogonal n={n} d={d} {o}")
+    got, ref = both(gc.problem(n, d, o, self_orthogonal=True))
+    assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("n,d,o,w", [(13, 4, "grevlex", -1), (16, 2, "grlex", -1), (15, 6, "grevlex", -1),
+                                     (14, 4, "grlex", 6)])
+def test_self_orthogonal_ranges_and_prefixes(n, d, o, w):
+    kw = dict(weight=w, self_orthogonal=True)
+    total = gc.problem_positions(gc.problem(n, d, o, **kw))
+    full, _ = both(gc.problem(n, d, o, **kw))
+    for cut in (1, total // 4, total // 2 + 1, total - 1):
+        log(f"[cover] self-orthogonal {o} n={n} w={w} cut {cut} of {total}")
+        head, ref = both(gc.problem(n, d, o, stop=cut, **kw))
+        assert np.array_equal(head, ref) and np.array_equal(head, full[: len(head)])
+        got, ref = both(gc.problem(n, d, o, start=cut, prefix=len(head), **kw), prefix_words=head)
+        assert np.array_equal(got, ref) and np.array_equal(got, full)
+        # Any words may be given: odd ones, overlapping oddly, longer than n.
+        other = np.random.default_rng(cut).integers(0, 1 << n + 2, size=5).astype(np.uint32)
+        got, ref = both(gc.problem(n, d, o, start=cut, prefix=5, **kw), prefix_words=other)
+        assert np.array_equal(got, ref)
+
+
 @pytest.mark.parametrize("d", [3, 5])
 def test_capacity_keeps_the_beginning_and_nothing_past_it(cuda, d):
     full, _ = both(gc.problem(17, d, "grlex"))
