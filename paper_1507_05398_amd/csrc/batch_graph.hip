@@ -92,7 +92,7 @@ int gc_batch_graph_create(const gc_job *jobs, int njobs, int teams, gc_batch_gra
 
   Params P;
   memset(&P, 0, sizeof(P));
-  P.jobs = reinterpret_cast<Job *>(g->dev + off_jobs);
+  P.jobs = P.out = reinterpret_cast<Job *>(g->dev + off_jobs);
   P.hq = nullptr;
   P.dq = reinterpret_cast<DevQueue *>(g->dev + off_dq);
   P.bar = reinterpret_cast<Bar *>(g->dev);

@@ -96,6 +96,7 @@ struct Bar {
 
 struct Params {
   Job *jobs;
+  Job *out;                      // where outputs go: jobs, or a pinned host copy
   HostQueue *hq;
   DevQueue *dq;
   Bar *bar;
@@ -115,6 +116,14 @@ struct Params {
   char *team_ws;                 // per-team workspace, team_ws_stride bytes each
   unsigned long long team_ws_stride;
 };
+
+// Host side of a pooled workspace: a pinned block that kernels write results
+// to (no copy back), and events to time a launch.
+struct WsHost {
+  char *ptr, *dev;          // kWsHostBytes, host and device address
+  hipEvent_t begin, end;
+};
+constexpr size_t kWsHostBytes = 128u << 10;
 
 size_t team_workspace_bytes();
 int device_info(int dev, int *cus, int *coop, int *blocks_per_cu);

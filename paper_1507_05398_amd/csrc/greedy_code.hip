@@ -1600,7 +1600,7 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
         c->job = j;
         if (j >= 0) {
           const Job &J = *reinterpret_cast<const Job *>(L.in);
-          st_sys(&P.jobs[j].t_claim, (unsigned long long)wall_clock64());
+          st_sys(&P.out[j].t_claim, (unsigned long long)wall_clock64());
           c->m = J.m_start;
           c->p = J.p_start;
           c->w = kWMin;
@@ -1720,7 +1720,7 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
     // Completion: outputs first, then `done` with system-scope release, so a
     // host that sees done=1 also sees the words and the count.
     if (L.team_rank == 0 && tid == 0) {
-      Job *out = &P.jobs[L.job];
+      Job *out = &P.out[L.job];
       Ctl *c = W.ctl;
       // All reads first: one round trip.
       const unsigned long long m = ld_relaxed(&c->m), windows = ld_relaxed(&c->stat_windows),
@@ -1980,6 +1980,7 @@ struct WsEntry {
   char *ptr;
   size_t bytes;
   bool busy;
+  WsHost host;     // made on the first use that wants it
 };
 std::mutex g_ws_mu;
 std::vector<WsEntry> g_ws;
@@ -2001,7 +2002,7 @@ int acquire_workspace(size_t bytes, char **ptr, int *slot) {
   char *p = nullptr;
   const hipError_t e = hipMalloc((void **)&p, rounded);
   if (e != hipSuccess) return fail(GC_ENOMEM, "workspace of %zu bytes: %s", rounded, hipGetErrorString(e));
-  g_ws.push_back(WsEntry{dev, p, rounded, true});
+  g_ws.push_back(WsEntry{dev, p, rounded, true, WsHost{nullptr, nullptr, nullptr, nullptr}});
   *ptr = p;
   *slot = (int)g_ws.size() - 1;
   return GC_OK;
@@ -2010,6 +2011,23 @@ int acquire_workspace(size_t bytes, char **ptr, int *slot) {
 void release_workspace(int slot) {
   std::lock_guard<std::mutex> lk(g_ws_mu);
   if (slot >= 0 && (size_t)slot < g_ws.size()) g_ws[slot].busy = false;
+}
+
+// Pinned block and events of a workspace in use (kept with it; the pool holds
+// one per concurrent call).
+int workspace_host(int slot, WsHost *out) {
+  std::lock_guard<std::mutex> lk(g_ws_mu);
+  WsHost &h = g_ws[slot].host;
+  hipError_t e = hipSuccess;
+  if (!h.ptr) {
+    e = hipHostMalloc((void **)&h.ptr, kWsHostBytes, hipHostMallocCoherent | hipHostMallocMapped);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&h.dev, h.ptr, 0);
+  }
+  if (e == hipSuccess && !h.begin) e = hipEventCreate(&h.begin);
+  if (e == hipSuccess && !h.end) e = hipEventCreate(&h.end);
+  if (e != hipSuccess) return fail(GC_ENOMEM, "pinned result block: %s", hipGetErrorString(e));
+  *out = h;
+  return GC_OK;
 }
 
 // Byte layout of a launch workspace: barrier block, device queue, job table,
@@ -2029,7 +2047,7 @@ LaunchLayout launch_layout(int njobs, int nteams) {
 Params launch_params(char *ws, const LaunchLayout &l, int njobs, int nteams) {
   Params P;
   memset(&P, 0, sizeof(P));
-  P.jobs = reinterpret_cast<Job *>(ws + l.off_jobs);
+  P.jobs = P.out = reinterpret_cast<Job *>(ws + l.off_jobs);
   P.hq = nullptr;
   P.dq = reinterpret_cast<DevQueue *>(ws + l.off_dq);
   P.bar = reinterpret_cast<Bar *>(ws);
@@ -2042,8 +2060,10 @@ Params launch_params(char *ws, const LaunchLayout &l, int njobs, int nteams) {
   return P;
 }
 
-// Run a batch of jobs on `stream` with `nteams` teams and wait for it.  Jobs
-// are copied to device memory and their outputs copied back into `jobs`.
+// Run a batch of jobs on `stream` with `nteams` teams and wait for it.  A
+// single job goes to the device as a kernel argument, several from the
+// workspace's pinned block; the kernel writes the outputs to that block (more
+// jobs than it holds are copied from and to `jobs`).
 int run_batch(Job *jobs, int njobs, int nteams, unsigned int grid_req, hipStream_t stream,
               float *kernel_ms, LaunchKind kind) {
   if (njobs <= 0) return GC_OK;
@@ -2057,28 +2077,41 @@ int run_batch(Job *jobs, int njobs, int nteams, unsigned int grid_req, hipStream
   int slot = -1;
   rc = acquire_workspace(lay.bytes, &ws, &slot);
   if (rc) return rc;
-  const Params P = launch_params(ws, lay, njobs, nteams);
-  hipEvent_t ev0 = nullptr, ev1 = nullptr;
-  hipError_t e = hipEventCreate(&ev0);
-  if (e == hipSuccess) e = hipEventCreate(&ev1);
-  if (e == hipSuccess) e = hipMemcpyAsync(P.jobs, jobs, sizeof(Job) * njobs, hipMemcpyHostToDevice, stream);
-  if (e == hipSuccess) e = launch_init(P.bar, P.dq, 1, stream);
-  if (e == hipSuccess) e = hipEventRecord(ev0, stream);
+  WsHost host;
+  rc = workspace_host(slot, &host);
+  if (rc) {
+    release_workspace(slot);
+    return rc;
+  }
+  Params P = launch_params(ws, lay, njobs, nteams);
+  const size_t bytes = sizeof(Job) * (size_t)njobs;
+  Job *const seen = bytes <= kWsHostBytes ? reinterpret_cast<Job *>(host.ptr) : nullptr;
+  if (seen) {
+    memcpy(seen, jobs, bytes);
+    P.out = reinterpret_cast<Job *>(host.dev);
+  }
+  hipError_t e = hipSuccess;
+  if (njobs == 1) {
+    hipLaunchKernelGGL(init_job_kernel, dim3(4), dim3(256), 0, stream, P.bar, P.dq, P.jobs, jobs[0]);
+    e = hipGetLastError();
+  } else {
+    e = hipMemcpyAsync(P.jobs, seen ? seen : jobs, bytes, hipMemcpyHostToDevice, stream);
+    if (e == hipSuccess) e = launch_init(P.bar, P.dq, 1, stream);
+  }
+  if (e == hipSuccess && kernel_ms) e = hipEventRecord(host.begin, stream);
   if (e == hipSuccess) e = launch_persistent(P, grid, stream, kind);
-  if (e == hipSuccess) e = hipEventRecord(ev1, stream);
-  DevQueue dq;
-  memset(&dq, 0, sizeof(dq));
-  if (e == hipSuccess) e = hipMemcpyAsync(jobs, P.jobs, sizeof(Job) * njobs, hipMemcpyDeviceToHost, stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(&dq, P.dq, sizeof(dq), hipMemcpyDeviceToHost, stream);
+  if (e == hipSuccess && kernel_ms) e = hipEventRecord(host.end, stream);
+  if (e == hipSuccess && !seen) e = hipMemcpyAsync(jobs, P.jobs, bytes, hipMemcpyDeviceToHost, stream);
   // The workspace goes back to the pool only once the stream is idle.
   const hipError_t es = hipStreamSynchronize(stream);
   if (e == hipSuccess) e = es;
-  if (e == hipSuccess && kernel_ms) e = hipEventElapsedTime(kernel_ms, ev0, ev1);
+  if (e == hipSuccess && kernel_ms) e = hipEventElapsedTime(kernel_ms, host.begin, host.end);
+  if (e == hipSuccess && seen) memcpy(jobs, seen, bytes);
   if (es == hipSuccess) release_workspace(slot);
-  if (ev0) (void)hipEventDestroy(ev0);
-  if (ev1) (void)hipEventDestroy(ev1);
   if (e != hipSuccess) return fail(GC_EDEVICE, "persistent kernel failed: %s", hipGetErrorString(e));
-  if (dq.abort) return fail(GC_ETIMEOUT, "a bounded device-side wait expired");
+  // An expired wait ends the launch: some job is not done.
+  for (int i = 0; i < njobs; ++i)
+    if (!jobs[i].done) return fail(GC_ETIMEOUT, "a bounded device-side wait expired");
   return GC_OK;
 }
 
@@ -2393,7 +2426,7 @@ int greedy_code_problem_device(const gc_problem *p, uint32_t *d_words, uint64_t 
     }
   }
   J.cover = cover_job(J) && !(tuning && tuning->grid_blocks);
-  rc = run_batch(&J, 1, 1, tuning ? tuning->grid_blocks : 0, stream, &ms,
+  rc = run_batch(&J, 1, 1, tuning ? tuning->grid_blocks : 0, stream, stats ? &ms : nullptr,
                  p->self_orthogonal ? LaunchKind::kSingleSO : LaunchKind::kSingle);
   if (rc) return rc;
   copy_stats(stats, J, ms);

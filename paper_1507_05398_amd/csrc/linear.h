@@ -176,18 +176,39 @@ __device__ __forceinline__ void lin_levels(S &L, Bits A, unsigned int max_words,
   const unsigned int tid = threadIdx.x;
   const unsigned int st = (unsigned int)(D + 1) | 1u;
   const int top = so && !(D & 1) ? D - 1 : D;
-  int k = L.k, r = L.r, dim = L.dim;
-  uint32_t u = L.u;
+  // The state is the same for every lane: scalar registers and branches.
+  int k = __builtin_amdgcn_readfirstlane(L.k), r = __builtin_amdgcn_readfirstlane(L.r),
+      dim = __builtin_amdgcn_readfirstlane(L.dim);
+  uint32_t u = __builtin_amdgcn_readfirstlane(L.u);
+  // Words w and v (= w XOR label / 64; the same word when that is 0) of every
+  // A[s], largest s first, four at a time: their reads go out together.
+  auto update = [&](unsigned int w, unsigned int v, unsigned int ub) {
+    for (int s = D; s >= 1; s -= 4) {
+      unsigned long long aw[5], av[5];
+#pragma unroll
+      for (int q = 0; q < 5; ++q) {
+        const int i = s - q >= 0 ? s - q : 0;
+        aw[q] = A[w * st + i];
+        av[q] = A[v * st + i];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (s - q >= 1) {
+          A[w * st + s - q] = aw[q] | xor_permute(av[q + 1], ub);
+          if (v != w) A[v * st + s - q] = av[q] | xor_permute(aw[q + 1], ub);
+        }
+    }
+  };
   for (; k < K; ++k) {
     const unsigned int nw = r < 6 ? 1u : 1u << (r - 6);
     if ((r + 1 < 6 ? 1u : 1u << (r - 5)) > max_words) break;
     const uint32_t t = ord == GC_GRAY ? u : 0u;  // label of (unit vector k) + img[k]
     const uint32_t c = so ? lin_overlaps(L, dim, L.img[k]) : 0u;
-    const uint32_t m = lin_min_label<kThreads>(nw, &L.best[k & 1], [&](unsigned int w) {
+    const uint32_t m = __builtin_amdgcn_readfirstlane(lin_min_label<kThreads>(nw, &L.best[k & 1], [&](unsigned int w) {
       unsigned long long x = top < 0 ? ~0ull : ~xor_permute(A[(w ^ (t >> 6)) * st + top], t & 63);
       if (r < 6) x &= (1ull << (1 << r)) - 1;
       return so ? lin_first_orthogonal(L, dim, c, w, x) : x;
-    });
+    }));
     const bool grew = m == ~0u;
     u = t ^ (grew ? 1u << r : m);
     if (kThreads > 64 && tid == 0) L.best[(k + 1) & 1] = ~0u;
@@ -200,16 +221,12 @@ __device__ __forceinline__ void lin_levels(S &L, Bits A, unsigned int max_words,
         A[(w ^ uw) * st] = 0;
       }
     } else if (uw == 0) {
-      for (unsigned int w = tid; w < nw; w += kThreads)
-        for (int s = D; s >= 1; --s) A[w * st + s] |= xor_permute(A[w * st + s - 1], ub);
+      for (unsigned int w = tid; w < nw; w += kThreads) update(w, w, ub);
     } else {
       const int hb = 31 - __builtin_clz(uw);  // pairs: the words whose bit hb is clear
       for (unsigned int i = tid; i < nw / 2; i += kThreads) {
-        const unsigned int w = ((i >> hb) << (hb + 1)) | (i & ((1u << hb) - 1u)), v = w ^ uw;
-        for (int s = D; s >= 1; --s) {
-          A[w * st + s] |= xor_permute(A[v * st + s - 1], ub);
-          A[v * st + s] |= xor_permute(A[w * st + s - 1], ub);
-        }
+        const unsigned int w = ((i >> hb) << (hb + 1)) | (i & ((1u << hb) - 1u));
+        update(w, w ^ uw, ub);
       }
     }
     lin_sync<kThreads>();

@@ -1,14 +1,17 @@
 // linear.hip -- single linear codes (lex, Gray, B-ordering, self-orthogonal
-// lex and Gray): the generator search by one workgroup, then the words by the
-// whole GPU.  Two ordinary launches (three for a long B-ordering list); the
-// mathematics is in linear.h.
+// lex and Gray): one ordinary launch in which every workgroup finds the
+// generators for itself and writes its part of the words (a launch more lists
+// the low-weight words of a larger B-ordering; a prefix to check or bitmaps in
+// global memory leave the search to one workgroup and a launch of its own).
+// The mathematics is in linear.h.
 //
 // What bounds it: launch latency and the chain of n search levels (one wave
 // while the label bitmaps are short).  One call, without and with this path:
-// n = 15 d = 3 to host memory 600 and 78 us, n = 20 d = 4 3236 and 56 us,
-// n = 26 d = 3 (2^21 words) 520 ms and 66 us, n = 30 d = 10 128 ms and 382 us
-// (2^19 labels: the bitmaps leave LDS), a random basis at n = 23 d = 5 2774
-// and 96 us.
+// n = 15 d = 3 to host memory 600 and 69 us, n = 20 d = 4 3235 and 46 us,
+// n = 26 d = 3 (2^21 words) 526 ms and 56 us, n = 30 d = 10 128 ms and 305 us
+// (2^19 labels: the bitmaps leave LDS), a random basis at n = 23 d = 5 2698
+// and 81 us.  Search and words as two launches with the result copied back
+// cost 78, 55, 66, 384 and 97 us: a launch and a copy are 5 us each.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -24,6 +27,7 @@ namespace gcimpl {
 
 int acquire_workspace(size_t bytes, char **ptr, int *slot);
 void release_workspace(int slot);
+int workspace_host(int slot, WsHost *out);
 
 namespace {
 
@@ -143,6 +147,7 @@ __global__ void __launch_bounds__(kScanBlock) lin_list_kernel(LinArgs P) {
 // bit's level (byte tables give the label of a position).
 __device__ __forceinline__ bool border_search(LinLds<kLinWords> &L, ScanLds &S, uint32_t (*lam)[256], const LinArgs &P) {
   const int tid = threadIdx.x, n = P.n;
+  // (One segment: every workgroup lists it, all the same.)
   if (P.segs == 1) list_segment<kBlock>(P, S, 0);
   if (tid < 32) L.img[tid] = P.basis[tid];
   for (int i = tid; i < 4 * 256; i += kBlock) lam[i >> 8][i & 255] = 0;
@@ -180,13 +185,14 @@ __device__ __forceinline__ bool border_search(LinLds<kLinWords> &L, ScanLds &S, 
   return k >= n;
 }
 
-// One workgroup: the generators, the range of code words to write, and (a
-// resumed construction) whether the given prefix is the code's beginning.
+// The generators, the range of code words to write, and (a resumed
+// construction, one workgroup only) whether the given prefix is the code's
+// beginning; with `write` the workgroup also writes its part of the words.
 template <bool kBorder>
-__global__ void __launch_bounds__(kBlock) lin_find_kernel(LinArgs P) {
+__global__ void __launch_bounds__(kBlock) lin_find_kernel(LinArgs P, unsigned long long *count, int write) {
   __shared__ LinLds<kLinWords> L;
-  __shared__ uint32_t tab[4][256];
-  __shared__ unsigned long long begin_s;
+  __shared__ __align__(16) uint32_t tab[4][256];
+  __shared__ unsigned long long begin_s, end_s;
   __shared__ int ok_s;
   const int tid = threadIdx.x;
   bool ok;
@@ -201,23 +207,36 @@ __global__ void __launch_bounds__(kBlock) lin_find_kernel(LinArgs P) {
     ok_s = ok && begin_s == P.prefix;
   }
   __syncthreads();
-  if (ok_s && P.prefix) {
+  if (ok_s && (P.prefix || write)) {
     lin_word_tables(tab, L.gen, L.dim);
     __syncthreads();
+  }
+  if (ok_s && P.prefix) {
     bool same = true;
     for (unsigned long long i = tid; i < P.prefix; i += kBlock) same &= P.code[i] == lin_word(tab, i);
     if (!__syncthreads_and(same)) ok_s = 0;
     __syncthreads();
   }
-  if (tid < 32) P.res->gen[tid] = tid < L.dim ? L.gen[tid] : 0u;
   if (tid == 0) {
     const unsigned long long all = ok_s ? lin_count_below(L, P.stop) : 0;
-    P.res->ok = ok_s;
-    P.res->dim = L.dim;
-    P.res->status = all > P.capacity ? GC_ECAPACITY : GC_OK;
-    P.res->begin = begin_s;
-    P.res->end = all < P.capacity ? all : P.capacity;
+    end_s = all < P.capacity ? all : P.capacity;
+    if (blockIdx.x == 0) {
+      P.res->dim = L.dim;
+      P.res->status = all > P.capacity ? GC_ECAPACITY : GC_OK;
+      P.res->begin = begin_s;
+      P.res->end = end_s;
+      P.res->ok = ok_s;
+      if (write && ok_s && count) *count = end_s;
+    }
   }
+  if (!write) {
+    if (tid < 32) P.res->gen[tid] = tid < L.dim ? L.gen[tid] : 0u;
+    return;
+  }
+  __syncthreads();
+  if (ok_s)
+    lin_emit(tab, P.code, begin_s, end_s, (unsigned long long)blockIdx.x * kBlock + tid,
+             (unsigned long long)gridDim.x * kBlock);
 }
 
 __global__ void __launch_bounds__(kEmitBlock) lin_emit_kernel(const LinResult *res, uint32_t *code,
@@ -302,49 +321,56 @@ int run_linear(Job *J, hipStream_t stream, char *fixed, size_t fixed_bytes, floa
   }
   char *ws = fixed;
   int slot = -1;
+  WsHost host;
+  memset(&host, 0, sizeof(host));
   if (!fixed) {
-    const int rc = acquire_workspace(bytes, &ws, &slot);
+    int rc = acquire_workspace(bytes, &ws, &slot);
     if (rc) return rc;
+    rc = workspace_host(slot, &host);
+    if (rc) {
+      release_workspace(slot);
+      return rc;
+    }
   }
-  P.res = reinterpret_cast<LinResult *>(ws);
+  // The result goes to pinned host memory, or (fixed workspace) is copied back.
+  LinResult *const seen = reinterpret_cast<LinResult *>(host.ptr);
   P.offs = reinterpret_cast<uint32_t *>(ws + off_offs);
   P.list = reinterpret_cast<uint32_t *>(ws + off_list);
   P.gbits = reinterpret_cast<unsigned long long *>(ws + off_bits);
   P.gwords = (unsigned int)((bytes - off_bits) / 8);
-  // Words of the code, at most: four a thread and step, up to four
-  // workgroups per compute unit.
+  const bool one_launch = P.prefix == 0 && (J->ord == GC_BORDER || P.gwords == 0);
+  P.res = one_launch && seen ? reinterpret_cast<LinResult *>(host.dev) : reinterpret_cast<LinResult *>(ws);
+  // Words of the code, at most: four a thread and step.  In one launch up to a
+  // workgroup per compute unit (LDS holds one), else up to four.
   const unsigned long long most = std::min<unsigned long long>(J->capacity, 1ull << K);
-  const unsigned int grid = (unsigned int)std::min<unsigned long long>(1024, most / (4 * kEmitBlock) + 1);
-  hipEvent_t ev0 = nullptr, ev1 = nullptr;
-  hipError_t e = hipSuccess;
-  if (kernel_ms) {
-    e = hipEventCreate(&ev0);
-    if (e == hipSuccess) e = hipEventCreate(&ev1);
-    if (e == hipSuccess) e = hipEventRecord(ev0, stream);
-  }
+  const unsigned int grid = one_launch ? (unsigned int)std::min<unsigned long long>(256, most / (4 * kBlock) + 1)
+                                       : (unsigned int)std::min<unsigned long long>(1024, most / (4 * kEmitBlock) + 1);
+  if (seen) seen->ok = 0;
+  hipError_t e = kernel_ms ? hipEventRecord(host.begin, stream) : hipSuccess;
   if (e == hipSuccess && P.segs > 1) {
     hipLaunchKernelGGL(lin_list_kernel, dim3(P.segs), dim3(kScanBlock), 0, stream, P);
     e = hipGetLastError();
   }
   if (e == hipSuccess) {
-    if (J->ord == GC_BORDER) hipLaunchKernelGGL(lin_find_kernel<true>, dim3(1), dim3(kBlock), 0, stream, P);
-    else hipLaunchKernelGGL(lin_find_kernel<false>, dim3(1), dim3(kBlock), 0, stream, P);
+    const dim3 wgs(one_launch ? grid : 1);
+    if (J->ord == GC_BORDER) hipLaunchKernelGGL(lin_find_kernel<true>, wgs, dim3(kBlock), 0, stream, P, J->count, one_launch);
+    else hipLaunchKernelGGL(lin_find_kernel<false>, wgs, dim3(kBlock), 0, stream, P, J->count, one_launch);
     e = hipGetLastError();
   }
-  if (e == hipSuccess) {
+  if (e == hipSuccess && !one_launch) {
     hipLaunchKernelGGL(lin_emit_kernel, dim3(grid), dim3(kEmitBlock), 0, stream, P.res, J->code, J->count);
     e = hipGetLastError();
   }
-  if (e == hipSuccess && kernel_ms) e = hipEventRecord(ev1, stream);
+  if (e == hipSuccess && kernel_ms) e = hipEventRecord(host.end, stream);
   LinResult res;
   memset(&res, 0, sizeof(res));
-  if (e == hipSuccess) e = hipMemcpyAsync(&res, P.res, sizeof(res), hipMemcpyDeviceToHost, stream);
+  if (e == hipSuccess && !(one_launch && seen))
+    e = hipMemcpyAsync(seen ? seen : &res, P.res, sizeof(res), hipMemcpyDeviceToHost, stream);
   const hipError_t es = hipStreamSynchronize(stream);
   if (e == hipSuccess) e = es;
-  if (e == hipSuccess && kernel_ms) e = hipEventElapsedTime(kernel_ms, ev0, ev1);
+  if (e == hipSuccess && kernel_ms) e = hipEventElapsedTime(kernel_ms, host.begin, host.end);
+  if (e == hipSuccess && seen) res = *seen;
   if (slot >= 0 && es == hipSuccess) release_workspace(slot);
-  if (ev0) (void)hipEventDestroy(ev0);
-  if (ev1) (void)hipEventDestroy(ev1);
   if (e != hipSuccess) return fail(GC_EDEVICE, "linear code kernels failed: %s", hipGetErrorString(e));
   if (!res.ok) return GC_OK;
   J->out_count = res.end;

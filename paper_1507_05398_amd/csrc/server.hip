@@ -169,7 +169,7 @@ bool is_wide(const gc_server *s, const Job &J) {
 int launch_server_kernel(gc_server *s) {
   Params P;
   memset(&P, 0, sizeof(P));
-  P.jobs = s->jobs_dev;
+  P.jobs = P.out = s->jobs_dev;
   P.hq = s->hq_dev;
   P.dq = s->dq;
   P.bar = s->bar;
