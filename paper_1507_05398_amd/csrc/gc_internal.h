@@ -156,6 +156,8 @@ int run_linear(Job *J, hipStream_t stream, char *fixed, size_t fixed_bytes, floa
 // Validates a caller's job array and fills `J` (caller order) and `order`
 // (queue position -> caller index, longest jobs first).
 int prepare_batch(const gc_job *jobs, int njobs, Job *J, int *order);
+// Teams of a batch that names no number.
+int default_teams(const Job *J, int njobs);
 extern thread_local std::string g_error;
 
 }  // namespace gcimpl
