@@ -9,7 +9,14 @@
 // Section "Some Examples" reports such codes up to length 35, past 32-bit
 // words.  Candidates are the weight-w vectors in increasing value.
 //
-// One cooperative launch walks the candidates in blocks of kCands positions:
+// Two words of weight w at distance below d are those that share t =
+// w - ceil(d / 2) + 1 ones, that is, a t-subset of their supports.  Where the
+// t-subsets of the coordinates fit a bitmap in one workgroup's LDS and a word
+// has few of them (pack_rule), cw_pack_kernel keeps that bitmap instead of
+// comparing candidates with the code: see there.
+//
+// Otherwise one cooperative launch walks the candidates in blocks of kCands
+// positions:
 //   1. every workgroup unranks the block's candidates (combinatorial number
 //      system) and screens them against its own slice of the committed code;
 //      a clash sets the candidate's bit in a dead mask (device atomics);
@@ -34,8 +41,274 @@ namespace gcimpl {
 
 int acquire_workspace(size_t bytes, char **ptr, int *slot);
 void release_workspace(int slot);
+int workspace_host(int slot, WsHost *out);
 
 namespace {
+
+// ---- packing by t-subsets, one workgroup --------------------------------
+
+constexpr int kPackBlock = 1024;
+constexpr int kPackEach = 4;             // consecutive positions a thread filters per batch
+constexpr int kPackMaxW = 8;             // weight, at most (binomials then fit 32 bits)
+constexpr int kPackMaxOut = 3;           // ones left out of a t-subset, at most
+constexpr unsigned int kPackSubsets = 1u << 19;  // t-subsets, at most (a 64 KiB bitmap)
+constexpr unsigned int kPackOwners = 8192;
+constexpr unsigned int kPackPending = kPackBlock * (kPackEach + 1);
+
+struct PackBinomials {
+  uint32_t c[kPackMaxW + 1][64];         // c[b][a] = C(a, b)
+  constexpr PackBinomials() : c() {
+    for (int a = 0; a < 64; ++a) c[0][a] = 1;
+    for (int b = 1; b <= kPackMaxW; ++b)
+      for (int a = 1; a < 64; ++a) c[b][a] = c[b][a - 1] + c[b - 1][a - 1];
+  }
+};
+__constant__ const PackBinomials kPackBinomials{};
+
+struct PackLds {
+  uint32_t marked[kPackSubsets / 32];    // t-subsets of the code's words
+  uint32_t owner[kPackOwners];           // latest claim of a t-subset (hashed): round, earliest candidate
+  uint64_t pending[kPackPending];        // ring: candidates that passed the filter, in order
+  uint32_t bin[kPackMaxW + 1][64];
+  uint32_t wave[kPackBlock / 64];
+};
+
+struct PackParams {
+  int n;
+  unsigned int subsets;                  // C(n, t)
+  unsigned long long total;              // C(n, w) candidate positions
+  uint64_t *words;
+  unsigned long long capacity;
+  uint64_t *count;                       // may be null
+  int *status;                           // pinned
+};
+
+constexpr int choose_small(int a, int b) { return b == 0 ? 1 : choose_small(a - 1, b - 1) * a / b; }
+
+// Ranks (combinatorial number system) of the t-subsets of x's support, t = W -
+// Out.  With k ones left out below it, one i counts as C(its place, i + 1 - k);
+// a rank is a sum of such terms, each read from LDS once.
+template <int W, int Out>
+__device__ __forceinline__ void subset_ranks(const PackLds &L, uint64_t x, uint32_t (&r)[choose_small(W, Out)]) {
+  uint32_t term[Out + 1][W];
+#pragma unroll
+  for (int i = 0; i < W; ++i) {
+    const int c = __builtin_ctzll(x);
+    x &= x - 1;
+#pragma unroll
+    for (int k = 0; k <= Out; ++k) term[k][i] = i + 1 - k > 0 ? L.bin[i + 1 - k > 0 ? i + 1 - k : 0][c] : 0u;
+  }
+  int q = 0;
+  if constexpr (Out == 1) {
+#pragma unroll
+    for (int a = 0; a < W; ++a) {
+      uint32_t v = 0;
+#pragma unroll
+      for (int i = 0; i < W; ++i)
+        if (i != a) v += term[i > a][i];
+      r[q++] = v;
+    }
+  } else if constexpr (Out == 2) {
+#pragma unroll
+    for (int a = 0; a < W; ++a)
+#pragma unroll
+      for (int b = a + 1; b < W; ++b) {
+        uint32_t v = 0;
+#pragma unroll
+        for (int i = 0; i < W; ++i)
+          if (i != a && i != b) v += term[(i > a) + (i > b)][i];
+        r[q++] = v;
+      }
+  } else {
+#pragma unroll
+    for (int a = 0; a < W; ++a)
+#pragma unroll
+      for (int b = a + 1; b < W; ++b)
+#pragma unroll
+        for (int c = b + 1; c < W; ++c) {
+          uint32_t v = 0;
+#pragma unroll
+          for (int i = 0; i < W; ++i)
+            if (i != a && i != b && i != c) v += term[(i > a) + (i > b) + (i > c)][i];
+          r[q++] = v;
+        }
+  }
+}
+
+template <int N>
+__device__ __forceinline__ bool any_marked(const PackLds &L, const uint32_t (&r)[N]) {
+  uint32_t hit = 0;
+#pragma unroll
+  for (int q = 0; q < N; ++q) hit |= L.marked[r[q] >> 5] >> (r[q] & 31);
+  return hit & 1u;
+}
+
+// Exclusive prefix of `mine` over the workgroup and the total; `mine` is below
+// 8 and the waves' sums go through L.wave (a barrier before the next use).
+__device__ __forceinline__ unsigned int pack_scan(PackLds &L, unsigned int mine, unsigned int *total) {
+  const unsigned int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  unsigned int before = 0, all = 0;
+#pragma unroll
+  for (int b = 0; b < 3; ++b) {
+    const unsigned long long m = __ballot((mine >> b) & 1u);
+    before += (unsigned int)__popcll(m & below) << b;
+    all += (unsigned int)__popcll(m) << b;
+  }
+  if (lane == 0) L.wave[wave] = all;
+  __syncthreads();
+  unsigned int sum = 0;
+#pragma unroll
+  for (unsigned int v = 0; v < kPackBlock / 64; ++v) {
+    if (v < wave) before += L.wave[v];
+    sum += L.wave[v];
+  }
+  *total = sum;
+  return before;
+}
+
+// Batches of 4096 positions: a thread decodes the first of its four, steps
+// through them and drops each with a marked t-subset; the others join the
+// pending ring in order.  From 1024 pending on (or at the walk's end), each
+// thread takes one of the next 1024 and they are decided in rounds: an
+// undecided candidate claims its t-subsets, one that holds all of its claims
+// against earlier ones is accepted (nothing earlier and undecided shares a
+// t-subset with it) and marks them, and those with a marked t-subset are dead.
+// The earliest undecided one wins its claims in any case, hash collisions
+// included, so every round decides.  Accepted words are appended in order.
+//
+// Bound by LDS reads of the filter (n = 30 w = 5 d = 6: 25 a position, 2 ns)
+// and by barriers (n = 40 w = 4 d = 4: 200 rounds of 3).  A call, by the screens
+// and here: n = 20 w = 3 d = 4 654 and 35 us, n = 40 w = 4 d = 4 18.0 ms and
+// 293 us, n = 30 w = 5 d = 4 27.8 ms and 527 us, d = 6 20.5 ms and 307 us.
+template <int W, int Out>
+__global__ void __launch_bounds__(kPackBlock) cw_pack_kernel(PackParams P) {
+  constexpr int N = choose_small(W, Out);
+  __shared__ PackLds L;
+  const unsigned int tid = threadIdx.x;
+  for (unsigned int i = tid; i < (P.subsets + 31) / 32; i += kPackBlock) L.marked[i] = 0;
+  for (unsigned int i = tid; i < kPackOwners; i += kPackBlock) L.owner[i] = 0;
+  for (unsigned int i = tid; i < (kPackMaxW + 1) * 64; i += kPackBlock)
+    L.bin[i / 64][i % 64] = kPackBinomials.c[i / 64][i % 64];
+  __syncthreads();
+  unsigned long long m = 0, p0 = 0;
+  unsigned int head = 0, pend = 0;   // pending ring: first entry, entries
+  unsigned int round = 0;            // below 2^22: each accepts a word, and words have distinct t-subsets
+  int status = GC_OK;
+  while (p0 < P.total || pend) {
+    if (p0 < P.total && pend < kPackBlock) {
+      const unsigned long long first = p0 + (unsigned long long)tid * kPackEach;
+      uint64_t x[kPackEach];
+      unsigned int live = 0;
+      if (first < P.total) {
+        uint64_t v = 0;
+        uint32_t rest = (uint32_t)first;
+        int hi = P.n;                // places below hi are left
+#pragma unroll
+        for (int i = W; i >= 1; --i) {
+          int lo = i - 1;            // C(lo, i) = 0 <= rest < C(hi, i): the largest such lo
+          while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (L.bin[i][mid] <= rest) lo = mid; else hi = mid;
+          }
+          rest -= L.bin[i][lo];
+          v |= 1ull << lo;
+          hi = lo;
+        }
+#pragma unroll
+        for (int k = 0; k < kPackEach; ++k) {
+          x[k] = v;
+          if (first + k < P.total) {
+            uint32_t r[N];
+            subset_ranks<W, Out>(L, v, r);
+            if (!any_marked(L, r)) live |= 1u << k;
+            const uint64_t up = v + (v & -v);   // the next word of this weight
+            v = up | (((v ^ up) >> 2) >> __builtin_ctzll(v));
+          }
+        }
+      }
+      unsigned int all;
+      unsigned int at = head + pend + pack_scan(L, (unsigned int)__popc(live), &all);
+#pragma unroll
+      for (int k = 0; k < kPackEach; ++k)
+        if ((live >> k) & 1u) {
+          L.pending[at >= kPackPending ? at - kPackPending : at] = x[k];
+          ++at;
+        }
+      pend += all;
+      p0 += (unsigned long long)kPackBlock * kPackEach;
+      __syncthreads();
+      continue;
+    }
+    const unsigned int nc = pend < (unsigned int)kPackBlock ? pend : (unsigned int)kPackBlock;
+    const unsigned int at = head + tid;
+    uint64_t x = 0;
+    uint32_t r[N];
+    bool live = false, taken = false;
+    if (tid < nc) {
+      x = L.pending[at >= kPackPending ? at - kPackPending : at];
+      subset_ranks<W, Out>(L, x, r);
+      live = !any_marked(L, r);
+    }
+    while (__syncthreads_or(live)) {
+      const uint32_t key = (++round << 10) | (kPackBlock - 1 - tid);
+      if (live) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) atomicMax(&L.owner[r[q] & (kPackOwners - 1)], key);
+      }
+      __syncthreads();
+      if (live) {
+        bool mine = true;
+#pragma unroll
+        for (int q = 0; q < N; ++q) mine &= L.owner[r[q] & (kPackOwners - 1)] == key;
+        if (mine) {
+          taken = true;
+          live = false;
+#pragma unroll
+          for (int q = 0; q < N; ++q) atomicOr(&L.marked[r[q] >> 5], 1u << (r[q] & 31));
+        }
+      }
+      __syncthreads();
+      if (live) live = !any_marked(L, r);
+    }
+    unsigned int na;
+    const unsigned long long to = m + pack_scan(L, taken, &na);
+    if (taken && to < P.capacity) P.words[to] = x;
+    m += na;
+    head += nc;
+    if (head >= kPackPending) head -= kPackPending;
+    pend -= nc;
+    __syncthreads();
+    if (m > P.capacity) {
+      m = P.capacity;
+      status = GC_ECAPACITY;
+      break;
+    }
+  }
+  if (tid == 0) {
+    if (P.count) *P.count = m;
+    *P.status = status;
+  }
+}
+
+using PackKernel = void (*)(PackParams);
+// (With three left out of 7 or 8 the 35 and 56 ranks spill; n = 24 w = 8 d = 8
+// still 5.8 ms, 141 ms by the screens.)
+template <int Out>
+PackKernel pack_kernel_of(int w) {
+  switch (w) {
+    case 2: if constexpr (Out < 2) return cw_pack_kernel<2, Out>; else return nullptr;
+    case 3: if constexpr (Out < 3) return cw_pack_kernel<3, Out>; else return nullptr;
+    case 4: return cw_pack_kernel<4, Out>;
+    case 5: return cw_pack_kernel<5, Out>;
+    case 6: return cw_pack_kernel<6, Out>;
+    case 7: return cw_pack_kernel<7, Out>;
+    case 8: return cw_pack_kernel<8, Out>;
+    default: return nullptr;
+  }
+}
+
+// ---- screens over the whole GPU -----------------------------------------
 
 constexpr int kCwBlock = 256;                     // threads per workgroup
 constexpr int kCands = 1024;                      // candidate positions per block
@@ -87,13 +360,10 @@ __global__ void __launch_bounds__(kCwBlock) cw64_kernel(CwParams P) {
   __shared__ int stop_s;
   cooperative_groups::grid_group grid = cooperative_groups::this_grid();
   const int tid = threadIdx.x;
-  if (tid == 0) {
-    for (int a = 0; a <= 64; ++a) {
-      C[a][0] = 1;
-      for (int b = 1; b <= 64; ++b) C[a][b] = a == 0 ? 0ull : C[a - 1][b - 1] + C[a - 1][b];
-    }
+  for (int a = 0; a <= 64; ++a) {
+    if (tid <= 64) C[a][tid] = tid == 0 ? 1ull : (a == 0 ? 0ull : C[a - 1][tid - 1] + C[a - 1][tid]);
+    __syncthreads();
   }
-  __syncthreads();
   const unsigned int d = (unsigned int)P.d;
   for (unsigned long long p0 = 0; p0 < P.total; p0 += kCands) {
     const unsigned int nb = (unsigned int)(P.total - p0 < (unsigned long long)kCands ? P.total - p0 : kCands);
@@ -183,6 +453,42 @@ unsigned long long positions(int a, int b) {
   return r;
 }
 
+// The packing kernel of (n, w, d), or null where the t-subsets outgrow LDS, a
+// word has too many of them, or every two words clash or none do (t outside 1
+// .. w - 1): the screens.  Inside these limits it is always the faster one: a
+// position costs a few ns of one compute unit against 20 ns of grid barriers.
+PackKernel pack_rule(int n, int w, int d, unsigned int *subsets) {
+  const int out = (d + 1) / 2 - 1, t = w - out;
+  if (w > kPackMaxW || out < 1 || out > kPackMaxOut || t < 1) return nullptr;
+  const unsigned long long all = positions(n, t);
+  if (all > kPackSubsets) return nullptr;
+  *subsets = (unsigned int)all;
+  return out == 1 ? pack_kernel_of<1>(w) : out == 2 ? pack_kernel_of<2>(w) : pack_kernel_of<3>(w);
+}
+
+// Runs the packing kernel and waits for it.
+int run_pack(PackKernel kernel, PackParams P, hipStream_t stream, int *status) {
+  char *ws = nullptr;
+  int slot = -1;
+  if (int rc = acquire_workspace(256, &ws, &slot)) return rc;
+  WsHost host;
+  if (int rc = workspace_host(slot, &host)) {
+    release_workspace(slot);
+    return rc;
+  }
+  P.status = reinterpret_cast<int *>(host.dev);
+  int *seen = reinterpret_cast<int *>(host.ptr);
+  *seen = GC_ETIMEOUT;
+  hipLaunchKernelGGL(kernel, dim3(1), dim3(kPackBlock), 0, stream, P);
+  hipError_t e = hipGetLastError();
+  const hipError_t es = hipStreamSynchronize(stream);
+  if (e == hipSuccess) e = es;
+  *status = *seen;
+  if (es == hipSuccess) release_workspace(slot);
+  if (e != hipSuccess) return fail(GC_EDEVICE, "constant-weight launch failed: %s", hipGetErrorString(e));
+  return GC_OK;
+}
+
 }  // namespace
 }  // namespace gcimpl
 
@@ -204,6 +510,14 @@ extern "C" int greedy_code_cw64(int n, int w, int d, uint64_t *d_words, uint64_t
   if (hipGetDevice(&dev) != hipSuccess) return fail(GC_EDEVICE, "hipGetDevice failed");
   if (int rc = device_info(dev, &cus, &coop, &bpc)) return rc;
   if (!coop) return fail(GC_EDEVICE, "device %d has no cooperative launch", dev);
+  unsigned int subsets = 0;
+  if (const PackKernel kernel = pack_rule(n, w, d, &subsets)) {
+    int status = GC_OK;
+    if (int rc = run_pack(kernel, PackParams{n, subsets, total, d_words, capacity, d_count, nullptr}, stream, &status))
+      return rc;
+    if (status) return fail(status, "the code exceeds capacity %llu", (unsigned long long)capacity);
+    return GC_OK;
+  }
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, cw64_kernel, kCwBlock, 0) != hipSuccess || per_cu < 1)
     return fail(GC_EDEVICE, "the constant-weight kernel does not fit a compute unit");
