@@ -69,4 +69,15 @@ struct CoverWs {
   unsigned int pad[63];
 };
 
+// Join state of the team of a launch of its own.
+struct CoverCtl {
+  unsigned int xcd;       // 1 + the team's XCD; 0: none yet
+  unsigned int members;   // workgroups that joined, and whether the team is closed
+  unsigned int size;      // members when it was closed
+  unsigned int left;      // workgroups of the launch that are done
+  unsigned int built;     // 1 the code is built, 2 the team is too small
+  int abort;
+  unsigned int pad[58];
+};
+
 }  // namespace gcimpl

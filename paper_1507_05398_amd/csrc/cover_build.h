@@ -540,16 +540,21 @@ __device__ __noinline__ void cover_team(CoverWs *ws_v, Ctl *ctl_v, unsigned int 
 // their conflict graphs, so workgroups pay from 8 words each (n = 16, d = 5:
 // 220 us with 32, 294 us with one).  False (alike in every workgroup) when
 // the slices would not fit.
-template <bool kSelf>
-__device__ __forceinline__ bool build_cover(Lds &L, const Params &P, const TeamWs &W) {
-  const unsigned int words = L.n > 6 ? 1u << (L.n - 6) : 1u, most = umin(L.sub_size, (unsigned int)kCovTeam);
-  const unsigned int least = kSelf || L.d > kCovMaxD ? 8u : words > 1024 ? 512u : 1024u;  // words of a slice
+constexpr unsigned int cover_team_size(int n, int d, bool self, unsigned int workgroups) {
+  const unsigned int words = n > 6 ? 1u << (n - 6) : 1u, most = workgroups < kCovTeam ? workgroups : kCovTeam;
+  const unsigned int least = self || d > kCovMaxD ? 8u : words > 1024 ? 512u : 1024u;  // words of a slice
   unsigned int team = 1;
   while (2 * team <= most && words / (2 * team) >= least) team *= 2;
+  return team;
+}
+
+template <bool kSelf>
+__device__ __forceinline__ bool build_cover(Lds &L, const TeamWs &W, int *abort_flag, unsigned int limit) {
+  const unsigned int words = L.n > 6 ? 1u << (L.n - 6) : 1u, team = cover_team_size(L.n, L.d, kSelf, L.sub_size);
   if (words / team > (unsigned int)kCovWords) return false;
   if (L.sub_rank < team) {
-    if (!kSelf && L.d <= kCovMaxD) cover_team(W.cover, W.ctl, L.sub_rank, team, &P.dq->abort, P.spin_limit);
-    else cover_window_team<kSelf>(W.cover, W.ctl, L.sub_rank, team, &P.dq->abort, P.spin_limit);
+    if (!kSelf && L.d <= kCovMaxD) cover_team(W.cover, W.ctl, L.sub_rank, team, abort_flag, limit);
+    else cover_window_team<kSelf>(W.cover, W.ctl, L.sub_rank, team, abort_flag, limit);
   }
   return true;
 }

@@ -121,6 +121,7 @@ struct Params {
 // to (no copy back), and events to time a launch.
 struct WsHost {
   char *ptr, *dev;          // kWsHostBytes, host and device address
+  struct CoverCtl *ctl;     // join state of a cover launch (device memory)
   hipEvent_t begin, end;
 };
 constexpr size_t kWsHostBytes = 128u << 10;

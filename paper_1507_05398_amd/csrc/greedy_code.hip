@@ -1562,6 +1562,95 @@ __device__ int claim_job(const Params &P, unsigned int team) {
   }
 }
 
+// The job whose inputs are in L.in, for every phase of its construction.
+__device__ __forceinline__ void load_job(Lds &L) {
+  const int tid = threadIdx.x;
+  const Job &J = *reinterpret_cast<const Job *>(L.in);
+  if (tid == 0) {
+    L.n = J.n;
+    L.d = J.d;
+    L.ord = J.ord;
+    // Defaults by ordering (measured on the n=24..28 screens): graded
+    // orders reject many candidates deep in the code, so they screen the
+    // whole code up front; lex screens the newest 16K words and Gray the
+    // newest 8K (where almost every rejected candidate meets its killer),
+    // and both then deep-scan every survivor once.
+    const bool graded = L.ord == GC_GRLEX || L.ord == GC_GREVLEX;
+    const int mode = J.mode;
+    L.mode = mode ? mode : MODE_DEEP_ALL;
+    const unsigned long long nd = J.near_depth;
+    L.near_depth = nd ? nd : (graded ? ~0ull : (L.ord == GC_GRAY ? kDefaultNearGray : kDefaultNear));
+    const unsigned int tg = J.target;
+    L.target = tg ? (tg > (unsigned int)kSMax ? (unsigned int)kSMax : (tg < 16 ? 16 : tg))
+                  : (graded ? kDefaultTarget : kDefaultTargetLinear);
+    L.code = J.code;
+    L.capacity = J.capacity;
+    const unsigned int dt = J.deep_tile;
+    L.deep_tile = dt ? dt : (unsigned int)kTile;
+    L.mfma = J.valu_screen == 0;
+    L.linear = J.linear;
+    L.by_cover = J.cover;
+    const int wclass = J.wclass;
+    L.walk.n = L.n;
+    L.walk.ord = L.ord;
+    L.walk.so = J.so;
+    // Allowed weight classes of a graded walk: one class (constant
+    // weight), the even ones (self-orthogonal) or all of them.
+    L.classes = wclass > 0 ? 1ull << (wclass - 1) : (L.walk.so ? 0x5555555555555555ull : ~0ull);
+    L.p_start = J.p_start;
+    L.m_start = J.m_start;
+    L.total = J.p_stop;
+    L.cnt_near = L.cnt_deep = L.cnt_pairs = 0;
+  }
+  __syncthreads();
+  init_tables(L.tab, L.walk, L.classes, J.basis);
+  if (tid == 0) {
+    // The walk's length: 2^n positions (2^(n-1) self-orthogonal) for the
+    // positional walks, the sizes of the allowed classes for graded ones.
+    const bool positional = L.ord == GC_LEX || L.ord == GC_GRAY || L.ord == GC_BORDER;
+    const unsigned long long len = positional ? (1ull << (L.n - (L.walk.so ? 1 : 0))) : L.tab.off[33];
+    if (L.total == 0 || L.total > len) L.total = len;
+  }
+  __syncthreads();
+}
+
+__device__ __forceinline__ void start_ctl(Ctl *c, const Job &J) {
+  c->m = J.m_start;
+  c->p = J.p_start;
+  c->w = kWMin;
+  c->status = 0;
+  c->action = ACT_NEXT;
+  c->ndeep = 0;
+  c->stat_windows = c->stat_rounds = c->stat_surv = 0;
+  c->stat_near = c->stat_deep = c->stat_pairs = 0;
+  c->ticks[0] = c->ticks[1] = c->ticks[2] = c->ticks[3] = 0;
+}
+
+// A finished job's outputs but `done`; by one thread.
+__device__ __forceinline__ void write_outputs(const Job &J, Job *out, Ctl *c) {
+  // All reads first: one round trip.
+  const unsigned long long m = ld_relaxed(&c->m), windows = ld_relaxed(&c->stat_windows),
+                           rounds = ld_relaxed(&c->stat_rounds), survivors = ld_relaxed(&c->stat_surv),
+                           near = ld_relaxed(&c->stat_near), deep = ld_relaxed(&c->stat_deep),
+                           pairs = ld_relaxed(&c->stat_pairs), t0 = ld_relaxed(&c->ticks[0]),
+                           t1 = ld_relaxed(&c->ticks[1]), t2 = ld_relaxed(&c->ticks[2]), t3 = ld_relaxed(&c->ticks[3]);
+  const int status = ld_relaxed(&c->status);
+  if (J.count) *J.count = m;
+  st_sys(&out->out_count, m);
+  st_sys(&out->windows, windows);
+  st_sys(&out->rounds, rounds);
+  st_sys(&out->survivors, survivors);
+  st_sys(&out->chk_near, near);
+  st_sys(&out->chk_deep, deep);
+  st_sys(&out->chk_pairs, pairs);
+  st_sys(&out->ticks_near, t0);
+  st_sys(&out->ticks_surv, t1);
+  st_sys(&out->ticks_resolve, t2);
+  st_sys(&out->ticks_deep, t3);
+  st_sys(&out->status, status);
+  st_sys(&out->t_done, (unsigned long long)wall_clock64());
+}
+
 // Body of the persistent kernel: the team claims jobs until the queue is empty
 // (batch), the host shuts it down or it stays idle too long (server).
 // kLinear: jobs may be linear (batch and server; a single linear code has
@@ -1601,15 +1690,7 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
         if (j >= 0) {
           const Job &J = *reinterpret_cast<const Job *>(L.in);
           st_sys(&P.out[j].t_claim, (unsigned long long)wall_clock64());
-          c->m = J.m_start;
-          c->p = J.p_start;
-          c->w = kWMin;
-          c->status = 0;
-          c->action = ACT_NEXT;
-          c->ndeep = 0;
-          c->stat_windows = c->stat_rounds = c->stat_surv = 0;
-          c->stat_near = c->stat_deep = c->stat_pairs = 0;
-          c->ticks[0] = c->ticks[1] = c->ticks[2] = c->ticks[3] = 0;
+          start_ctl(c, J);
         }
       }
     }
@@ -1634,54 +1715,9 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
     if (L.job < 0 || L.abort) break;
 
     const Job &J = *reinterpret_cast<const Job *>(L.in);
-    if (tid == 0) {
-      L.n = J.n;
-      L.d = J.d;
-      L.ord = J.ord;
-      // Defaults by ordering (measured on the n=24..28 screens): graded
-      // orders reject many candidates deep in the code, so they screen the
-      // whole code up front; lex screens the newest 16K words and Gray the
-      // newest 8K (where almost every rejected candidate meets its killer),
-      // and both then deep-scan every survivor once.
-      const bool graded = L.ord == GC_GRLEX || L.ord == GC_GREVLEX;
-      const int mode = J.mode;
-      L.mode = mode ? mode : MODE_DEEP_ALL;
-      const unsigned long long nd = J.near_depth;
-      L.near_depth = nd ? nd : (graded ? ~0ull : (L.ord == GC_GRAY ? kDefaultNearGray : kDefaultNear));
-      const unsigned int tg = J.target;
-      L.target = tg ? (tg > (unsigned int)kSMax ? (unsigned int)kSMax : (tg < 16 ? 16 : tg))
-                    : (graded ? kDefaultTarget : kDefaultTargetLinear);
-      L.code = J.code;
-      L.capacity = J.capacity;
-      const unsigned int dt = J.deep_tile;
-      L.deep_tile = dt ? dt : (unsigned int)kTile;
-      L.mfma = J.valu_screen == 0;
-      L.linear = J.linear;
-      L.by_cover = J.cover;
-      const int wclass = J.wclass;
-      L.walk.n = L.n;
-      L.walk.ord = L.ord;
-      L.walk.so = J.so;
-      // Allowed weight classes of a graded walk: one class (constant
-      // weight), the even ones (self-orthogonal) or all of them.
-      L.classes = wclass > 0 ? 1ull << (wclass - 1) : (L.walk.so ? 0x5555555555555555ull : ~0ull);
-      L.p_start = J.p_start;
-      L.m_start = J.m_start;
-      L.total = J.p_stop;
-      L.cnt_near = L.cnt_deep = L.cnt_pairs = 0;
-    }
-    __syncthreads();
-    init_tables(L.tab, L.walk, L.classes, J.basis);
-    if (tid == 0) {
-      // The walk's length: 2^n positions (2^(n-1) self-orthogonal) for the
-      // positional walks, the sizes of the allowed classes for graded ones.
-      const bool positional = L.ord == GC_LEX || L.ord == GC_GRAY || L.ord == GC_BORDER;
-      const unsigned long long len = positional ? (1ull << (L.n - (L.walk.so ? 1 : 0))) : L.tab.off[33];
-      if (L.total == 0 || L.total > len) L.total = len;
-    }
-    __syncthreads();
+    load_job(L);
     if (L.d <= 1 && !L.walk.so) emit_ordering(L, W);
-    else if ((!kLinear || !L.linear || !build_linear(L, P, W)) && (!L.by_cover || !build_cover<SO>(L, P, W))) {
+    else if ((!kLinear || !L.linear || !build_linear(L, P, W)) && (!L.by_cover || !build_cover<SO>(L, W, &P.dq->abort, P.spin_limit))) {
       build_code<SO>(L, P, W);
       screened = true;
     }
@@ -1722,27 +1758,7 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
     if (L.team_rank == 0 && tid == 0) {
       Job *out = &P.out[L.job];
       Ctl *c = W.ctl;
-      // All reads first: one round trip.
-      const unsigned long long m = ld_relaxed(&c->m), windows = ld_relaxed(&c->stat_windows),
-                               rounds = ld_relaxed(&c->stat_rounds), survivors = ld_relaxed(&c->stat_surv),
-                               near = ld_relaxed(&c->stat_near), deep = ld_relaxed(&c->stat_deep),
-                               pairs = ld_relaxed(&c->stat_pairs), t0 = ld_relaxed(&c->ticks[0]),
-                               t1 = ld_relaxed(&c->ticks[1]), t2 = ld_relaxed(&c->ticks[2]), t3 = ld_relaxed(&c->ticks[3]);
-      const int status = ld_relaxed(&c->status);
-      if (J.count) *J.count = m;
-      st_sys(&out->out_count, m);
-      st_sys(&out->windows, windows);
-      st_sys(&out->rounds, rounds);
-      st_sys(&out->survivors, survivors);
-      st_sys(&out->chk_near, near);
-      st_sys(&out->chk_deep, deep);
-      st_sys(&out->chk_pairs, pairs);
-      st_sys(&out->ticks_near, t0);
-      st_sys(&out->ticks_surv, t1);
-      st_sys(&out->ticks_resolve, t2);
-      st_sys(&out->ticks_deep, t3);
-      st_sys(&out->status, status);
-      st_sys(&out->t_done, (unsigned long long)wall_clock64());
+      write_outputs(J, out, c);
       // (A batch's host reads after the launch, which writes everything back.)
       if (P.njobs_fixed >= 0) st_sys(&out->done, 1u);
       else __hip_atomic_store(&out->done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -1770,6 +1786,89 @@ __global__ void __launch_bounds__(kBlock) greedy_server_kernel(Params P) {
 // (a kernel of its own, so the plain screen's registers are unaffected).
 __global__ void __launch_bounds__(kBlock) greedy_code_so_kernel(Params P) {
   persistent_body<true, false>(g_lds, P);
+}
+
+// One code by cover marks, as an ordinary launch: the workgroups of the XCD
+// that the first one to arrive is on, as many as are there when that one
+// closes the team.  Every member runs before it can be waited for, so the team
+// needs no cooperative launch, which costs a call 50 us more (n = 1: 80 us by
+// the persistent kernel, 33 us here).  Workgroups of other XCDs, and
+// those that come too late, leave at once.
+constexpr unsigned int kCovClosed = 1u << 16;
+constexpr unsigned long long kCovJoinTicks = 2000;  // 20 us (100 MHz)
+
+struct CoverArgs {
+  Job job;
+  Job *out;               // outputs; done: 1 built, 2 not (too few workgroups came on one XCD), 0 a wait expired
+  char *team_ws;
+  CoverCtl *ctl;          // zero between launches
+  unsigned int want;      // workgroups of the team
+  unsigned int spin_limit;
+};
+
+__device__ __forceinline__ void cover_join(Lds &L, const CoverArgs &A, CoverWs *ws) {
+  CoverCtl *const c = A.ctl;
+  const unsigned int here = xcc_id() + 1;
+  unsigned int seen = 0, rank = ~0u, size = 1;
+  if (gridDim.x == 1 || __hip_atomic_compare_exchange_strong(&c->xcd, &seen, here, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                            __HIP_MEMORY_SCOPE_AGENT) || seen == here)
+    rank = gridDim.x == 1 ? 0u : __hip_atomic_fetch_add(&c->members, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (rank == 0) {
+    __hip_atomic_store(&ws->arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_waitcnt(0);
+    if (gridDim.x > 1) {
+      const unsigned long long t0 = wall_clock64();
+      while (ld_relaxed(&c->members) < A.want && (unsigned long long)wall_clock64() - t0 < kCovJoinTicks)
+        __builtin_amdgcn_s_sleep(1);
+      size = __hip_atomic_fetch_or(&c->members, kCovClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&c->size, size, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  } else if (rank < kCovClosed) {
+    unsigned int spins = 0;
+    while ((size = ld_relaxed(&c->size)) == 0) {
+      __builtin_amdgcn_s_sleep(1);
+      if (++spins > A.spin_limit) {
+        __hip_atomic_store(&c->abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        break;
+      }
+    }
+  }
+  L.sub_rank = rank < kCovClosed ? rank : ~0u;
+  L.sub_size = size;
+  L.abort = size == 0;
+}
+
+template <bool SO>
+__global__ void __launch_bounds__(kBlock) cover_kernel(CoverArgs A) {
+  Lds &L = g_lds;
+  const int tid = threadIdx.x;
+  const TeamWs W = team_ws(A.team_ws);
+  if (tid == 0) cover_join(L, A, W.cover);
+  if (tid < kJobInputWords) L.in[tid] = reinterpret_cast<const uint32_t *>(&A.job)[tid];
+  __syncthreads();
+  if (L.sub_rank != ~0u && !L.abort) {
+    const Job &J = *reinterpret_cast<const Job *>(L.in);
+    if (L.sub_rank == 0 && tid == 0) {
+      st_sys(&A.out->t_claim, (unsigned long long)wall_clock64());
+      start_ctl(W.ctl, J);
+    }
+    load_job(L);
+    const bool built = build_cover<SO>(L, W, &A.ctl->abort, A.spin_limit);
+    if (L.sub_rank == 0 && tid == 0 && !L.abort) {
+      if (built) write_outputs(J, A.out, W.ctl);
+      __hip_atomic_store(&A.ctl->built, built ? 1u : 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  // The last workgroup to leave tells how it ended (a wait may have expired in
+  // any of them) and clears the join state.
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (tid == 0 && __hip_atomic_fetch_add(&A.ctl->left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x) {
+    st_sys(&A.out->done, ld_relaxed(&A.ctl->abort) ? 0u : ld_relaxed(&A.ctl->built));
+    unsigned int *const w = reinterpret_cast<unsigned int *>(A.ctl);
+    for (unsigned int i = 0; i < sizeof(CoverCtl) / 4; ++i)
+      __hip_atomic_store(&w[i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 
 // Reset of the barrier block and the device queue before a launch (a kernel
@@ -1812,6 +1911,7 @@ __global__ void init_job_kernel(Bar *bar, DevQueue *dq, Job *dst, Job job) {
 constexpr size_t kScratchBytes =
     align256(sizeof(Bar)) + align256(sizeof(DevQueue)) + align256(sizeof(Job)) + kTeamWsBytes;
 static __device__ __align__(256) char scratch[kScratchBytes];
+static __device__ CoverCtl scratch_ctl;   // its cover team's join state
 
 // ---------------------------------------------------------------------------
 // Measurement probes (the roofline's denominator and the barrier latency)
@@ -2002,7 +2102,7 @@ int acquire_workspace(size_t bytes, char **ptr, int *slot) {
   char *p = nullptr;
   const hipError_t e = hipMalloc((void **)&p, rounded);
   if (e != hipSuccess) return fail(GC_ENOMEM, "workspace of %zu bytes: %s", rounded, hipGetErrorString(e));
-  g_ws.push_back(WsEntry{dev, p, rounded, true, WsHost{nullptr, nullptr, nullptr, nullptr}});
+  g_ws.push_back(WsEntry{dev, p, rounded, true, WsHost{}});
   *ptr = p;
   *slot = (int)g_ws.size() - 1;
   return GC_OK;
@@ -2013,8 +2113,8 @@ void release_workspace(int slot) {
   if (slot >= 0 && (size_t)slot < g_ws.size()) g_ws[slot].busy = false;
 }
 
-// Pinned block and events of a workspace in use (kept with it; the pool holds
-// one per concurrent call).
+// Pinned block, join state and events of a workspace in use (kept with it; the
+// pool holds one per concurrent call).
 int workspace_host(int slot, WsHost *out) {
   std::lock_guard<std::mutex> lk(g_ws_mu);
   WsHost &h = g_ws[slot].host;
@@ -2022,6 +2122,12 @@ int workspace_host(int slot, WsHost *out) {
   if (!h.ptr) {
     e = hipHostMalloc((void **)&h.ptr, kWsHostBytes, hipHostMallocCoherent | hipHostMallocMapped);
     if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&h.dev, h.ptr, 0);
+  }
+  if (e == hipSuccess && !h.ctl) {
+    // A copy, done when it returns: the first launch may be on any stream.
+    const CoverCtl zero{};
+    e = hipMalloc((void **)&h.ctl, sizeof(CoverCtl));
+    if (e == hipSuccess) e = hipMemcpy(h.ctl, &zero, sizeof(zero), hipMemcpyHostToDevice);
   }
   if (e == hipSuccess && !h.begin) e = hipEventCreate(&h.begin);
   if (e == hipSuccess && !h.end) e = hipEventCreate(&h.end);
@@ -2112,6 +2218,65 @@ int run_batch(Job *jobs, int njobs, int nteams, unsigned int grid_req, hipStream
   // An expired wait ends the launch: some job is not done.
   for (int i = 0; i < njobs; ++i)
     if (!jobs[i].done) return fail(GC_ETIMEOUT, "a bounded device-side wait expired");
+  return GC_OK;
+}
+
+// Builds a cover job with a launch of its own and waits for it; outputs into
+// *J.  `fixed`: a workspace to use instead of the pool, with its join state
+// (may be null).  *built stays false when too few workgroups came to one XCD:
+// the persistent kernel then builds the code.
+int run_cover(Job *J, hipStream_t stream, char *fixed, CoverCtl *fixed_ctl, float *kernel_ms, bool *built) {
+  *built = false;
+  int dev = 0, cus = 0, coop = 0, bpc = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  int rc = device_info(dev, &cus, &coop, &bpc);
+  if (rc) return rc;
+  const LaunchLayout lay = launch_layout(1, 1);
+  char *ws = fixed;
+  int slot = -1;
+  WsHost host{};
+  if (!fixed) {
+    rc = acquire_workspace(lay.bytes, &ws, &slot);
+    if (rc) return rc;
+    rc = workspace_host(slot, &host);
+    if (rc) {
+      release_workspace(slot);
+      return rc;
+    }
+  }
+  Job *const seen = reinterpret_cast<Job *>(host.ptr);
+  CoverArgs A;
+  A.job = *J;
+  A.job.done = 0;
+  A.out = seen ? reinterpret_cast<Job *>(host.dev) : reinterpret_cast<Job *>(ws + lay.off_jobs);
+  A.team_ws = ws + lay.off_ws;
+  A.ctl = fixed ? fixed_ctl : host.ctl;
+  A.want = cover_team_size(J->n, J->d, J->so != 0, kCovTeam);
+  A.spin_limit = spin_limit_from_env();
+  if (seen) *seen = A.job;
+  // Workgroups go to the XCDs in turn: `want` for each of eight.
+  const unsigned int grid = A.want == 1 ? 1u : std::min<unsigned int>(8 * A.want, (unsigned int)cus);
+  hipError_t e = kernel_ms ? hipEventRecord(host.begin, stream) : hipSuccess;
+  if (e == hipSuccess) {
+    if (J->so) hipLaunchKernelGGL(cover_kernel<true>, dim3(grid), dim3(kBlock), 0, stream, A);
+    else hipLaunchKernelGGL(cover_kernel<false>, dim3(grid), dim3(kBlock), 0, stream, A);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess && kernel_ms) e = hipEventRecord(host.end, stream);
+  Job res = A.job;
+  if (e == hipSuccess && !seen) e = hipMemcpyAsync(&res, A.out, sizeof(Job), hipMemcpyDeviceToHost, stream);
+  const hipError_t es = hipStreamSynchronize(stream);
+  if (e == hipSuccess) e = es;
+  if (e == hipSuccess && kernel_ms) e = hipEventElapsedTime(kernel_ms, host.begin, host.end);
+  if (e == hipSuccess && seen) res = *seen;
+  if (es == hipSuccess) release_workspace(slot);
+  if (e != hipSuccess) return fail(GC_EDEVICE, "cover kernel failed: %s", hipGetErrorString(e));
+  if (res.done == 0) return fail(GC_ETIMEOUT, "a bounded device-side wait expired");
+  if (res.done != 1) return GC_OK;
+  // Outputs only: the inputs of a device-side record are not kept.
+  memcpy(reinterpret_cast<char *>(J) + offsetof(Job, out_count), reinterpret_cast<char *>(&res) + offsetof(Job, out_count),
+         sizeof(Job) - offsetof(Job, out_count));
+  *built = true;
   return GC_OK;
 }
 
@@ -2212,20 +2377,23 @@ int job_result(const Job &J, uint64_t capacity) {
 // device with that device current.
 std::mutex g_scratch_mu;
 char *g_scratch_ptr[64];
+CoverCtl *g_scratch_ctl[64];
 
-int scratch_address(char **out) {
+int scratch_address(char **out, CoverCtl **ctl) {
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));
   if (dev < 0 || dev >= 64) return fail(GC_EDEVICE, "device ordinal %d out of range", dev);
   std::lock_guard<std::mutex> lk(g_scratch_mu);
   if (!g_scratch_ptr[dev]) {
     void *ptr = nullptr;
-    const hipError_t e = hipGetSymbolAddress((void **)&ptr, HIP_SYMBOL(scratch));
+    hipError_t e = hipGetSymbolAddress((void **)&ptr, HIP_SYMBOL(scratch));
+    if (e == hipSuccess) e = hipGetSymbolAddress((void **)&g_scratch_ctl[dev], HIP_SYMBOL(scratch_ctl));
     if (e != hipSuccess || !ptr)
       return fail(GC_EDEVICE, "hipGetSymbolAddress(scratch) failed on device %d: %s", dev, hipGetErrorString(e));
     g_scratch_ptr[dev] = static_cast<char *>(ptr);
   }
   *out = g_scratch_ptr[dev];
+  *ctl = g_scratch_ctl[dev];
   return GC_OK;
 }
 
@@ -2439,6 +2607,15 @@ int greedy_code_problem_device(const gc_problem *p, uint32_t *d_words, uint64_t 
     }
   }
   J.cover = cover_job(J) && !(tuning && tuning->grid_blocks);
+  if (J.cover) {
+    bool built = false;
+    rc = run_cover(&J, stream, nullptr, nullptr, stats ? &ms : nullptr, &built);
+    if (rc) return rc;
+    if (built) {
+      copy_stats(stats, J, ms);
+      return job_result(J, capacity);
+    }
+  }
   rc = run_batch(&J, 1, 1, tuning ? tuning->grid_blocks : 0, stream, stats ? &ms : nullptr,
                  p->self_orthogonal ? LaunchKind::kSingleSO : LaunchKind::kSingle);
   if (rc) return rc;
@@ -2477,7 +2654,8 @@ int greedy_code_device_noalloc(int n, int d, int ordering, uint32_t *d_words, ui
     return fail(GC_EINVAL, "the launch needs %zu bytes of scratch, the library holds %zu", lay.bytes,
                 kScratchBytes);
   char *base = nullptr;
-  rc = scratch_address(&base);
+  CoverCtl *ctl = nullptr;
+  rc = scratch_address(&base, &ctl);
   if (rc) return rc;
   Job J;
   fill_job(&J, n, d, ordering, d_words, capacity, d_count, nullptr);
@@ -2489,6 +2667,12 @@ int greedy_code_device_noalloc(int n, int d, int ordering, uint32_t *d_words, ui
     if (built) return job_result(J, capacity);
   }
   J.cover = cover_job(J);
+  if (J.cover) {
+    bool built = false;
+    rc = run_cover(&J, stream, base, ctl, nullptr, &built);
+    if (rc) return rc;
+    if (built) return job_result(J, capacity);
+  }
   unsigned int grid = 0;
   rc = pick_grid(0, &grid);
   if (rc) return rc;
@@ -2722,7 +2906,9 @@ int greedy_code_tune(int n, int d, int ordering, void *hip_stream, gc_tuning *be
     fill_job(&J, n, d, ordering, words, cap, nullptr, &t);
     bool built = false;
     J.cover = cover_job(J);
-    int r = linear_job(J) ? run_linear(&J, st, nullptr, 0, ms, &built) : GC_OK;
+    int r = linear_job(J) ? run_linear(&J, st, nullptr, 0, ms, &built)
+            : J.cover     ? run_cover(&J, st, nullptr, nullptr, ms, &built)
+                          : GC_OK;
     if (r == GC_OK && !built) r = run_batch(&J, 1, 1, 0, st, ms, LaunchKind::kSingle);
     if (r) return r;
     r = job_result(J, cap);
