@@ -44,8 +44,10 @@ struct CoverLds {
       unsigned long long wball[8][64];   // as ball, radius -1 (none) .. 6 (every bit)
       alignas(16) uint32_t cand[kCovWin];  // the window's candidates, in walk order
       alignas(16) uint32_t took[kCovWin];  // those accepted
-      unsigned long long accm[kCovBlocks];   // accepted, by block of 64 candidates
-      uint3 run[kCovLevels * kCovTeam];  // per (level, slice): place in the window, length, place in its list
+      alignas(16) uint32_t block[2][64];   // those of a block of 64 candidates, up to a multiple of eight
+      unsigned int taken[kCovBlocks];      // how many of each block
+      uint2 run[kCovLevels * kCovTeam];    // per (level, slice): place in the window, place in its list
+      uint2 sums[32];                      // per wave: candidates of four levels, 16 bits each
       uint32_t basis[32], pick;          // self-orthogonal: a basis of the code's span
       int dim;
       unsigned int size, done_levels, listed;  // the window's candidates; levels it takes whole, and at all
@@ -60,7 +62,6 @@ struct CoverWs {
     struct {                                                 // windows
       uint32_t list[2][kCovTeam][kCovWin];                   // candidates a slice lists
       unsigned int head[2][kCovTeam][16];                    // levels listed, cut short?, candidates of each level
-      unsigned long long adj[64 * kCovBlocks * (kCovBlocks + 1) / 2];  // earlier neighbours, 64 x 64 tiles
     };
   };
   uint32_t seg[2][kCovTeam][kCovSeg];                    // words accepted in a round, by slice

@@ -533,16 +533,15 @@ __device__ __noinline__ void cover_team(CoverWs *ws_v, Ctl *ctl_v, unsigned int 
 #include "cover_windows.h"
 
 // A graded code by cover marks.  The team's workgroups on one XCD build it,
-// while the others wait at the barrier that ends the job.  Rounds: one
-// workgroup up to 1024 words (n = 16: 368 us against 429 us with two), then as
-// many (a power of two) as give each 512 words or more (n = 20, d = 3: 1.22
-// ms with 32 workgroups, 1.52 ms with 8, 2.22 ms with 2).  Windows share out
-// their conflict graphs, so workgroups pay from 8 words each (n = 16, d = 5:
-// 220 us with 32, 294 us with one).  False (alike in every workgroup) when
-// the slices would not fit.
+// while the others wait at the barrier that ends the job: as many (a power of
+// two) as give each 512 words or more (rounds, n = 20, d = 3: 1.22 ms with 32
+// workgroups, 1.52 ms with 8, 2.22 ms with 2; windows, n = 14, d = 5: 102 us
+// with one, 120 us with 32; n = 18, d = 5 216 us with 8, 230 us with 4), by
+// rounds from 1024 words on (n = 16: 368 us with one, 429 us with two).  False
+// (alike in every workgroup) when the slices would not fit.
 constexpr unsigned int cover_team_size(int n, int d, bool self, unsigned int workgroups) {
   const unsigned int words = n > 6 ? 1u << (n - 6) : 1u, most = workgroups < kCovTeam ? workgroups : kCovTeam;
-  const unsigned int least = self || d > kCovMaxD ? 8u : words > 1024 ? 512u : 1024u;  // words of a slice
+  const unsigned int least = self || d > kCovMaxD || words > 1024 ? 512u : 1024u;  // words of a slice
   unsigned int team = 1;
   while (2 * team <= most && words / (2 * team) >= least) team *= 2;
   return team;

@@ -3,21 +3,23 @@
 //
 // With a larger distance a level takes many short rounds, each a walk over
 // many neighbour words.  Here the team lists the first 1024 undecided
-// candidates in walk order, computes their
-// conflict graph from their distances (64 x 64 tiles, shared out to all
-// waves: three instructions a pair), and every workgroup finds the greedy's
-// choice among them for itself: a wave holds the conflicts of its block of 64
-// candidates in registers, and the blocks are decided in turn.  Each
-// workgroup then marks the balls of the accepted words in its slice, which
-// removes every candidate of the window.  Two XCD-local barriers a window.
+// candidates in walk order, and every workgroup finds the greedy's choice
+// among them for itself: a wave holds the conflicts inside its block of 64
+// candidates, the blocks are decided in turn, and the later ones compare
+// themselves with the words accepted (three instructions a pair, and of 1024
+// candidates some 110 are accepted at n = 22, d = 5).  Each workgroup then
+// marks the balls of the accepted words in its slice, which removes every
+// candidate of the window.  One XCD-local barrier a window, after the lists.
+// (With the whole conflict graph, shared out to the team, and a second
+// barrier: n = 22, d = 5 884 us against 805 us, n = 10, d = 5 73 and 53 us.)
 //
 // Self-orthogonal codes (kSelf; every distance): a pair clashes also when its
 // overlap is odd, and of the words accepted so far a basis is kept.  A new
 // basis word (at most n / 2 times) removes the candidates it overlaps oddly
 // from the bitmap, a word of 64 at a time.
 //
-// What bounds it: about 25 us a window at n = 22, d = 5 (listing 4, waiting
-// for the busiest slice 4, gathering 2.4, graph 2.5, choice 6.5, marks 4), and
+// What bounds it: about 21 us a window at n = 22, d = 5 (listing 2.6, waiting
+// for the busiest slice 3.5, gathering 1.7, choice 10, marks 3.4), and
 // from n = 24 on the LDS throughput of the marks, uneven over the slices: a
 // window's words are neighbours in the walk, so the slices near them mark
 // most (slices taken from lower bits, which share the marks evenly, need a
@@ -244,36 +246,54 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws_v, Ctl *ctl_v, unsign
   unsigned int windows = 0, par = 0;
   int level = first;
   while (level <= last) {
-    // This slice's first undecided candidates, level by level.
+    // This slice's first undecided candidates, level by level; counted four
+    // levels at a time (a lane's counts, and a wave's sums, fit 16 bits each).
     unsigned int listed = 0, levels = 0;
     bool cut = false;
-    for (; levels < (unsigned int)kCovLevels && level + (int)levels <= last && listed < share && !cut; ++levels) {
-      const int w = level + (int)levels, k = 32 + (rev ? n - w : w);
-      unsigned int mine = 0;
-      if (L.tab.off[w + 1] > L.tab.off[w])  // (a weight: the other levels have no candidates)
-        for (unsigned int i = w0; i < w0 + per && i < words; ++i)
-          mine += (unsigned int)__builtin_popcountll(C.level[k - __builtin_popcount(high + i)] & ~C.dead[i]);
-      unsigned int at = wave_scan(mine), all = 0;
-      if (lane == 63) C.wsum[16 * (levels & 1) + wave] = at;
+    while (levels < (unsigned int)kCovLevels && level + (int)levels <= last && listed < share && !cut) {
+      unsigned long long mine = 0;
+      const int w4 = level + (int)levels;
+      for (unsigned int i = w0; i < w0 + per && i < words; ++i) {
+        const unsigned long long left = ~C.dead[i];
+        const int k = 32 + (rev ? n - w4 : w4) - __builtin_popcount(high + i);
+#pragma unroll
+        for (int l = 0; l < 4; ++l)
+          mine += (unsigned long long)__builtin_popcountll(left & C.level[rev ? k - l : k + l]) << (16 * l);
+      }
+      const unsigned int lo2 = wave_scan((unsigned int)mine), hi2 = wave_scan((unsigned int)(mine >> 32));
+      const unsigned int buf = 16 * ((levels >> 2) & 1);
+      if (lane == 63) C.sums[buf + wave] = make_uint2(lo2, hi2);
       __syncthreads();
-      at += listed - mine;
+      unsigned int at4[4] = {lo2 & 0xffffu, lo2 >> 16, hi2 & 0xffffu, hi2 >> 16}, all4[4] = {};
 #pragma unroll
       for (int wv = 0; wv < kWaves; ++wv) {
-        const unsigned int sum = C.wsum[16 * (levels & 1) + wv];
-        if (wv < wave) at += sum;
-        all += sum;
+        const uint2 sum = C.sums[buf + wv];
+        const unsigned int of[4] = {sum.x & 0xffffu, sum.x >> 16, sum.y & 0xffffu, sum.y >> 16};
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+          if (wv < wave) at4[l] += of[l];
+          all4[l] += of[l];
+        }
       }
-      if (mine)
-        for (unsigned int i = w0; i < w0 + per && i < words; ++i)
-          for (unsigned long long f = C.level[k - __builtin_popcount(high + i)] & ~C.dead[i];
-               f && at < (unsigned int)kCovWin; f &= f - 1, ++at)
-            as_global(ws->list[par][rank])[at] = 64u * (high + i) + __builtin_ctzll(f);
-      if (listed + all > (unsigned int)kCovWin) {
-        all = kCovWin - listed;
-        cut = true;
+#pragma unroll
+      for (int l = 0; l < 4; ++l) {
+        if (cut || listed >= share || w4 + l > last) break;
+        const unsigned int own = (unsigned int)(mine >> (16 * l)) & 0xffffu;
+        unsigned int at = listed + at4[l] - own, all = all4[l];
+        if (own && at < (unsigned int)kCovWin)
+          for (unsigned int i = w0; i < w0 + per && i < words; ++i) {
+            const int k = 32 + (rev ? n - w4 - l : w4 + l) - __builtin_popcount(high + i);
+            for (unsigned long long f = C.level[k] & ~C.dead[i]; f && at < (unsigned int)kCovWin; f &= f - 1, ++at)
+              as_global(ws->list[par][rank])[at] = 64u * (high + i) + __builtin_ctzll(f);
+          }
+        if (listed + all > (unsigned int)kCovWin) {
+          all = kCovWin - listed;
+          cut = true;
+        }
+        if (tid == 0) as_global(ws->head[par][rank])[2 + levels] = all;
+        listed += all;
+        ++levels;
       }
-      if (tid == 0) as_global(ws->head[par][rank])[2 + levels] = all;
-      listed += all;
     }
     if (tid == 0) {
       as_global(ws->head[par][rank])[0] = levels;
@@ -301,7 +321,7 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws_v, Ctl *ctl_v, unsign
         if (cuts && lane > (int)__builtin_ctzll(cuts)) own = 0;
         const unsigned int at = wave_scan(own);
         if (in) {
-          C.run[l * kCovTeam + lane] = make_uint3(before + at - own, own, from);
+          C.run[l * kCovTeam + lane] = make_uint2(before + at - own, from);
           from += own;
         }
         before += (unsigned int)__builtin_amdgcn_readlane((int)at, 63);
@@ -319,67 +339,75 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws_v, Ctl *ctl_v, unsign
     }
     __syncthreads();
     const unsigned int size = C.size, complete = C.done_levels;
-    // Copy: a wave takes a slice's run of a level at a time.
-    const unsigned int runs = C.listed * team;
-    for (unsigned int e = wave; e < runs; e += kWaves) {
-      const uint3 run = C.run[(e >> slice_bits) * kCovTeam + (e & (team - 1))];
-      for (unsigned int i = lane; i < run.y && run.x + i < (unsigned int)kCovWin; i += 64)
-        C.cand[run.x + i] = cover_ld(&ws->list[par][e & (team - 1)][run.z + i]);
+    // A thread finds its candidate's run (the last one that begins at or before
+    // it) and copies it.
+    if ((unsigned int)tid < size) {
+      unsigned int lo = 0, hi = C.listed * team;
+      while (hi - lo > 1) {
+        const unsigned int mid = (lo + hi) >> 1;
+        if (C.run[(mid >> slice_bits) * kCovTeam + (mid & (team - 1))].x <= (unsigned int)tid) lo = mid;
+        else hi = mid;
+      }
+      const unsigned int slice = lo & (team - 1);
+      const uint2 run = C.run[(lo >> slice_bits) * kCovTeam + slice];
+      C.cand[tid] = cover_ld(&ws->list[par][slice][run.y + (unsigned int)tid - run.x]);
     }
     __syncthreads();
-    // Conflict graph: earlier neighbours, 64 x 64 tiles.
-    const unsigned int blocks = (size + 63) / 64, tiles = blocks * (blocks + 1) / 2;
-    for (unsigned int t = (unsigned int)wave * team + rank; t < tiles; t += kWaves * team) {
-      unsigned int I = 0;
-      while ((I + 1) * (I + 2) / 2 <= t) ++I;
-      const unsigned int J = t - I * (I + 1) / 2, j = 64 * I + lane;
-      unsigned long long mask = clash_mask<kSelf>(&C.cand[64 * J], C.cand[j], d, odd);
-      mask &= I == J ? lanemask_lt() : ~0ull;
-      if (j >= size) mask = 0;
-      as_global(ws->adj)[64 * t + lane] = mask;
-    }
-    cover_barrier(ws, team, abort_flag, limit);
-    if (L.abort) return;
-    // The greedy's choice.  A wave keeps the conflicts of its block; a block
-    // is decided once every earlier one is.
-    unsigned long long row[kCovBlocks];
-#pragma unroll
-    for (int J = 0; J < kCovBlocks; ++J)
-      row[J] = J <= wave && wave < (int)blocks ? cover_ld(&ws->adj[64 * (wave * (wave + 1) / 2 + J) + lane]) : 0ull;
-    bool killed = (unsigned int)tid >= size;
-#pragma unroll
-    for (int I = 0; I < kCovBlocks; ++I) {
-      if (I < (int)blocks) {
-        if (wave == I) {
-          // The first candidate left is accepted and takes its later
-          // neighbours with it (few words a block: synchronous rounds over
-          // all lanes measured slower, 954 us against 946 us at n = 22, d = 5).
-          unsigned long long acc = 0, und = ballot(!killed);
-          while (und) {
-            const int j = __builtin_ctzll(und);
-            const unsigned int part = j < 32 ? (unsigned int)row[I] : (unsigned int)(row[I] >> 32);
-            acc |= 1ull << j;
-            und &= ~((1ull << j) | ballot((part >> (j & 31)) & 1));
-          }
-          if (lane == 0) C.accm[I] = acc;
+    // The greedy's choice, a block of 64 candidates a wave: its wave decides a
+    // block with the conflicts inside it, once those that clash with a word
+    // accepted in an earlier block are out; the later ones compare themselves
+    // with its words.
+    const unsigned int blocks = (size + 63) / 64;
+    const uint32_t x = C.cand[tid];
+    unsigned long long row = 0;
+    if ((unsigned int)wave < blocks) row = clash_mask<kSelf>(&C.cand[64 * wave], x, d, odd);
+    unsigned int all = 0, least = (unsigned int)tid < size ? ~0u : 0u, mixed = 0;
+    for (unsigned int I = 0; I < blocks; ++I) {
+      if ((unsigned int)wave == I) {
+        __builtin_amdgcn_s_setprio(3);
+        // The first candidate left is accepted and takes its neighbours with
+        // it (itself among them).
+        unsigned long long acc = 0, und = ballot(least >= (unsigned int)d && !(mixed & 1));
+        while (und) {
+          const int j = __builtin_ctzll(und);
+          acc |= 1ull << j;
+          und &= ~(((unsigned long long)(unsigned int)__builtin_amdgcn_readlane((int)(row >> 32), j) << 32) |
+                   (unsigned int)__builtin_amdgcn_readlane((int)row, j));
         }
-        __syncthreads();
-        killed |= (row[I] & C.accm[I]) != 0;
+        const unsigned int got = (unsigned int)__builtin_popcountll(acc);
+        if (lane == 0) C.taken[I] = got;
+        if ((acc >> lane) & 1) {
+          const unsigned int at = (unsigned int)__builtin_popcountll(acc & lanemask_lt());
+          C.took[all + at] = C.block[I & 1][at] = x;
+        } else if (acc) {
+          // Up to a multiple of eight: the last one again.
+          const unsigned int at = got + (unsigned int)__builtin_popcountll(~acc & lanemask_lt());
+          if (at < ((got + 7) & ~7u)) C.block[I & 1][at] = (uint32_t)__builtin_amdgcn_readlane((int)x, 63 - (int)__builtin_clzll(acc));
+        }
+        __builtin_amdgcn_s_setprio(0);
+      }
+      __syncthreads();
+      const unsigned int got = (unsigned int)__builtin_amdgcn_readfirstlane((int)C.taken[I]);
+      all += got;
+      if ((unsigned int)wave > I && (unsigned int)wave < blocks) {
+        if ((unsigned int)wave == I + 1) __builtin_amdgcn_s_setprio(3);
+        for (unsigned int i = 0; i < got; i += 8) {
+          const uint4 *b = reinterpret_cast<const uint4 *>(&C.block[I & 1][i]);
+          const uint4 t = b[0], u = b[1];
+          least = umin3(least, dist(x, t.x), dist(x, t.y));
+          least = umin3(least, dist(x, t.z), dist(x, t.w));
+          least = umin3(least, dist(x, u.x), dist(x, u.y));
+          least = umin3(least, dist(x, u.z), dist(x, u.w));
+          if (kSelf)
+            mixed |= (__builtin_popcount(x & t.x) + odd) | (__builtin_popcount(x & t.y) + odd) |
+                     (__builtin_popcount(x & t.z) + odd) | (__builtin_popcount(x & t.w) + odd) |
+                     (__builtin_popcount(x & u.x) + odd) | (__builtin_popcount(x & u.y) + odd) |
+                     (__builtin_popcount(x & u.z) + odd) | (__builtin_popcount(x & u.w) + odd);
+        }
       }
     }
-    // The accepted words, in order.
-    unsigned int before = 0, all = 0;
-    for (unsigned int I = 0; I < blocks; ++I) {
-      const unsigned int c = (unsigned int)__builtin_popcountll(C.accm[I]);
-      if (I < (unsigned int)wave) before += c;
-      all += c;
-    }
-    if ((unsigned int)wave < blocks && ((C.accm[wave] >> lane) & 1)) {
-      const unsigned int at = before + (unsigned int)__builtin_popcountll(C.accm[wave] & lanemask_lt());
-      const uint32_t c = C.cand[tid];
-      C.took[at] = c;
-      if (rank == 0 && m + at < capacity) as_global(code)[m + at] = cover_number(c, n, rev);
-    }
+    if (rank == 0 && (unsigned int)tid < all && m + tid < capacity)
+      as_global(code)[m + tid] = cover_number(C.took[tid], n, rev);
     __syncthreads();
     m += all;
     if (m > capacity) break;
