@@ -532,16 +532,27 @@ __device__ __noinline__ void cover_team(CoverWs *ws_v, Ctl *ctl_v, unsigned int 
 
 #include "cover_windows.h"
 
+// Windows or rounds.  Windows for larger distances, and where codes are small:
+// a round passes every level (4 us, with few candidates) and decides what one
+// workgroup does for itself in a window (rounds and windows: n = 10, d = 3 105
+// and 56 us; n = 16, d = 4 288 and 241 us; n = 18, d = 3 739 and 706 us; n = 20,
+// d = 3 1.14 and 2.47 ms; distance 2, where a level is one round: n = 9 63 and
+// 61 us, n = 12 85 and 174 us).
+constexpr bool cover_by_windows(int n, int d, bool self) {
+  return self || d > kCovMaxD || n <= (d > 2 ? 18 : 9);
+}
+
 // A graded code by cover marks.  The team's workgroups on one XCD build it,
 // while the others wait at the barrier that ends the job: as many (a power of
 // two) as give each 512 words or more (rounds, n = 20, d = 3: 1.22 ms with 32
 // workgroups, 1.52 ms with 8, 2.22 ms with 2; windows, n = 14, d = 5: 102 us
 // with one, 120 us with 32; n = 18, d = 5 216 us with 8, 230 us with 4), by
-// rounds from 1024 words on (n = 16: 368 us with one, 429 us with two).  False
-// (alike in every workgroup) when the slices would not fit.
+// rounds more than one from 2048 words on (n = 16: 368 us with one, 429 us with
+// two), at distance 2 256 words or more (n = 17: 179 us, with 512 231 us).
+// False (alike in every workgroup) when the slices would not fit.
 constexpr unsigned int cover_team_size(int n, int d, bool self, unsigned int workgroups) {
   const unsigned int words = n > 6 ? 1u << (n - 6) : 1u, most = workgroups < kCovTeam ? workgroups : kCovTeam;
-  const unsigned int least = self || d > kCovMaxD || words > 1024 ? 512u : 1024u;  // words of a slice
+  const unsigned int least = cover_by_windows(n, d, self) ? 512u : d == 2 ? 256u : words > 1024 ? 512u : 1024u;
   unsigned int team = 1;
   while (2 * team <= most && words / (2 * team) >= least) team *= 2;
   return team;
@@ -552,8 +563,8 @@ __device__ __forceinline__ bool build_cover(Lds &L, const TeamWs &W, int *abort_
   const unsigned int words = L.n > 6 ? 1u << (L.n - 6) : 1u, team = cover_team_size(L.n, L.d, kSelf, L.sub_size);
   if (words / team > (unsigned int)kCovWords) return false;
   if (L.sub_rank < team) {
-    if (!kSelf && L.d <= kCovMaxD) cover_team(W.cover, W.ctl, L.sub_rank, team, abort_flag, limit);
-    else cover_window_team<kSelf>(W.cover, W.ctl, L.sub_rank, team, abort_flag, limit);
+    if (cover_by_windows(L.n, L.d, kSelf)) cover_window_team<kSelf>(W.cover, W.ctl, L.sub_rank, team, abort_flag, limit);
+    else cover_team(W.cover, W.ctl, L.sub_rank, team, abort_flag, limit);
   }
   return true;
 }

@@ -36,8 +36,8 @@ def both(p, prefix_words=None):
     return a.cpu().numpy().view(np.uint32), b.cpu().numpy().view(np.uint32)
 
 
-# n <= 6: one bitmap word; 16 and 17: one workgroup, then four; 18, 19, 20: up
-# to 32.  At n = 20, d = 2 slices accept more words in a round than they may.
+# n <= 6: one bitmap word; 17 to 20: up to 32 workgroups.  At n = 20, d = 2
+# slices accept more words in a round than they may.
 @pytest.mark.parametrize("o", ["grlex", "grevlex"])
 @pytest.mark.parametrize("n,d", [(1, 2), (2, 2), (3, 3), (4, 4), (5, 2), (5, 3), (6, 3), (6, 4), (7, 4), (9, 3), (13, 4),
                                  (16, 3), (16, 4), (17, 2), (17, 3), (18, 4), (19, 3), (20, 2), (20, 4), (21, 3),
@@ -48,9 +48,9 @@ def test_walks(n, d, o):
     assert np.array_equal(got, ref)
 
 
-# Windows: n = 9 and 10: one workgroup, then two; 14 and 15: 16, then 32.  At
-# n = 16, d = 16 a window lists many levels; at n = 19, d = 12 and 22, d = 9 a
-# slice alone has more candidates of a level than a window takes.
+# Windows: one workgroup up to n = 15, two at 16, 32 from 20 on.  At n = 16,
+# d = 16 a window lists many levels; at n = 19, d = 12 and 22, d = 9 a slice
+# alone has more candidates of a level than a window takes.
 @pytest.mark.parametrize("o", ["grlex", "grevlex"])
 @pytest.mark.parametrize("n,d", [(1, 5), (3, 9), (5, 5), (6, 6), (7, 5), (9, 5), (10, 6), (11, 5), (13, 7), (14, 5),
                                  (15, 6), (16, 5), (16, 16), (16, 17), (17, 8), (19, 12), (20, 5), (22, 9), (23, 14)])
