@@ -64,7 +64,7 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws_v, Ctl *ctl_v, unsign
   CoverLds &C = g_lds.cover;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const unsigned int rank = __builtin_amdgcn_readfirstlane(rank_v), team = __builtin_amdgcn_readfirstlane(team_v);
-  const int n = __builtin_amdgcn_readfirstlane(L.n), d = __builtin_amdgcn_readfirstlane(L.d);
+  const int n = __builtin_amdgcn_readfirstlane(L.n), d = __builtin_amdgcn_readfirstlane(cover_distance(L));
   const bool rev = L.ord == GC_GREVLEX;
   const int slice_bits = __builtin_ctz(team);
   const unsigned int words = n > 6 ? 1u << (n - 6 - slice_bits) : 1u;
