@@ -47,6 +47,7 @@ struct CoverLds {
       alignas(16) uint32_t block[2][64];   // those of a block of 64 candidates, up to a multiple of eight
       unsigned int taken[kCovBlocks];      // how many of each block
       uint2 run[kCovLevels * kCovTeam];    // per (level, slice): place in the window, place in its list
+      unsigned long long none[32];         // [v]: bits that are no candidates in words of index weight v
       uint2 sums[32];                      // per wave: candidates of four levels, 16 bits each
       uint32_t basis[32], pick;          // self-orthogonal: a basis of the code's span
       int dim;

@@ -225,12 +225,14 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws_v, Ctl *ctl_v, unsign
   __syncthreads();
 
   if (walked != (2u << n) - 1u) {
-    for (unsigned int i = tid; i < words; i += kBlock) {
+    if (tid < 32) {
       unsigned long long none = 0;
       for (int j = 0; j <= 6; ++j)
-        if (!((walked >> (__builtin_popcount(high + i) + j)) & 1)) none |= C.level[32 + j];
-      C.dead[i] |= none;
+        if (!((walked >> (tid + j)) & 1)) none |= C.level[32 + j];
+      C.none[tid] = none;
     }
+    __syncthreads();
+    for (unsigned int i = tid; i < words; i += kBlock) C.dead[i] |= C.none[__builtin_popcount(high + i)];
     __syncthreads();
   }
   // Clock cycles of an accepted word's marks (a third of a cycle each, the
@@ -360,7 +362,11 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws_v, Ctl *ctl_v, unsign
     const unsigned int blocks = (size + 63) / 64;
     const uint32_t x = C.cand[tid];
     unsigned long long row = 0;
-    if ((unsigned int)wave < blocks) row = clash_mask<kSelf>(&C.cand[64 * wave], x, d, odd);
+    // (A basis of n / 2 words: the candidates left are in their span, and no
+    // pair has an odd overlap.)
+    const bool overlaps = kSelf && 2 * C.dim < n;
+    if ((unsigned int)wave < blocks)
+      row = overlaps ? clash_mask<kSelf>(&C.cand[64 * wave], x, d, odd) : clash_mask<false>(&C.cand[64 * wave], x, d, odd);
     unsigned int all = 0, least = (unsigned int)tid < size ? ~0u : 0u, mixed = 0;
     for (unsigned int I = 0; I < blocks; ++I) {
       if ((unsigned int)wave == I) {
@@ -398,7 +404,7 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws_v, Ctl *ctl_v, unsign
           least = umin3(least, dist(x, t.z), dist(x, t.w));
           least = umin3(least, dist(x, u.x), dist(x, u.y));
           least = umin3(least, dist(x, u.z), dist(x, u.w));
-          if (kSelf)
+          if (overlaps)
             mixed |= (__builtin_popcount(x & t.x) + odd) | (__builtin_popcount(x & t.y) + odd) |
                      (__builtin_popcount(x & t.z) + odd) | (__builtin_popcount(x & t.w) + odd) |
                      (__builtin_popcount(x & u.x) + odd) | (__builtin_popcount(x & u.y) + odd) |
@@ -443,10 +449,14 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws_v, Ctl *ctl_v, unsign
           for (unsigned long long f = ~C.dead[i]; f; f &= f - 1, ++at)
             if (at - c0 < (unsigned int)kCovWin) C.cand[at - c0] = 64u * (high + i) + __builtin_ctzll(f);
         __syncthreads();
-        if (c0 + tid < undecided) {
-          const uint32_t x = C.cand[tid];
+        // Few candidates: several threads share one's comparisons.
+        const unsigned int some = __builtin_amdgcn_readfirstlane(umin(undecided - c0, kCovWin));
+        const unsigned int log = some > 64 ? 32 - (unsigned int)__builtin_clz(some - 1) : 6u, parts = kCovWin >> log;
+        const unsigned int at_ = (unsigned int)tid & ((1u << log) - 1u);
+        if (at_ < some) {
+          const uint32_t x = C.cand[at_];
           unsigned int least = ~0u;
-          for (unsigned int i = 0; i < all; i += 4) {
+          for (unsigned int i = 4 * ((unsigned int)wave >> (log - 6)); i < all; i += 4 * parts) {
             const uint4 t = *reinterpret_cast<const uint4 *>(&C.took[i]);
             least = umin3(least, dist(x, t.x), dist(x, t.y));
             least = umin3(least, dist(x, t.z), dist(x, t.w));
