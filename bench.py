@@ -3,7 +3,8 @@
 
 A step is one pass of the whole construction over the workload: every
 instance (n, d, ordering) is built from scratch on the GPU (all 2^n candidate
-positions screened, resolved and committed).  The default workload is the
+positions decided: linear codes from their generators, graded codes up to n =
+24 by marking the space, others by distance screens).  The default workload is the
 screens at n = 24..28: the four orderings x d in {3, 4, 5, 6, 8} at n=24 (the
 n=24 part of the sweep) plus lex and Gray at n in {26, 28} with d=3 (24
 instances).  ``--workload sweep`` runs the whole sweep (four orderings x n in
@@ -16,10 +17,11 @@ exit, counted by the CPU oracle and stored in tests/golden/expected_codes.txt)
 divided by the wall time of the step.
 
 Also measured (one JSON line in all):
-  * roofline of greedy_code_kernel, the single-code kernel, over every timed
-    launch of the workload: algorithmic checks (W_ee) per launch over the
-    launch's duration (HIP events on the launch stream, recorded by the
-    library);
+  * roofline of the single-code kernels over every timed launch of the
+    workload (HIP events on the launch stream, recorded by the library): the
+    distance checks that the screens executed against the int8 matrix peak,
+    or, where no code of the workload takes a screen, the bytes of the code
+    words against the HBM peak;
   * batched: the 256-instance workload (seed 1507) as one persistent launch,
     as a captured graph and as a loop of plain per-instance calls on the same
     buffers, with the built-in defaults and then autotuned;
@@ -59,6 +61,7 @@ PEAK_GCHECKS = VALU_LANE_OPS / OPS_PER_CHECK / 1e9
 INT8_PEAK_TOPS = 5000.0
 MFMA_CHECKS_PEAK_G = INT8_PEAK_TOPS * 1e12 / 64 / 1e9
 FOLD_CHECKS_PEAK_G = VALU_LANE_OPS / 0.5 / 1e9
+HBM_PEAK_GBS = 8000.0
 
 
 def progress(msg):
@@ -202,19 +205,22 @@ def oracle_times(expected, workers):
 
 
 class LaunchLog:
-    """Kernel time and algorithmic checks of every timed greedy_code_kernel
-    launch, and each instance's launch times."""
+    """Kernel time, algorithmic and executed checks and words of every timed
+    single-code launch, and each instance's launch times."""
 
     def __init__(self):
         self.ms, self.w_ee, self.executed, self.launches = 0.0, 0, 0, 0
-        self.ops = 0  # int8 operations: 2n per algorithmic check
+        self.ops = 0    # int8 operations: 2n per executed check
+        self.bytes = 0  # of the codes' words
         self.per_key = {}
 
     def add(self, key, stats, w_ee):
         self.ms += stats["kernel_ms"]
         self.w_ee += w_ee
-        self.ops += 2 * int(key.split("_")[0]) * w_ee
-        self.executed += stats["checks_near"] + stats["checks_deep"] + stats["checks_pairs"]
+        executed = stats["checks_near"] + stats["checks_deep"] + stats["checks_pairs"]
+        self.ops += 2 * int(key.split("_")[0]) * executed
+        self.bytes += 4 * stats["count"]
+        self.executed += executed
         self.launches += 1
         self.per_key.setdefault(key, []).append(stats["kernel_ms"])
 
@@ -222,7 +228,10 @@ class LaunchLog:
         return {k: round(sorted(v)[len(v) // 2], 3) for k, v in self.per_key.items()}
 
     def gchecks(self):
-        return self.w_ee / (self.ms / 1e3) / 1e9 if self.ms else 0.0
+        return self.executed / (self.ms / 1e3) / 1e9 if self.ms else 0.0
+
+    def gbytes(self):
+        return self.bytes / (self.ms / 1e3) / 1e9 if self.ms else 0.0
 
     def tops(self):
         return self.ops / (self.ms / 1e3) / 1e12 if self.ms else 0.0
@@ -449,8 +458,8 @@ def bench_served(gc, njobs, arena_bytes, teams, load_frac):
     span, lat, waits = serve(arrivals)
     q = lambda v, f: v[min(njobs - 1, int(f * njobs))]
     return {"jobs": njobs, "seed": 1507, "arena_bytes": arena_bytes, "teams": teams,
-            "wide_jobs": ("2^n * capacity(n, d) >= 2^38: wide queue, one team of 8 - teams XCDs; "
-                          "other jobs: teams teams of one XCD (and the wide team when idle)"
+            "wide_jobs": ("built by the screens with 2^n * capacity(n, d) >= 2^38: wide queue, one team of "
+                          "8 - teams XCDs; others: teams of one XCD, all eight while no wide job is open"
                           if teams in (2, 4) else "one queue, equal teams"),
             "serial_makespan_s": round(serial_s, 3), "serial_jobs_per_s": round(njobs / serial_s, 2),
             "burst_makespan_s": round(burst_span, 3), "capacity_jobs_per_s": round(capacity, 2),
@@ -559,7 +568,8 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "i8",  # the distance checks are int8 products (int32 sums) on the matrix cores
+        # Screens: int8 products (int32 sums) on the matrix cores; else words and bitmaps.
+        "dtype": "i8" if sweep.executed else "u32",
         "data": "synthetic: the full space F_2^n in each ordering (no dataset)",
         "config": {"workload": name, "instances": len(insts), "w_ee_per_step": w_ee,
                    "w_full_per_step": w_full},
@@ -577,25 +587,43 @@ def main():
     if not args.no_batched:
         batched = bench_batched(gc, torch, max(args.steps, 3), args.warmup)
         progress("batched done")
-    line["roofline"] = {
-        "bound": "mfma",
-        "kernel": "greedy_code_kernel",
-        "achieved": round(sweep.tops(), 3),
-        "peak": INT8_PEAK_TOPS,
-        "unit": "TOP/s (int8: 2n operations per check of n-bit words)",
-        "frac": round(sweep.tops() / INT8_PEAK_TOPS, 5),
-        "achieved_gchecks_per_s": round(sweep.gchecks(), 3),
-        "checks_ceiling_mfma_gchecks_per_s": round(MFMA_CHECKS_PEAK_G, 1),
-        "checks_ceiling_fold_gchecks_per_s": round(FOLD_CHECKS_PEAK_G, 1),
-        "frac_of_checks_ceiling": round(sweep.gchecks() / min(MFMA_CHECKS_PEAK_G, FOLD_CHECKS_PEAK_G), 5),
-        "valu_screen_peak_gchecks_per_s": round(PEAK_GCHECKS, 1),
-        "frac_of_valu_screen_peak": round(sweep.gchecks() / PEAK_GCHECKS, 5),
-        "traffic": measured_traffic(),
-        "traffic_unit": "bytes per launch (FETCH_SIZE x 2.0 + WRITE_SIZE, copy-calibrated)",
+    timed = {
         "launches": sweep.launches,
         "avg_launch_ms": round(sweep.ms / max(sweep.launches, 1), 4),
         "covers": "every timed launch of the workload (HIP events around each launch on its stream)",
     }
+    if sweep.executed:
+        line["roofline"] = {
+            "bound": "mfma",
+            "kernel": "greedy_code_kernel",
+            "achieved": round(sweep.tops(), 3),
+            "peak": INT8_PEAK_TOPS,
+            "unit": "TOP/s (int8: 2n operations per executed check of n-bit words)",
+            "frac": round(sweep.tops() / INT8_PEAK_TOPS, 5),
+            "achieved_gchecks_per_s": round(sweep.gchecks(), 3),
+            "checks_ceiling_mfma_gchecks_per_s": round(MFMA_CHECKS_PEAK_G, 1),
+            "checks_ceiling_fold_gchecks_per_s": round(FOLD_CHECKS_PEAK_G, 1),
+            "frac_of_checks_ceiling": round(sweep.gchecks() / min(MFMA_CHECKS_PEAK_G, FOLD_CHECKS_PEAK_G), 5),
+            "valu_screen_peak_gchecks_per_s": round(PEAK_GCHECKS, 1),
+            "frac_of_valu_screen_peak": round(sweep.gchecks() / PEAK_GCHECKS, 5),
+            "traffic": measured_traffic(),
+            "traffic_unit": "bytes per launch (FETCH_SIZE x 2.0 + WRITE_SIZE, copy-calibrated)",
+            **timed,
+        }
+    else:
+        # No distance check runs: what is left of the path's obligations is
+        # the code words, written once.  (The launches are bound by their
+        # chains of dependent steps and by LDS, not by this.)
+        line["roofline"] = {
+            "bound": "hbm",
+            "kernel": "lin_find_kernel, lin_emit_kernel, cover_kernel",
+            "achieved": round(sweep.gbytes(), 3),
+            "peak": HBM_PEAK_GBS,
+            "unit": "GB/s (the code words, written once)",
+            "frac": round(sweep.gbytes() / HBM_PEAK_GBS, 5),
+            "traffic": None,
+            **timed,
+        }
     line["executed_checks_per_step"] = sweep.executed // max(args.steps, 1)
     line["executed_over_w_ee"] = round(sweep.executed / max(sweep.w_ee, 1), 4)
     line["per_instance_kernel_ms"] = sweep.median_ms()
