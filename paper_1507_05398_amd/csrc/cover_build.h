@@ -1,7 +1,7 @@
 // cover_build.h -- graded codes (grlex, grevlex; constant weight, ranges and
 // prefixes too) of distance 2, 3 or 4 for n <= 24, from a bitmap of the whole
 // space instead of distance checks.  Included by greedy_code.hip.  Larger
-// distances: cover_windows.h.
+// distances, and small codes of these: cover_windows.h.
 //
 // An accepted word marks the ball of radius d - 1 around it (301 words at n =
 // 24, d = 3), so a candidate costs one bit and not a scan of the code.  The
@@ -18,7 +18,7 @@
 // candidates of a word.  The level's undecided candidates and the words
 // accepted in a round go through global memory.  All workgroups are on one
 // XCD, so that L2 joins them: a barrier is one atomic and a poll there (0.9
-// us for 32 workgroups against 5.3 us over eight XCDs), stores need no
+// us for 32 workgroups against 4.7 us over eight XCDs), stores need no
 // write-back, and what others wrote is read past the vector L1 (relaxed
 // agent-scope loads).  One barrier a round: a neighbour's candidates may be
 // read before or after it has marked the last round's words.  They only
@@ -28,7 +28,7 @@
 // reads (about 11 us at n = 20, d = 3: marks 3, reads 2.5, waiting for the
 // slowest slice 4), and for the largest codes the LDS throughput of the marks
 // (n = 24, d = 4: 988 words for each of 262144 code words).  Kernel time of
-// this path and of the windowed screens: n = 20, d = 3 1.2 and 9 ms; n = 22,
+// this path and of the windowed screens: n = 20, d = 3 1.1 and 9 ms; n = 22,
 // d = 4 2.2 and 17 ms; n = 24, d = 3 4.4 and 106 ms; n = 24, d = 4 5.9 and 64
 // ms.
 

@@ -11,6 +11,12 @@
 // of one job on one team that spans the GPU; a batch pre-fills the queue; the
 // server feeds the queue from host memory while the kernel runs.
 //
+// Most codes need no distance checks: the positional orderings' are linear and
+// are built from their generators (linear.h), graded ones up to n = 24 from a
+// bitmap of the space (cover_build.h, cover_windows.h).  Single codes of both
+// have launches of their own (linear.hip, cover_kernel).  The others take the
+// screens:
+//
 // Building one code: the ordering is cut into windows of consecutive
 // positions.  For a window starting with m0 committed words:
 //
@@ -39,9 +45,9 @@
 // the code first, the rest only if that passes) becomes the near screen /
 // deep scan split, reordered newest-first.
 //
-// Distance checks run on the vector ALUs: v_xor_b32, v_bcnt_u32_b32 and
-// v_min3_u32 (2.5 instructions per check).  No matrix cores: this is bit-packed
-// popcount work, not a dense contraction.
+// Distance checks run as int8 products on the matrix cores (bits as signed
+// bytes), or on the vector ALUs (self-orthogonal walks, tuning): v_xor_b32,
+// v_bcnt_u32_b32 and v_min3_u32, 2.5 instructions per check.
 #include <hip/hip_runtime.h>
 
 #include <stdarg.h>

@@ -40,7 +40,7 @@ constexpr unsigned int kServerIdlePolls = 50000;  // about 0.1 s of empty queue 
 // narrow ring, served by the teams of one XCD and, when no wide job waits, by
 // the wide team too.  Linear and cover jobs use one XCD at most: while no wide
 // job is open, every XCD is a team of its own (a burst of 200 jobs, n = 10 ..
-// 20: 15.4 ms with a wide team and two narrow ones).
+// 20: 3.0 ms; with a wide team and two narrow ones 15.4 ms).
 constexpr double kWideWork = 274877906944.0;  // 2^38
 // Narrow jobs may be admitted past a wide job that waits for arena space,
 // until that wide job has waited this long; then admission stops behind it
