@@ -260,6 +260,41 @@ __device__ __forceinline__ void lin_levels(S &L, Bits A, unsigned int max_words,
   }
 }
 
+// The same by one wave for a plain search of up to 64 labels, from the start:
+// lane s holds A[s], a level is some forty instructions without LDS reads
+// (n = 20, d = 4 14 us of kernel, 33 with the bitmaps in LDS).  Leaves the
+// search to lin_levels where a seventh label bit is due.
+template <typename S>
+__device__ __forceinline__ void lin_levels_short(S &L, int ord, int K, int D) {
+  const unsigned int lane = threadIdx.x;
+  unsigned long long a = (int)lane <= D ? 1ull : 0ull;  // the zero word
+  int k = 0, r = 0, dim = 0;
+  uint32_t u = 0;
+  for (; k < K; ++k) {
+    const uint32_t t = ord == GC_GRAY ? u : 0u;
+    const unsigned long long last = ((unsigned long long)(unsigned int)__builtin_amdgcn_readlane((int)(a >> 32), D) << 32) |
+                                    (unsigned int)__builtin_amdgcn_readlane((int)a, D);
+    unsigned long long x = ~xor_permute(last, t);
+    if (r < 6) x &= (1ull << (1 << r)) - 1;
+    if (x == 0 && r == 6) break;
+    const uint32_t m = x ? (uint32_t)__builtin_ctzll(x) : ~0u;
+    u = t ^ (x ? m : 1u << r);
+    lin_record(L, m, k, r, dim);
+    const unsigned long long below = __shfl_up(a, 1);
+    if (lane > 0 && (int)lane <= D) a |= xor_permute(below, u);
+    if (x) ++dim;
+    else ++r;
+  }
+  if ((int)lane <= D) L.bits[lane] = a;
+  if (lane == 0) {
+    L.k = k;
+    L.r = r;
+    L.dim = dim;
+    L.u = u;
+  }
+  lin_sync<64>();
+}
+
 // Lex and Gray: the whole search by one workgroup, the bitmaps in LDS while
 // they fit and then in `gbits` (global memory, gwords words).  Returns
 // whether it finished.
@@ -282,7 +317,10 @@ __device__ __forceinline__ bool lin_search(LinLds<kWords> &L, int n, int d, int 
   __syncthreads();
   if (d <= n) {
     // One wave up to 256 label words (four a lane), then the workgroup.
-    if (tid < 64) lin_levels<64>(L, L.bits, kWords / st < 256 ? kWords / st : 256, ord, so, K, D);
+    if (tid < 64) {
+      if (!so && D >= 0) lin_levels_short(L, ord, K, D);
+      lin_levels<64>(L, L.bits, kWords / st < 256 ? kWords / st : 256, ord, so, K, D);
+    }
     __syncthreads();
     if (L.k < K && kWords / st > 256) lin_levels<kBlock>(L, L.bits, kWords / st, ord, so, K, D);
     __syncthreads();
@@ -304,15 +342,16 @@ __device__ __forceinline__ bool lin_search(LinLds<kWords> &L, int n, int d, int 
 // of pos[i] over the bits i of m, increasing with m.
 template <typename S>
 __device__ __forceinline__ unsigned long long lin_count_below(const S &L, unsigned long long stop) {
-  unsigned long long lo = 0, hi = 1ull << L.dim;  // the count is in [lo, hi]
-  while (lo < hi) {
-    const unsigned long long m = (lo + hi) / 2;
-    unsigned long long p = 0;
-    for (unsigned long long b = m; b; b &= b - 1) p ^= L.pos[__builtin_ctzll(b)];
-    if (p < stop) lo = m + 1;
-    else hi = m;
+  if (stop == 0) return 0;
+  unsigned long long m = 0, p = 0;  // the last word below `stop`, from its top bit down
+  for (int i = L.dim - 1; i >= 0; --i) {
+    const unsigned long long q = p ^ L.pos[i];
+    if (q < stop) {
+      m |= 1ull << i;
+      p = q;
+    }
   }
-  return lo;
+  return m + 1;
 }
 
 // Byte tables of the code: word m is the XOR of tab[j][byte j of m].

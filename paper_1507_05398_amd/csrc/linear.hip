@@ -7,11 +7,11 @@
 //
 // What bounds it: launch latency and the chain of n search levels (one wave
 // while the label bitmaps are short).  One call, without and with this path:
-// n = 15 d = 3 to host memory 600 and 69 us, n = 20 d = 4 3235 and 46 us,
-// n = 26 d = 3 (2^21 words) 526 ms and 56 us, n = 30 d = 10 128 ms and 305 us
+// n = 15 d = 3 to host memory 600 and 56 us, n = 20 d = 4 3235 and 27 us,
+// n = 26 d = 3 (2^21 words) 526 ms and 31 us, n = 30 d = 10 128 ms and 293 us
 // (2^19 labels: the bitmaps leave LDS), a random basis at n = 23 d = 5 2698
-// and 81 us.  Search and words as two launches with the result copied back
-// cost 78, 55, 66, 384 and 97 us: a launch and a copy are 5 us each.
+// and 77 us.  Search and words as two launches with the result copied back
+// cost 15 us more.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
