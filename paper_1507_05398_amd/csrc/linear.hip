@@ -1,7 +1,7 @@
 // linear.hip -- single linear codes (lex, Gray, B-ordering, self-orthogonal
 // lex and Gray): one ordinary launch in which every workgroup finds the
 // generators for itself and writes its part of the words (a launch more lists
-// the low-weight words of a larger B-ordering; a prefix to check or bitmaps in
+// the low-weight words of a B-ordering with more than 16384; a prefix to check or bitmaps in
 // global memory leave the search to one workgroup and a launch of its own).
 // The mathematics is in linear.h.
 //
@@ -10,7 +10,7 @@
 // n = 15 d = 3 to host memory 600 and 56 us, n = 20 d = 4 3235 and 27 us,
 // n = 26 d = 3 (2^21 words) 526 ms and 31 us, n = 30 d = 10 128 ms and 293 us
 // (2^19 labels: the bitmaps leave LDS), a random basis at n = 23 d = 5 2698
-// and 77 us.  Search and words as two launches with the result copied back
+// and 64 us.  Search and words as two launches with the result copied back
 // cost 15 us more.
 #include <hip/hip_runtime.h>
 
@@ -39,6 +39,10 @@ constexpr size_t kLinGlobalBytes = 16u << 20;
 // B-ordering: low-weight words listed per workgroup, and in all.
 constexpr unsigned int kSegWords = 4096;
 constexpr unsigned long long kMaxListed = 1ull << 21;
+// As many as a workgroup holds in registers: a search of no more keeps its
+// words there (n = 23, d = 5, 10902 words: 64 us a call, 77 with a list).
+constexpr int kHeld = 16;
+constexpr unsigned int kMaxHeld = kHeld * kBlock;
 constexpr int kScanBlock = 256;
 constexpr int kEmitBlock = 256;
 
@@ -73,25 +77,21 @@ struct ScanLds {
   uint32_t hist[33];
 };
 
-// Segment `seg` of the list of all words z with 0 < wt(z) < d: their
-// positions, sorted by top position bit (kept as a run, the bit itself
-// cleared).  Whole workgroup of kThreads; a thread takes consecutive words in
-// the order weight, value (the next word of a weight by the usual bit trick).
+// Byte tables of the position of a word.
 template <int kThreads>
-__device__ __forceinline__ void list_segment(const LinArgs &P, ScanLds &S, unsigned int seg) {
-  const int tid = threadIdx.x;
-  constexpr int kPer = kSegWords / kThreads;
-  for (int i = tid; i < 4 * 256; i += kThreads) {
+__device__ __forceinline__ void position_tables(const LinArgs &P, ScanLds &S) {
+  for (int i = threadIdx.x; i < 4 * 256; i += kThreads) {
     uint32_t x = 0;
     for (int j = 0; j < 8; ++j)
       if ((i >> j) & 1) x ^= P.inv[8 * (i >> 8) + j];
     S.inv[i >> 8][i & 255] = x;
   }
-  if (tid < 33) S.hist[tid] = 0;
-  __syncthreads();
-  unsigned int rank = seg * kSegWords + (unsigned int)tid * kPer;
-  uint32_t p[kPer], slot[kPer];
-  unsigned int have = rank < P.listed ? (P.listed - rank < kPer ? P.listed - rank : kPer) : 0;
+}
+
+// Positions of the words `rank` .. rank + have - 1 of those with 0 < wt < d, in
+// the order weight, value (the next word of a weight by the usual bit trick).
+template <int kPer, typename F>
+__device__ __forceinline__ void low_words(const LinArgs &P, const ScanLds &S, unsigned int rank, unsigned int have, F &&f) {
   int s = 1;
   unsigned long long z = 0;
   if (have) {
@@ -109,13 +109,30 @@ __device__ __forceinline__ void list_segment(const LinArgs &P, ScanLds &S, unsig
 #pragma unroll
   for (int i = 0; i < kPer; ++i) {
     if (i < (int)have) {
-      p[i] = S.inv[0][z & 255] ^ S.inv[1][(z >> 8) & 255] ^ S.inv[2][(z >> 16) & 255] ^ S.inv[3][(z >> 24) & 255];
-      slot[i] = atomicAdd(&S.hist[31 - __builtin_clz(p[i])], 1u);
+      f(i, S.inv[0][z & 255] ^ S.inv[1][(z >> 8) & 255] ^ S.inv[2][(z >> 16) & 255] ^ S.inv[3][(z >> 24) & 255]);
       const unsigned long long low = z & (~z + 1), up = z + low;
       z = up | (((z ^ up) >> 2) >> __builtin_ctzll(low));
       if (z >> P.n) z = (1ull << ++s) - 1;  // the next weight's first word
     }
   }
+}
+
+// Segment `seg` of the list of all words z with 0 < wt(z) < d: their
+// positions, sorted by top position bit (kept as a run, the bit itself
+// cleared).  A thread takes consecutive words.
+__device__ __forceinline__ void list_segment(const LinArgs &P, ScanLds &S, unsigned int seg) {
+  const int tid = threadIdx.x;
+  constexpr int kPer = kSegWords / kScanBlock;
+  position_tables<kScanBlock>(P, S);
+  if (tid < 33) S.hist[tid] = 0;
+  __syncthreads();
+  const unsigned int rank = seg * kSegWords + (unsigned int)tid * kPer;
+  uint32_t p[kPer], slot[kPer];
+  const unsigned int have = rank < P.listed ? (P.listed - rank < kPer ? P.listed - rank : kPer) : 0;
+  low_words<kPer>(P, S, rank, have, [&](int i, uint32_t x) {
+    p[i] = x;
+    slot[i] = atomicAdd(&S.hist[31 - __builtin_clz(x)], 1u);
+  });
   __syncthreads();
   if (tid == 0) {
     uint32_t acc = 0;
@@ -134,21 +151,31 @@ __device__ __forceinline__ void list_segment(const LinArgs &P, ScanLds &S, unsig
       P.list[seg * kSegWords + S.hist[b] + slot[i]] = p[i] ^ (1u << b);
     }
   }
-  __syncthreads();
 }
 
 __global__ void __launch_bounds__(kScanBlock) lin_list_kernel(LinArgs P) {
   __shared__ ScanLds S;
-  list_segment<kScanBlock>(P, S, blockIdx.x);
+  list_segment(P, S, blockIdx.x);
 }
 
-// B-ordering: V_k is no coordinate subspace, so the low-weight words of
-// F_2^n are listed once by top position bit and each marks its label at that
-// bit's level (byte tables give the label of a position).
+// B-ordering: V_k is no coordinate subspace, so each low-weight word of F_2^n
+// marks its label at the level of its top position bit (byte tables give the
+// label of a position).  The words' positions are in registers, or listed by
+// that bit in global memory.
 __device__ __forceinline__ bool border_search(LinLds<kLinWords> &L, ScanLds &S, uint32_t (*lam)[256], const LinArgs &P) {
   const int tid = threadIdx.x, n = P.n;
-  // (One segment: every workgroup lists it, all the same.)
-  if (P.segs == 1) list_segment<kBlock>(P, S, 0);
+  uint32_t held[kHeld];
+  const bool in_registers = P.listed <= kMaxHeld;
+  const unsigned int per = (P.listed + kBlock - 1) / kBlock;
+  if (in_registers) {
+    position_tables<kBlock>(P, S);
+    __syncthreads();
+    const unsigned int rank = (unsigned int)tid * per;
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) held[i] = 0;
+    low_words<kHeld>(P, S, rank, rank < P.listed ? (P.listed - rank < per ? P.listed - rank : per) : 0u,
+                     [&](int i, uint32_t x) { held[i] = x; });
+  }
   if (tid < 32) L.img[tid] = P.basis[tid];
   for (int i = tid; i < 4 * 256; i += kBlock) lam[i >> 8][i & 255] = 0;
   if (tid < 2) L.best[tid] = ~0u;
@@ -159,12 +186,18 @@ __device__ __forceinline__ bool border_search(LinLds<kLinWords> &L, ScanLds &S, 
     if (nw > (unsigned int)kLinWords) break;
     for (unsigned int w = tid; w < nw; w += kBlock) L.bits[w] = 0;
     __syncthreads();
-    for (unsigned int seg = tid >> 6; seg < P.segs; seg += kBlock / 64) {
-      const uint32_t e = P.offs[seg * 33 + k + 1];
-      for (uint32_t i = P.offs[seg * 33 + k] + (tid & 63); i < e; i += 64) {
-        const uint32_t p = P.list[seg * kSegWords + i];
-        const uint32_t l = lam[0][p & 255] ^ lam[1][(p >> 8) & 255] ^ lam[2][(p >> 16) & 255] ^ lam[3][p >> 24];
-        atomicOr(&bits32[l >> 5], 1u << (l & 31));
+    auto mark = [&](uint32_t p) {
+      const uint32_t l = lam[0][p & 255] ^ lam[1][(p >> 8) & 255] ^ lam[2][(p >> 16) & 255] ^ lam[3][p >> 24];
+      atomicOr(&bits32[l >> 5], 1u << (l & 31));
+    };
+    if (in_registers) {
+#pragma unroll
+      for (int i = 0; i < kHeld; ++i)
+        if (i < (int)per && held[i] >> k == 1) mark(held[i] ^ (1u << k));
+    } else {
+      for (unsigned int seg = tid >> 6; seg < P.segs; seg += kBlock / 64) {
+        const uint32_t e = P.offs[seg * 33 + k + 1];
+        for (uint32_t i = P.offs[seg * 33 + k] + (tid & 63); i < e; i += 64) mark(P.list[seg * kSegWords + i]);
       }
     }
     __syncthreads();
@@ -347,7 +380,7 @@ int run_linear(Job *J, hipStream_t stream, char *fixed, size_t fixed_bytes, floa
                                        : (unsigned int)std::min<unsigned long long>(1024, most / (4 * kEmitBlock) + 1);
   if (seen) seen->ok = 0;
   hipError_t e = kernel_ms ? hipEventRecord(host.begin, stream) : hipSuccess;
-  if (e == hipSuccess && P.segs > 1) {
+  if (e == hipSuccess && P.listed > kMaxHeld) {
     hipLaunchKernelGGL(lin_list_kernel, dim3(P.segs), dim3(kScanBlock), 0, stream, P);
     e = hipGetLastError();
   }
