@@ -17,12 +17,18 @@ constexpr int kBlock = 1024;   // threads per workgroup
 constexpr int kMaxXcd = 16;    // XCD ids are taken modulo this
 constexpr int kMaxTeams = 8;
 
+// Distance of a job.  No two 32-bit words are further apart than 32, so any
+// larger distance means the same code; kernels count with 64 * d and index
+// arrays by d.
+constexpr int kMaxDistance = 33;
+constexpr int job_distance(int d) { return d < kMaxDistance ? d : kMaxDistance; }
+
 // One code to build.  In batch mode the array lives in device memory, in
 // server mode in pinned host memory (coherent, mapped): the device reads the
 // inputs once and writes the outputs, `done` last.
 struct Job {
   // inputs
-  int n, d, ord, mode;            // mode: 0 by ordering, 1 tentative, 2 deep-scan all survivors
+  int n, d, ord, mode;            // d: at most kMaxDistance; mode: 0 by ordering, 1 tentative, 2 deep-scan all survivors
   unsigned long long near_depth;  // 0: default
   unsigned int target;            // 0: default
   unsigned int deep_tile;         // candidates per deep-scan tile (0: default)

@@ -2315,7 +2315,7 @@ void fill_job(Job *J, int n, int d, int ordering, uint32_t *words, uint64_t capa
   if (!tuning && tuned_for(n, d, ordering, &remembered)) tuning = &remembered;
   memset(J, 0, sizeof(*J));
   J->n = n;
-  J->d = d;
+  J->d = job_distance(d);
   J->ord = ordering;
   J->code = words;
   J->capacity = capacity;
@@ -2472,7 +2472,7 @@ uint64_t problem_capacity(const gc_problem &p) {
   const uint64_t stop = p.stop ? p.stop : pos, screened = stop - p.start;
   uint64_t bound;
   if (p.d <= 1 && !p.self_orthogonal) bound = pos;
-  else if (p.weight >= 0) bound = johnson_bound(p.n, (p.d + 1) / 2, p.weight);
+  else if (p.weight >= 0) bound = johnson_bound(p.n, (job_distance(p.d) + 1) / 2, p.weight);
   else bound = greedy_code_capacity(p.n, p.d);
   if (p.self_orthogonal && bound > (1ull << (p.n / 2))) bound = 1ull << (p.n / 2);
   if (bound > p.prefix + screened) bound = p.prefix + screened;
@@ -2485,7 +2485,7 @@ void fill_job_problem(Job *J, const gc_problem &p, uint32_t *words, uint64_t cap
   if (!tuning && problem_plain(p) && tuned_for(p.n, p.d, p.ordering, &remembered)) tuning = &remembered;
   memset(J, 0, sizeof(*J));
   J->n = p.n;
-  J->d = p.d;
+  J->d = job_distance(p.d);
   // One weight class in increasing value is the graded lexicographic walk
   // restricted to that class.
   J->ord = p.weight >= 0 && p.ordering == GC_LEX ? GC_GRLEX : p.ordering;

@@ -308,7 +308,8 @@ __device__ __forceinline__ bool lin_search(LinLds<kWords> &L, int n, int d, int 
     L.img[tid] = ord == GC_GRAY ? w ^ (w >> 1) : w | parity;
     L.gen[tid] = L.np[tid] = L.q[tid] = 0;
   }
-  for (int s = tid; s <= D; s += blockDim.x) L.bits[s] = 1;  // the zero word
+  if (d <= n)  // (else the code is the zero word alone)
+    for (int s = tid; s <= D; s += blockDim.x) L.bits[s] = 1;  // the zero word
   if (tid == 0) {
     L.k = L.r = L.dim = 0;
     L.u = 0;

@@ -147,7 +147,7 @@ int wide_xcds(int teams) { return teams == 2 || teams == 4 ? 8 - teams : 0; }
 void fill_server_job(Job *J, int n, int d, int ord) {
   memset(J, 0, sizeof(*J));
   J->n = n;
-  J->d = d;
+  J->d = job_distance(d);
   J->ord = ord;
   gc_tuning tu;
   if (tuned_for(n, d, ord, &tu)) {

@@ -1,0 +1,75 @@
+"""Distances above the length: no second word is that far away, so every code
+has one word, whatever the distance, up to the largest int."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_1507_05398_amd as gc
+
+TOP = 2**31 - 1
+# Just above the length, past 32, where arrays indexed by the distance end (2048
+# and 16384 words), where 64 times the distance leaves 32 bits, and the largest.
+DISTANCES = [10, 32, 33, 34, 2050, 2163, 3000, 16386, 16499, 20000, 2**25 + 1, 2**26 - 1, 2**30 + 1, TOP - 1, TOP]
+ORDERINGS = ["lex", "gray", "grlex", "grevlex"]
+N = 9
+
+
+@pytest.mark.parametrize("d", DISTANCES)
+def test_capacities(d):
+    assert gc.greedy_code_capacity(N, d) == 1
+    for w in (0, 3, N):
+        assert gc.problem_capacity(gc.problem(N, d, "grlex", weight=w)) == 1
+
+
+def device(call, *args):
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a ROCm device"
+    words = torch.full((16,), -1, dtype=torch.int32, device="cuda")
+    count = torch.zeros(1, dtype=torch.int64, device="cuda")
+    call(*args, words[:1], count)
+    got = words.cpu().numpy().view(np.uint32)
+    assert (got[1:] == 0xFFFFFFFF).all()
+    return got[:int(count.item())].tolist()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d", DISTANCES)
+def test_single_codes(d):
+    print(f"[distance] d={d}", flush=True)
+    sys.stdout.flush()
+    for o in ORDERINGS:
+        assert gc.greedy_code(N, d, o).tolist() == [0], o
+        assert device(gc.greedy_code_device, N, d, o) == [0], o
+        assert device(gc.greedy_code_device_noalloc, N, d, o) == [0], o
+        assert device(lambda *a: gc.greedy_code_device_ex(*a, target_survivors=1000), N, d, o) == [0], o
+        so = gc.problem(N, d, o, self_orthogonal=True)
+        assert device(gc.greedy_code_problem_device, so) == [0], o
+    basis = [1 << (j + 1) % N ^ (1 << j if j % 2 else 0) for j in range(N)]
+    assert device(gc.greedy_code_problem_device, gc.problem(N, d, "border", basis=basis)) == [0]
+    # A weight: the walk's first word.  After a given word: that word alone, also
+    # where it is further from every candidate than the length.
+    for o in ("grlex", "grevlex"):
+        first = int(oracle.weight_class(N, 4, oracle.ORDERINGS[o])[0])
+        assert device(gc.greedy_code_problem_device, gc.problem(N, d, o, weight=4)) == [first], o
+        p = gc.problem(N, max(d, 33), o, self_orthogonal=True, start=1, prefix=1)
+        got, _ = gc.device_problem_code(p, prefix_words=np.array([0xFFFFFFFF], np.uint32))
+        assert got.cpu().numpy().view(np.uint32).tolist() == [0xFFFFFFFF], o
+
+
+@pytest.mark.gpu
+def test_batched_and_served():
+    jobs = [(n, d, o) for d in DISTANCES for o in ORDERINGS for n in (1, N)]
+    print(f"[distance] {len(jobs)} jobs", flush=True)
+    sys.stdout.flush()
+    for teams in (0, 4):
+        words, info, _ = gc.greedy_code_batch(jobs, teams=teams)
+        for j, w, i in zip(jobs, words, info):
+            assert i["status"] == 0 and w.cpu().tolist() == [0], j
+    for teams in (2, 8):
+        with gc.Server(arena_bytes=1 << 20, teams=teams) as srv:
+            tickets = [srv.submit(*j) for j in jobs]
+            srv.drain(timeout_ms=20000)
+            for t, j in zip(tickets, jobs):
+                assert srv.fetch(t).tolist() == [0], j
