@@ -23,9 +23,15 @@ def test_capacities(d):
         assert gc.problem_capacity(gc.problem(N, d, "grlex", weight=w)) == 1
 
 
-def device(call, *args):
+@pytest.fixture(scope="module")
+def cuda():
     import torch
     assert torch.cuda.is_available(), "GPU tests need a ROCm device"
+    gc.load()
+
+
+def device(call, *args):
+    import torch
     words = torch.full((16,), -1, dtype=torch.int32, device="cuda")
     count = torch.zeros(1, dtype=torch.int64, device="cuda")
     call(*args, words[:1], count)
@@ -36,7 +42,7 @@ def device(call, *args):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("d", DISTANCES)
-def test_single_codes(d):
+def test_single_codes(cuda, d):
     print(f"[distance] d={d}", flush=True)
     sys.stdout.flush()
     for o in ORDERINGS:
@@ -59,7 +65,7 @@ def test_single_codes(d):
 
 
 @pytest.mark.gpu
-def test_batched_and_served():
+def test_batched_and_served(cuda):
     jobs = [(n, d, o) for d in DISTANCES for o in ORDERINGS for n in (1, N)]
     print(f"[distance] {len(jobs)} jobs", flush=True)
     sys.stdout.flush()
