@@ -1504,6 +1504,20 @@ __device__ __noinline__ void find_generators(int n, int d, int ord, unsigned lon
   }
 }
 
+// A code by the screens.  Not inlined: the registers are its own, whatever the
+// kernel around it keeps and calls.  (Inlined, 45 vector registers spilled, and
+// 65 beside the calls of the other builders.  n = 24, d = 3 lex 96.9 ms alone,
+// 100.4 beside the calls, 92.0 here; n = 25, d = 6 grlex 9.41, 9.52 and 8.90 ms.)
+template <bool SO>
+__device__ __noinline__ void build_by_screens(Bar *bar_v, DevQueue *dq_v, char *ws_v, unsigned int limit_v) {
+  // Arguments are the same for every lane: pointers in scalar registers.
+  Params P{};
+  P.bar = uniform_ptr(bar_v);
+  P.dq = uniform_ptr(dq_v);
+  P.spin_limit = (unsigned int)__builtin_amdgcn_readfirstlane((int)limit_v);
+  build_code<SO>(g_lds, P, team_ws(uniform_ptr(ws_v)));
+}
+
 // A linear code (whole lex or Gray walk) from its generators: team rank 0
 // finds them while the others wait, then the team writes the words.  False
 // (alike in every workgroup) when the search did not fit its workspace.
@@ -1668,7 +1682,7 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
   team_join(L, P);
   // The team's workspace pointers are uniform: computed in scalar registers.
   const unsigned int team = __builtin_amdgcn_readfirstlane(L.team);
-  char *base = P.team_ws + (unsigned long long)team * P.team_ws_stride;
+  char *const base = P.team_ws + (unsigned long long)team * P.team_ws_stride;
   const TeamWs W = team_ws(base);
   // The claim wait (server) may last up to idle_limit polls.
   const unsigned int claim_limit = P.idle_limit + P.spin_limit;
@@ -1724,7 +1738,7 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
     load_job(L);
     if (L.d <= 1 && !L.walk.so) emit_ordering(L, W);
     else if ((!kLinear || !L.linear || !build_linear(L, P, W)) && (!L.by_cover || !build_cover<SO>(L, W, &P.dq->abort, P.spin_limit))) {
-      build_code<SO>(L, P, W);
+      build_by_screens<SO>(P.bar, P.dq, base, P.spin_limit);
       screened = true;
     }
 
