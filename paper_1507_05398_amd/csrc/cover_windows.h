@@ -74,6 +74,7 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws_v, Ctl *ctl_v, unsign
   uint32_t *const code = uniform_ptr(L.code);
   const unsigned long long capacity = uniform64(L.capacity), start = uniform64(L.p_start), stop = uniform64(L.total);
   unsigned long long m = uniform64(L.m_start);
+  const bool given = m > 0;  // words before `start`: any, not always of a self-orthogonal code
   // Overlap of two even words by their numbers: the bits both have, plus n
   // for complemented ones.
   const unsigned int odd = rev ? (unsigned int)n & 1u : 0u, all_bits = (1u << n) - 1u;
@@ -362,9 +363,9 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws_v, Ctl *ctl_v, unsign
     const unsigned int blocks = (size + 63) / 64;
     const uint32_t x = C.cand[tid];
     unsigned long long row = 0;
-    // (A basis of n / 2 words: the candidates left are in their span, and no
-    // pair has an odd overlap.)
-    const bool overlaps = kSelf && 2 * C.dim < n;
+    // (A basis of n / 2 words that overlap evenly: the candidates left are in
+    // their span, and no pair has an odd overlap.  Given words need not.)
+    const bool overlaps = kSelf && (given || 2 * C.dim < n);
     if ((unsigned int)wave < blocks)
       row = overlaps ? clash_mask<kSelf>(&C.cand[64 * wave], x, d, odd) : clash_mask<false>(&C.cand[64 * wave], x, d, odd);
     unsigned int all = 0, least = (unsigned int)tid < size ? ~0u : 0u, mixed = 0;
