@@ -162,8 +162,8 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws_v, Ctl *ctl_v, unsign
       if (b) atomicMax(&C.pick, b);
       __syncthreads();
       const uint32_t pick = C.pick;
+      __syncthreads();  // every wave has read it: a wave that leaves may raise the next call's at once
       if (pick == 0) break;
-      __syncthreads();
       if (tid == 0) {
         C.basis[dim] = pick;
         C.dim = dim + 1;

@@ -76,3 +76,36 @@ def test_spanning_prefixes(n, d, kind, o):
     given = words_given(n, kind)
     got, ref = both(gc.problem(n, d, o, self_orthogonal=True, start=1, prefix=len(given)), given)
     assert np.array_equal(got, ref)
+
+
+# More given words than a workgroup takes at a time (1024), with new dimensions
+# among the later ones: those of a code, and any.
+@pytest.mark.parametrize("o", ["grlex", "grevlex"])
+@pytest.mark.parametrize("n,d", [(22, 2), (24, 4)])
+def test_long_prefixes_of_a_code(n, d, o):
+    full, _ = both(gc.problem(n, d, o, self_orthogonal=True), np.zeros(0, np.uint32))
+    total = gc.problem_positions(gc.problem(n, d, o, self_orthogonal=True))
+    for cut in (total // 2, total * 3 // 4):
+        head, _ = both(gc.problem(n, d, o, self_orthogonal=True, stop=cut), np.zeros(0, np.uint32))
+        print(f"[so] n={n} d={d} {o} cut {cut}: {len(head)} of {len(full)}", flush=True)
+        sys.stdout.flush()
+        assert np.array_equal(head, full[: len(head)])
+        got, ref = both(gc.problem(n, d, o, self_orthogonal=True, start=cut, prefix=len(head)), head)
+        assert np.array_equal(got, ref) and np.array_equal(got, full)
+
+
+@pytest.mark.parametrize("o", ["grlex", "grevlex"])
+@pytest.mark.parametrize("count", [1024, 1025, 2047, 3100])
+def test_long_prefixes_of_any_words(count, o):
+    n = 18
+    rng = np.random.default_rng(count)
+    # Each 1024 words add two dimensions to those before them.
+    basis = rng.permutation(n)
+    given = np.zeros(count, np.uint32)
+    for i in range(count):
+        for j in range(2 * (i // 1024) + 2):
+            given[i] ^= np.uint32(int(rng.integers(2)) * (3 << int(basis[j]) & (1 << n) - 1))
+    print(f"[so] {count} words {o}", flush=True)
+    sys.stdout.flush()
+    got, ref = both(gc.problem(n, 2, o, self_orthogonal=True, start=5, prefix=count), given)
+    assert np.array_equal(got, ref)
