@@ -1755,8 +1755,10 @@ __device__ __forceinline__ void persistent_body(Lds &L, const Params &P) {
     // them over the fabric (no copy engine or extra kernel is needed while this
     // kernel holds the GPU), then releases them at system scope before the
     // barrier that precedes `done`.
-    if (J.host_copy != nullptr && ld_relaxed(&W.ctl->status) == 0) {
-      const unsigned long long m = ld_relaxed(&W.ctl->m);
+    // (A job with a status copies none, but meets the barrier: the next job's
+    // start clears the status, so all must have read it.)
+    if (J.host_copy != nullptr) {
+      const unsigned long long m = ld_relaxed(&W.ctl->status) == 0 ? ld_relaxed(&W.ctl->m) : 0ull;
       const uint4 *src = reinterpret_cast<const uint4 *>(L.code);
       uint4 *dst = reinterpret_cast<uint4 *>(J.host_copy);
       const unsigned long long stride = (unsigned long long)L.team_size * kBlock;
