@@ -229,7 +229,7 @@ __device__ __noinline__ void cover_window_team(CoverWs *ws_v, Ctl *ctl_v, unsign
     if (tid < 32) {
       unsigned long long none = 0;
       for (int j = 0; j <= 6; ++j)
-        if (!((walked >> (tid + j)) & 1)) none |= C.level[32 + j];
+        if (tid + j > n || !((walked >> (tid + j)) & 1)) none |= C.level[32 + j];
       C.none[tid] = none;
     }
     __syncthreads();
