@@ -321,10 +321,11 @@ int greedy_code_batch_tune(gc_job *jobs, int njobs, void *hip_stream, int *best_
  * Wide jobs go to a wide queue; while one is open, one team spanning 8 - teams
  * of the eight XCDs serves it, and the other jobs, in a narrow queue, are
  * served by `teams` teams of one XCD each and by the wide team whenever no
- * wide job waits (to change teams the kernel finishes the jobs it is building
- * and is launched again).  Each queue runs in arrival order; narrow jobs never
- * wait behind a wide one, and may be admitted past a wide job that waits for
- * arena space until it has waited 1 s.  Finished
+ * wide job waits.  To change teams the kernel finishes the jobs it is building
+ * and a launch queued behind it takes up the rest (no further call is needed):
+ * jobs not yet begun then wait for those, all of them narrow.  Each queue runs
+ * in arrival order; narrow jobs never wait behind a wide one, and may be admitted
+ * past a wide job that waits for arena space until it has waited 1 s.  Finished
  * codes stay resident in the arena until released.  The kernel
  * exits after about 0.1 s without work and is relaunched on demand.  If a
  * bounded device-side wait expires, every unfinished job fails with

@@ -1894,7 +1894,9 @@ __global__ void __launch_bounds__(kBlock) cover_kernel(CoverArgs A) {
 }
 
 // Reset of the barrier block and the device queue before a launch (a kernel
-// rather than a memset, so that it can live in captured graphs).
+// rather than a memset, so that it can live in captured graphs).  A server's
+// queue goes on, an abort of an earlier launch included: a launch that was queued
+// behind it stops at once, and the host sees the abort.
 __global__ void init_kernel(Bar *bar, DevQueue *dq, int reset_queue) {
   const unsigned int i = blockIdx.x * blockDim.x + threadIdx.x;
   const unsigned int nbar = sizeof(Bar) / sizeof(unsigned int);
@@ -1904,8 +1906,8 @@ __global__ void init_kernel(Bar *bar, DevQueue *dq, int reset_queue) {
       dq->claimed = 0;
       dq->claimed_wide = 0;
       dq->completed = 0;
+      dq->abort = 0;
     }
-    dq->abort = 0;
     dq->launches += 1;
   }
 }

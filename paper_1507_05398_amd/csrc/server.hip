@@ -15,6 +15,7 @@
 
 #include <stdlib.h>
 
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <cmath>
@@ -65,7 +66,7 @@ struct gc_server {
   int launch_teams = 1;     // teams of a launch, at most
   bool split = false;       // the last launch has a wide team and `teams` narrow ones
   unsigned int layout_launched = 0;  // HostQueue::layout of the last launch
-  unsigned int wide_open = 0;  // wide jobs published and not yet seen finished
+  std::vector<int> wide_open;  // slots of the wide jobs published and not yet seen finished
   bool stopped = false;     // a bounded device-side wait expired: no further launches
   unsigned int grid = 0;
   hipStream_t stream = nullptr;
@@ -137,6 +138,15 @@ bool kernel_running(gc_server *s) {
   return hipEventQuery(s->kernel_done) == hipErrorNotReady;
 }
 
+bool job_done(gc_server *s, int slot) { return __atomic_load_n(&s->jobs[slot].done, __ATOMIC_ACQUIRE) != 0; }
+
+// Whether a published job is not finished.
+bool unfinished(gc_server *s) {
+  for (uint64_t id : s->inflight)
+    if (!job_done(s, s->tickets[id].slot)) return true;
+  return false;
+}
+
 // Wide XCDs of a server: with teams 2 and 4, while a wide job is open, the 8
 // XCDs are one wide team of 8 - teams XCDs and `teams` narrow teams of one XCD;
 // teams 1 and 8 have equal teams (one team spanning the GPU, or one per XCD)
@@ -174,7 +184,7 @@ int launch_server_kernel(gc_server *s) {
   P.dq = s->dq;
   P.bar = s->bar;
   P.njobs_fixed = -1;
-  s->split = s->wide_open > 0;
+  s->split = !s->wide_open.empty();
   P.nteams = s->split ? 1 + s->teams : wide_xcds(s->teams) ? 8 : s->teams;
   P.split = s->split ? wide_xcds(s->teams) : 0;
   P.layout = s->layout_launched = s->hq->layout;
@@ -201,7 +211,7 @@ void fail_unfinished(gc_server *s, int code) {
   for (uint64_t id : s->inflight) {
     Ticket &t = s->tickets[id];
     const Job &J = s->jobs[t.slot];
-    if (__atomic_load_n(&J.done, __ATOMIC_ACQUIRE)) {
+    if (job_done(s, t.slot)) {
       t.status = J.status;
       t.state = t.status == 0 ? GC_JOB_DONE : GC_JOB_FAILED;
     } else {
@@ -222,6 +232,8 @@ void fail_unfinished(gc_server *s, int code) {
 // and make sure a kernel is running while published work is unfinished.
 int pump(gc_server *s) {
   if (s->stopped) return GC_OK;
+  auto &open = s->wide_open;
+  open.erase(std::remove_if(open.begin(), open.end(), [&](int slot) { return job_done(s, slot); }), open.end());
   bool published_any = false;
   // Arrival order, except that a narrow job may pass a wide job that waits
   // for arena space (for at most kWideAdmitWaitS, so wide jobs do not
@@ -259,7 +271,7 @@ int pump(gc_server *s) {
     J->count = nullptr;
     J->host_copy = reinterpret_cast<uint32_t *>(s->mirror_dev + off);
     J->wide = wide ? 1 : 0;
-    if (wide) ++s->wide_open;
+    if (wide) s->wide_open.push_back(t.slot);
     if (J->wide) s->ring_wide[s->published_wide++] = (unsigned int)t.slot;
     else s->ring[s->published_narrow++] = (unsigned int)t.slot;
     s->slot_ticket[t.slot] = id;
@@ -273,20 +285,17 @@ int pump(gc_server *s) {
     __atomic_store_n(&s->hq->submitted, s->published_narrow, __ATOMIC_RELEASE);
   }
   // Other teams are wanted than those of the running launch: its teams finish
-  // the jobs they have, and the launch that follows takes up the rest.
-  if (wide_xcds(s->teams) && s->launched && s->split != (s->wide_open > 0) && s->hq->layout == s->layout_launched)
+  // the jobs they have, and a launch queued behind it takes up the rest, so that
+  // published work needs no further call.
+  if (wide_xcds(s->teams) && s->split == s->wide_open.empty() && kernel_running(s) && unfinished(s)) {
     __atomic_store_n(&s->hq->layout, s->layout_launched + 1, __ATOMIC_RELEASE);
+    return launch_server_kernel(s);
+  }
   // Relaunch if published jobs are unfinished and no kernel is running (the
-  // previous one may have gone idle just before the publication, stopped at
-  // a job of the other kind, or given up on a bounded wait).
+  // previous one may have gone idle just before the publication or given up on
+  // a bounded wait).
   if (!kernel_running(s)) {
-    bool unfinished = false;
-    for (uint64_t id : s->inflight)
-      if (!__atomic_load_n(&s->jobs[s->tickets[id].slot].done, __ATOMIC_ACQUIRE)) {
-        unfinished = true;
-        break;
-      }
-    if (!unfinished) return GC_OK;
+    if (!unfinished(s)) return GC_OK;
     // The last launch has finished: its queue state tells where to resume.
     DevQueue dq;
     memset(&dq, 0, sizeof(dq));
@@ -309,10 +318,10 @@ int pump(gc_server *s) {
 }
 
 void refresh(gc_server *s, uint64_t id, Ticket &t) {
-  if (t.state == GC_JOB_ADMITTED && __atomic_load_n(&s->jobs[t.slot].done, __ATOMIC_ACQUIRE)) {
+  if (t.state == GC_JOB_ADMITTED && job_done(s, t.slot)) {
     t.status = s->jobs[t.slot].status;
     t.state = t.status == 0 ? GC_JOB_DONE : GC_JOB_FAILED;
-    if (s->inflight.erase(id) && s->jobs[t.slot].wide) --s->wide_open;
+    s->inflight.erase(id);
   }
 }
 
@@ -422,6 +431,7 @@ int gc_server_words(gc_server *s, uint64_t ticket, const uint32_t **d_words, uin
   auto it = s->tickets.find(ticket);
   if (it == s->tickets.end()) return fail(GC_EINVAL, "unknown ticket %llu", (unsigned long long)ticket);
   refresh(s, it->first, it->second);
+  if (it->second.state == GC_JOB_WAITING || it->second.state == GC_JOB_ADMITTED) (void)pump(s);
   if (it->second.state == GC_JOB_FAILED)
     return fail(it->second.status, "job failed with status %d", it->second.status);
   if (it->second.state != GC_JOB_DONE) return fail(GC_EBUSY, "job not finished");
@@ -468,6 +478,7 @@ int gc_server_stats(gc_server *s, uint64_t ticket, gc_stats *stats, double *devi
   auto it = s->tickets.find(ticket);
   if (it == s->tickets.end()) return fail(GC_EINVAL, "unknown ticket %llu", (unsigned long long)ticket);
   refresh(s, it->first, it->second);
+  if (it->second.state == GC_JOB_WAITING || it->second.state == GC_JOB_ADMITTED) (void)pump(s);
   if (it->second.state != GC_JOB_DONE && it->second.state != GC_JOB_FAILED)
     return fail(GC_EBUSY, "job not finished");
   if (it->second.slot < 0) return fail(it->second.status, "job failed before it was admitted");
