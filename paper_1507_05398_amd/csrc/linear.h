@@ -295,6 +295,15 @@ __device__ __forceinline__ void lin_levels_short(S &L, int ord, int K, int D) {
   lin_sync<64>();
 }
 
+// Whether a lex or Gray code needs a search.  Three words at distance d or more
+// have 3 d differences in n coordinates, of which each takes part in two at most:
+// with 3 d > 2 n there are two words, zero and the walk's first of weight d or
+// more.  The first 2^k positions hold all words of the first k coordinates, so
+// that is the one of d (self-orthogonal: an even number of) ones on the first
+// coordinates.  (The search holds 2^(d - 1) labels for it: n = 24, d = 24 lex
+// 4046 us a call with the search, 22 without, 2164 by the screens.)
+__host__ __device__ constexpr bool lin_searched(int n, int d) { return 3 * d <= 2 * n; }
+
 // Lex and Gray: the whole search by one workgroup, the bitmaps in LDS while
 // they fit and then in `gbits` (global memory, gwords words).  Returns
 // whether it finished.
@@ -303,20 +312,29 @@ __device__ __forceinline__ bool lin_search(LinLds<kWords> &L, int n, int d, int 
                                            unsigned long long *gbits, unsigned int gwords) {
   const int tid = threadIdx.x, K = n - so, D = d - 2;
   const unsigned int st = (unsigned int)(D + 1) | 1u;
+  const bool search = lin_searched(n, d);
   if (tid < 32) {
     const unsigned int w = 1u << tid << so, parity = so ? 1u : 0u;
     L.img[tid] = ord == GC_GRAY ? w ^ (w >> 1) : w | parity;
-    L.gen[tid] = L.np[tid] = L.q[tid] = 0;
+    L.gen[tid] = L.q[tid] = 0;
+    L.np[tid] = search ? 0u : (uint32_t)tid;
   }
-  if (d <= n)  // (else the code is the zero word alone)
+  if (search)
     for (int s = tid; s <= D; s += blockDim.x) L.bits[s] = 1;  // the zero word
   if (tid == 0) {
     L.k = L.r = L.dim = 0;
     L.u = 0;
     L.best[0] = L.best[1] = ~0u;
+    const int weight = d + (so & d & 1), top = weight - 1 - so;
+    if (!search && weight <= n) {  // the second word: `weight` ones at the low coordinates
+      L.dim = 1;
+      L.top[0] = (uint32_t)top;
+      // Its position: ones up to the top bit (lex), or every second one (Gray).
+      L.lab[0] = (ord != GC_GRAY ? ~0u : top & 1 ? 0xaaaaaaaau : 0x55555555u) & ((1u << top) - 1u);
+    }
   }
   __syncthreads();
-  if (d <= n) {
+  if (search) {
     // One wave up to 256 label words (four a lane), then the workgroup.
     if (tid < 64) {
       if (!so && D >= 0) lin_levels_short(L, ord, K, D);
@@ -333,7 +351,7 @@ __device__ __forceinline__ bool lin_search(LinLds<kWords> &L, int n, int d, int 
     }
     __syncthreads();
   }
-  const bool ok = d > n || L.k >= K;
+  const bool ok = !search || L.k >= K;
   if (ok) lin_generators(L, L.dim);
   __syncthreads();
   return ok;

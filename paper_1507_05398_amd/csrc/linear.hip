@@ -342,14 +342,14 @@ int run_linear(Job *J, hipStream_t stream, char *fixed, size_t fixed_bytes, floa
     memcpy(P.basis, J->basis, sizeof(P.basis));
     invert_basis(J->basis, J->n, P.inv);
   } else {
-    // Global bitmaps for the labels that can occur: once 2^r exceeds the
-    // number of words of weight <= d - 2, some label is always free.
+    // Global bitmaps for the labels that can occur (none without a search): once
+    // 2^r exceeds the number of words of weight <= d - 2, some label is always free.
     unsigned long long low = 1;
     for (int s = 1; s <= std::min(J->d - 2, J->n - 1); ++s) low += make_binom().c[J->n - 1][s];
     unsigned long long words = 2;
     while (words * 32 < low) words *= 2;
     const unsigned long long need = words * ((unsigned int)(J->d > 1 ? J->d - 1 : 0) | 1u);
-    if (need > (unsigned long long)kLinWords)
+    if (lin_searched(P.n, P.d) && need > (unsigned long long)kLinWords)
       bytes += (size_t)std::min<unsigned long long>(need * 8, fixed ? fixed_bytes - bytes : kLinGlobalBytes);
   }
   char *ws = fixed;

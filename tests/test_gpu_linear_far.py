@@ -1,0 +1,68 @@
+"""Linear codes of large distance.  With 3 d > 2 n they have two words and are
+written without a search; below that line by the search.  Every length up to 13
+and every distance against the oracle, longer ones on both sides of the line
+against the screens."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_1507_05398_amd as gc
+
+pytestmark = pytest.mark.gpu
+SCREENS = dict(target_survivors=1000)
+
+
+@pytest.fixture(scope="module", autouse=True)
+def cuda():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a ROCm device"
+    gc.load()
+
+
+def host(t):
+    return t.cpu().numpy().view(np.uint32)
+
+
+@pytest.mark.parametrize("o", ["lex", "gray"])
+@pytest.mark.parametrize("n", range(1, 14))
+def test_every_distance(n, o):
+    print(f"[far] n={n} {o}", flush=True)
+    sys.stdout.flush()
+    walk = np.arange(1 << n, dtype=np.uint32)
+    walk = walk ^ (walk >> 1) if o == "gray" else walk
+    even = np.array([x for x in walk if int(x).bit_count() % 2 == 0], np.uint32)
+    if o == "lex":  # positions 2 p and 2 p + 1 hold one even word, in the order of p
+        assert np.array_equal(even >> 1, np.arange(1 << n - 1))
+    jobs, want = [], []
+    for d in range(1, n + 3):
+        full = oracle.greedy_ball(n, d, oracle.ORDERINGS[o])[0]
+        assert np.array_equal(host(gc.device_code(n, d, o)[0]), full), d
+        jobs.append((n, d, o))
+        want.append(full)
+        so = oracle.greedy_list(n, d, even, self_orth=True)[0]
+        assert np.array_equal(host(gc.device_problem_code(gc.problem(n, d, o, self_orthogonal=True))[0]), so), d
+        if len(full) == 2:  # a range with the second word, and one that ends before it
+            p = int(np.flatnonzero(walk == full[1])[0])
+            for stop in (p, p + 1):
+                got = host(gc.device_problem_code(gc.problem(n, d, o, stop=stop))[0])
+                assert got.tolist() == full[: 1 + (stop > p)].tolist(), (d, stop)
+            got = host(gc.device_problem_code(gc.problem(n, d, o, start=p, prefix=1), prefix_words=full[:1])[0])
+            assert np.array_equal(got, full), d
+    for w, ref, j in zip(gc.greedy_code_batch(jobs)[0], want, jobs):
+        assert np.array_equal(host(w), ref), j
+
+
+@pytest.mark.parametrize("so", [False, True])
+@pytest.mark.parametrize("o", ["lex", "gray"])
+@pytest.mark.parametrize("n,d", [(20, 13), (20, 14), (21, 14), (21, 15), (22, 22), (24, 16), (24, 17), (24, 23), (24, 24),
+                                 (25, 16), (25, 17)])
+def test_both_sides_of_two_words(n, d, o, so):
+    print(f"[far] n={n} d={d} {o} {so}", flush=True)
+    sys.stdout.flush()
+    p = gc.problem(n, d, o, self_orthogonal=so)
+    got, ref = gc.device_problem_code(p)[0], gc.device_problem_code(p, **SCREENS)[0]
+    assert np.array_equal(host(got), host(ref))
+    words = gc.greedy_code(n, d, o)
+    assert so or np.array_equal(words, host(ref))
