@@ -158,7 +158,8 @@ bool cover_job(const Job &J);
 // *built, kernel_ms (may be null) the device time.  `fixed`: a workspace of
 // fixed_bytes to use instead of the pool (may be null).  *built stays false
 // when the search does not fit the workspace or the prefix is not the code's
-// beginning: the screens then build the code.
+// beginning: the screens then build the code, from where *J then begins (a search
+// that ran out of memory has written the words of the walk's first part).
 int run_linear(Job *J, hipStream_t stream, char *fixed, size_t fixed_bytes, float *kernel_ms, bool *built);
 // Validates a caller's job array and fills `J` (caller order) and `order`
 // (queue position -> caller index, longest jobs first).

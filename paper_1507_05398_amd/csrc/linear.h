@@ -40,7 +40,7 @@ struct LinResult {
   int ok;                          // 0: not found within the given memory (the caller screens instead)
   int dim;                         // generators
   int status;                      // GC_OK or GC_ECAPACITY
-  int pad;
+  int part;                        // k: not found, but the code of the first 2^k positions
   unsigned long long begin, end;   // words to write: code indices [begin, end)
   uint32_t gen[32];
 };
@@ -351,10 +351,9 @@ __device__ __forceinline__ bool lin_search(LinLds<kWords> &L, int n, int d, int 
     }
     __syncthreads();
   }
-  const bool ok = !search || L.k >= K;
-  if (ok) lin_generators(L, L.dim);
+  lin_generators(L, L.dim);  // (of the first 2^k positions, if it did not finish)
   __syncthreads();
-  return ok;
+  return !search || L.k >= K;
 }
 
 // Words of the code at positions below `stop`: code index m has position XOR

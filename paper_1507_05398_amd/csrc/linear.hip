@@ -36,9 +36,18 @@ namespace {
 constexpr int kLinWords = 16384;
 // Global label bitmaps of a search: up to 16 MiB of the workspace pool.
 constexpr size_t kLinGlobalBytes = 16u << 20;
-// B-ordering: low-weight words listed per workgroup, and in all.
+// B-ordering: low-weight words listed per workgroup, and at most in all.  A word
+// costs a search some 0.5 ns, a position of the walk the screens 0.1 ns past 0.4
+// ms (random bases, by the search and by the screens: n = 20, d = 12, 784625 words
+// 505 and 413 us, d = 14, 988115 words 608 and 392; n = 21, d = 10, 695859 words
+// 513 and 733, d = 11, 2^20 - 1 words 678 and 609, d = 12, 1401291 words 833 and
+// 573; n = 22, d = 10, 1097789 words 724 and 922, d = 11, 1744435 words 977 and
+// 844).
 constexpr unsigned int kSegWords = 4096;
-constexpr unsigned long long kMaxListed = 1ull << 21;
+constexpr unsigned long long max_listed(int n) {
+  const unsigned long long some = (1ull << 19) + (1ull << n >> 2);
+  return some < 1ull << 21 ? some : 1ull << 21;
+}
 // As many as a workgroup holds in registers: a search of no more keeps its
 // words there (n = 23, d = 5, 10902 words: 64 us a call, 77 with a list).
 constexpr int kHeld = 16;
@@ -56,6 +65,7 @@ constexpr BinomTable make_binom() {
   return t;
 }
 __constant__ BinomTable kBinom = make_binom();
+constexpr BinomTable kHostBinom = make_binom();
 
 struct LinArgs {
   int n, d, ord, so;
@@ -253,7 +263,12 @@ __global__ void __launch_bounds__(kBlock) lin_find_kernel(LinArgs P, unsigned lo
   if (tid == 0) {
     const unsigned long long all = ok_s ? lin_count_below(L, P.stop) : 0;
     end_s = all < P.capacity ? all : P.capacity;
+    // A search cut short leaves the rest of the walk: the words so far are written.
+    const bool part = !kBorder && !write && !ok && P.start == 0 && P.prefix == 0 && 1ull << L.k < P.stop &&
+                      1ull << L.dim <= P.capacity;
+    if (part) end_s = 1ull << L.dim;
     if (blockIdx.x == 0) {
+      P.res->part = part ? L.k : 0;
       P.res->dim = L.dim;
       P.res->status = all > P.capacity ? GC_ECAPACITY : GC_OK;
       P.res->begin = begin_s;
@@ -275,7 +290,7 @@ __global__ void __launch_bounds__(kBlock) lin_find_kernel(LinArgs P, unsigned lo
 __global__ void __launch_bounds__(kEmitBlock) lin_emit_kernel(const LinResult *res, uint32_t *code,
                                                               unsigned long long *count) {
   __shared__ __align__(16) uint32_t tab[4][256];
-  if (!res->ok) return;
+  if (!res->ok && !res->part) return;
   lin_word_tables(tab, res->gen, res->dim);
   __syncthreads();
   lin_emit(tab, code, res->begin, res->end, (unsigned long long)blockIdx.x * kEmitBlock + threadIdx.x,
@@ -308,6 +323,33 @@ size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
 }  // namespace
 
+// The most label words of all arrays that a lex or Gray search can hold (none
+// without a search): once 2^r exceeds the number of words of weight <= d - 2,
+// some label is always free.
+unsigned long long lin_words_most(int n, int d) {
+  if (!lin_searched(n, d)) return 0;
+  unsigned long long low = 1;
+  for (int s = 1; s <= d - 2; ++s) low += kHostBinom.c[n - 1][s];
+  unsigned long long words = 2;
+  while (words * 32 < low) words *= 2;
+  return words * ((unsigned int)(d > 1 ? d - 1 : 0) | 1u);
+}
+
+// The least that one holds at its last level.  The code has at most 2^m words,
+// so at least K - 1 - m of the positions before the last are label bits.  (e even:
+// A(2 e, e) <= 4 e, Plotkin, and A(n, e) <= 2 A(n - 1, e); for 2 e > n A(n, e) <=
+// 2 floor(e / (2 e - n)); A(n, d) = A(n + 1, d + 1) for odd d.)
+unsigned long long lin_words_least(int n, int d, int so) {
+  if (!lin_searched(n, d)) return 0;
+  const int e = d + (d & 1), N = n + (d & 1);
+  unsigned long long most = greedy_code_capacity(n, d);
+  most = std::min<unsigned long long>(most, 2 * e > N ? 2ull * (e / (2 * e - N)) : 4ull * e << (N - 2 * e));
+  int m = 0;
+  while (most >> (m + 1)) ++m;
+  const int r = n - so - 1 - m;
+  return (r < 5 ? 1ull : 1ull << (r - 5)) * ((unsigned int)(d > 1 ? d - 1 : 0) | 1u);
+}
+
 bool linear_job(const Job &J) {
   return (J.ord == GC_LEX || J.ord == GC_GRAY || J.ord == GC_BORDER) && J.wclass == 0 && (J.d >= 2 || J.so) &&
          J.near_depth == 0 && J.target == 0 && J.mode == 0 && J.deep_tile == 0 && J.valu_screen == 0;
@@ -332,8 +374,8 @@ int run_linear(Job *J, hipStream_t stream, char *fixed, size_t fixed_bytes, floa
   const int dmax = std::min(J->d - 1, J->n);
   if (J->ord == GC_BORDER) {
     unsigned long long listed = 0;
-    for (int s = 1; s <= dmax; ++s) listed += make_binom().c[J->n][s];
-    if (listed > kMaxListed) return GC_OK;  // the screens build it
+    for (int s = 1; s <= dmax; ++s) listed += kHostBinom.c[J->n][s];
+    if (listed > max_listed(P.n)) return GC_OK;  // the screens build it
     P.listed = (unsigned int)listed;
     P.segs = (P.listed + kSegWords - 1) / kSegWords;
     off_offs = bytes;
@@ -342,15 +384,16 @@ int run_linear(Job *J, hipStream_t stream, char *fixed, size_t fixed_bytes, floa
     memcpy(P.basis, J->basis, sizeof(P.basis));
     invert_basis(J->basis, J->n, P.inv);
   } else {
-    // Global bitmaps for the labels that can occur (none without a search): once
-    // 2^r exceeds the number of words of weight <= d - 2, some label is always free.
-    unsigned long long low = 1;
-    for (int s = 1; s <= std::min(J->d - 2, J->n - 1); ++s) low += make_binom().c[J->n - 1][s];
-    unsigned long long words = 2;
-    while (words * 32 < low) words *= 2;
-    const unsigned long long need = words * ((unsigned int)(J->d > 1 ? J->d - 1 : 0) | 1u);
-    if (lin_searched(P.n, P.d) && need > (unsigned long long)kLinWords)
-      bytes += (size_t)std::min<unsigned long long>(need * 8, fixed ? fixed_bytes - bytes : kLinGlobalBytes);
+    const unsigned long long need = lin_words_most(P.n, P.d);
+    if (need > (unsigned long long)kLinWords) {
+      // A search that cannot end within the given memory is not begun (n = 26,
+      // d = 16 lex 6.8 ms by the screens, 9.9 with a search that fails before); one
+      // that turns out not to leaves the walk's last positions to the screens (n =
+      // 27, d = 14 lex 9.5 ms, all of it by the screens 13.4).
+      const unsigned long long room = fixed ? fixed_bytes - bytes : kLinGlobalBytes;
+      if (lin_words_least(P.n, P.d, P.so) * 8 > room) return GC_OK;
+      bytes += (size_t)std::min<unsigned long long>(need * 8, room);
+    }
   }
   char *ws = fixed;
   int slot = -1;
@@ -405,7 +448,13 @@ int run_linear(Job *J, hipStream_t stream, char *fixed, size_t fixed_bytes, floa
   if (e == hipSuccess && seen) res = *seen;
   if (slot >= 0 && es == hipSuccess) release_workspace(slot);
   if (e != hipSuccess) return fail(GC_EDEVICE, "linear code kernels failed: %s", hipGetErrorString(e));
-  if (!res.ok) return GC_OK;
+  if (!res.ok) {
+    if (res.part) {  // the screens go on from there
+      J->p_start = 1ull << res.part;
+      J->m_start = res.end;
+    }
+    return GC_OK;
+  }
   J->out_count = res.end;
   J->status = res.status;
   J->done = 1;

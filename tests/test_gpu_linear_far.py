@@ -66,3 +66,28 @@ def test_both_sides_of_two_words(n, d, o, so):
     assert np.array_equal(host(got), host(ref))
     words = gc.greedy_code(n, d, o)
     assert so or np.array_equal(words, host(ref))
+
+
+# Searches that cannot end in the memory they may have (16 MiB, or what the
+# no-allocation call holds) are left to the screens, and so are those that turn
+# out not to: n = 27, d = 14.
+@pytest.mark.parametrize("n,d,o", [(23, 14, "lex"), (24, 14, "gray"), (26, 15, "lex"), (26, 16, "gray"), (27, 14, "lex"),
+                                   (24, 13, "gray"), (28, 14, "gray")])
+def test_searches_that_do_not_fit(n, d, o):
+    import torch
+    print(f"[far] n={n} d={d} {o}", flush=True)
+    sys.stdout.flush()
+    ref = host(gc.device_code(n, d, o, **SCREENS)[0])
+    assert np.array_equal(host(gc.device_code(n, d, o)[0]), ref)
+    words = torch.zeros(gc.greedy_code_capacity(n, d), dtype=torch.int32, device="cuda")
+    count = torch.zeros(1, dtype=torch.int64, device="cuda")
+    gc.greedy_code_device_noalloc(n, d, o, words, count)
+    assert np.array_equal(host(words[: int(count.item())]), ref)
+
+
+def test_bases_whose_low_words_are_most_of_the_walk():
+    n = 20
+    basis = [1 << j ^ (1 << j - 1 if j else 0) for j in range(n)]
+    for d in (12, 13, 14, 15, 20, 21):
+        p = gc.problem(n, d, "border", basis=basis)
+        assert np.array_equal(host(gc.device_problem_code(p)[0]), host(gc.device_problem_code(p, **SCREENS)[0])), d
