@@ -152,8 +152,26 @@ void fill_job(Job *J, int n, int d, int ordering, uint32_t *words, uint64_t capa
 // Whether a job's code is linear and no tuning asks for the screens; its code
 // is then built from its generators.
 bool linear_job(const Job &J);
+// The same in a team of the persistent kernel (lex and Gray), where the search has
+// less memory: whether it may end there.
+bool team_linear(const Job &J);
+// Label words of all arrays that a lex or Gray search holds, at most, and at least
+// at its end.
+unsigned long long lin_words_most(int n, int d);
+unsigned long long lin_words_least(int n, int d, int so);
 // Whether a job's code may be built by cover marks (graded, n <= 24).
 bool cover_job(const Job &J);
+// Whether a prepared job (Job::linear and cover set) is "wide": the screens build
+// it, or may have to after a search, and its exhaustive work bound 2^n *
+// capacity(n, d) reaches this.  On a server it goes to the wide ring, which the
+// team spanning several XCDs serves first (on one XCD's team it would take up to
+// eight times longer and stretch the makespan); the other jobs go to the narrow
+// ring, served by the teams of one XCD and, when no wide job waits, by the wide
+// team too.  Linear and cover jobs use one XCD at most: while no wide job is open,
+// every XCD is a team of its own (a burst of 200 jobs, n = 10 .. 20: 3.0 ms; with
+// a wide team and two narrow ones 15.4 ms).
+constexpr double kWideWork = 274877906944.0;  // 2^38
+bool wide_job(const Job &J);
 // Builds a linear single code on `stream` and waits for it: outputs into *J and
 // *built, kernel_ms (may be null) the device time.  `fixed`: a workspace of
 // fixed_bytes to use instead of the pool (may be null).  *built stays false

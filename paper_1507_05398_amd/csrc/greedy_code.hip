@@ -120,8 +120,8 @@ struct TeamWs {
   uint32_t *deep_fail;       // kSMax / 32
   uint32_t *job;             // inputs of the job being built
   LinResult *lin;            // linear codes: the generators
-  unsigned long long *lin_bits;  // kLinTeamWords: label bitmaps past LDS
-  CoverWs *cover;            // graded codes of small distance
+  unsigned long long *lin_bits;  // kLinTeamWords: label bitmaps past LDS, over `cover`
+  CoverWs *cover;            // graded codes
 };
 
 constexpr size_t align256(size_t x) { return (x + 255) / 256 * 256; }
@@ -142,16 +142,15 @@ constexpr size_t kOffAdj = kOffDead + 2 * kDeadBytes;
 constexpr size_t kOffDword = kOffAdj + align256(kAdjWords * sizeof(unsigned long long));
 constexpr size_t kOffDidx = kOffDword + align256(kSMax * sizeof(uint32_t));
 constexpr size_t kOffDfail = kOffDidx + align256(kSMax * sizeof(uint32_t));
-// Linear codes: label bitmaps of a team's search, 16 KiB in LDS and then
-// 384 KiB of the workspace (enough for d <= 10 up to n = 26; a search that
-// needs more leaves its code to the screens).
+// Linear codes: label bitmaps of a team's search, 16 KiB in LDS and then 3.4 MiB
+// of the workspace, where a cover team's exchange is otherwise (enough for d <= 10
+// at every n; a search that needs more leaves its code to the screens).
 constexpr int kLinLdsWords = 2048;
-constexpr unsigned int kLinTeamWords = 49152;
 constexpr size_t kOffJob = kOffDfail + align256(kSMax / 32 * sizeof(uint32_t));
 constexpr size_t kOffLin = kOffJob + align256(kJobInputWords * sizeof(uint32_t));
-constexpr size_t kOffLinBits = kOffLin + align256(sizeof(LinResult));
-constexpr size_t kOffCover = kOffLinBits + align256(kLinTeamWords * sizeof(unsigned long long));
-constexpr size_t kTeamWsBytes = kOffCover + align256(sizeof(CoverWs));
+constexpr size_t kOffCover = kOffLin + align256(sizeof(LinResult));
+constexpr size_t kTeamWsBytes = kOffCover + align256(sizeof(CoverWs)) + (384u << 10);
+constexpr unsigned int kLinTeamWords = (kTeamWsBytes - kOffCover) / sizeof(unsigned long long);
 
 __host__ __device__ inline TeamWs team_ws(char *base) {
   TeamWs w;
@@ -165,7 +164,7 @@ __host__ __device__ inline TeamWs team_ws(char *base) {
   w.deep_fail = reinterpret_cast<uint32_t *>(base + kOffDfail);
   w.job = reinterpret_cast<uint32_t *>(base + kOffJob);
   w.lin = reinterpret_cast<LinResult *>(base + kOffLin);
-  w.lin_bits = reinterpret_cast<unsigned long long *>(base + kOffLinBits);
+  w.lin_bits = reinterpret_cast<unsigned long long *>(base + kOffCover);
   w.cover = reinterpret_cast<CoverWs *>(base + kOffCover);
   return w;
 }
@@ -2352,6 +2351,15 @@ bool cover_job(const Job &J) {
          J.near_depth == 0 && J.target == 0 && J.mode == 0 && J.deep_tile == 0 && J.valu_screen == 0;
 }
 
+bool team_linear(const Job &J) {
+  return linear_job(J) && J.ord != GC_BORDER && lin_words_least(J.n, J.d, 0) <= kLinTeamWords;
+}
+
+bool wide_job(const Job &J) {
+  const bool one_xcd = J.cover || (J.linear && lin_words_most(J.n, J.d) <= kLinTeamWords);
+  return !one_xcd && std::ldexp((double)greedy_code_capacity(J.n, J.d), J.n) >= kWideWork;
+}
+
 // A linear code, or one built by cover marks, uses one XCD whatever the team
 // has: from four such jobs up every XCD is a team of its own (30 jobs of
 // n <= 22, 4 and 8 teams: 1.37 to 1.98 and 0.95 to 1.97 ms over six job lists;
@@ -2361,7 +2369,7 @@ bool cover_job(const Job &J) {
 int default_teams(const Job *J, int njobs) {
   if (njobs < 4) return njobs >= 2 ? 2 : 1;
   for (int i = 0; i < njobs; ++i)
-    if (!J[i].linear && !J[i].cover) return 4;
+    if ((!J[i].linear && !J[i].cover) || wide_job(J[i])) return 4;
   return 8;
 }
 
@@ -2373,7 +2381,7 @@ int prepare_batch(const gc_job *jobs, int njobs, Job *J, int *order) {
     if (!g.d_words || ((uintptr_t)g.d_words & 15u) || g.capacity == 0)
       return fail(GC_EINVAL, "job %d: d_words must be a 16-byte aligned device array", i);
     fill_job(&J[i], g.n, g.d, g.ordering, g.d_words, g.capacity, g.d_count, nullptr);
-    J[i].linear = linear_job(J[i]);
+    J[i].linear = team_linear(J[i]);
     J[i].cover = cover_job(J[i]);
   }
   // Teams claim jobs in queue order; the queue holds the jobs longest first

@@ -34,15 +34,6 @@ namespace gcimpl {
 
 constexpr unsigned int kServerSlots = 1u << 16;   // jobs over the life of one server
 constexpr unsigned int kServerIdlePolls = 50000;  // about 0.1 s of empty queue before the kernel exits
-// A job that the screens build and whose exhaustive work bound 2^n *
-// capacity(n, d) reaches this is "wide": it goes to the wide ring, which the
-// team spanning several XCDs serves first (on one XCD's team it would take up
-// to eight times longer and stretch the makespan); the other jobs go to the
-// narrow ring, served by the teams of one XCD and, when no wide job waits, by
-// the wide team too.  Linear and cover jobs use one XCD at most: while no wide
-// job is open, every XCD is a team of its own (a burst of 200 jobs, n = 10 ..
-// 20: 3.0 ms; with a wide team and two narrow ones 15.4 ms).
-constexpr double kWideWork = 274877906944.0;  // 2^38
 // Narrow jobs may be admitted past a wide job that waits for arena space,
 // until that wide job has waited this long; then admission stops behind it
 // until it fits.
@@ -167,13 +158,12 @@ void fill_server_job(Job *J, int n, int d, int ord) {
     J->deep_tile = tu.deep_tile;
     J->valu_screen = tu.valu_screen;
   }
-  J->linear = linear_job(*J);
+  J->linear = team_linear(*J);
   J->cover = cover_job(*J);
 }
 
 bool is_wide(const gc_server *s, const Job &J) {
-  return wide_xcds(s->teams) > 0 && !J.linear && !J.cover &&
-         std::ldexp((double)greedy_code_capacity(J.n, J.d), J.n) >= kWideWork;
+  return wide_xcds(s->teams) > 0 && wide_job(J);
 }
 
 int launch_server_kernel(gc_server *s) {
