@@ -2136,26 +2136,56 @@ void release_workspace(int slot) {
   if (slot >= 0 && (size_t)slot < g_ws.size()) g_ws[slot].busy = false;
 }
 
-// Pinned block, join state and events of a workspace in use (kept with it; the
-// pool holds one per concurrent call).
+// Pinned block and events of a workspace in use (kept with it; the pool holds one
+// per concurrent call).  The caller holds the workspace, so they are made outside
+// the pool's lock.
 int workspace_host(int slot, WsHost *out) {
-  std::lock_guard<std::mutex> lk(g_ws_mu);
-  WsHost &h = g_ws[slot].host;
+  {
+    std::lock_guard<std::mutex> lk(g_ws_mu);
+    *out = g_ws[slot].host;
+  }
+  WsHost &h = *out;
+  if (h.ptr && h.begin && h.end) return GC_OK;
   hipError_t e = hipSuccess;
   if (!h.ptr) {
     e = hipHostMalloc((void **)&h.ptr, kWsHostBytes, hipHostMallocCoherent | hipHostMallocMapped);
-    if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&h.dev, h.ptr, 0);
-  }
-  if (e == hipSuccess && !h.ctl) {
-    // A copy, done when it returns: the first launch may be on any stream.
-    const CoverCtl zero{};
-    e = hipMalloc((void **)&h.ctl, sizeof(CoverCtl));
-    if (e == hipSuccess) e = hipMemcpy(h.ctl, &zero, sizeof(zero), hipMemcpyHostToDevice);
+    if (e == hipSuccess && (e = hipHostGetDevicePointer((void **)&h.dev, h.ptr, 0)) != hipSuccess) {
+      (void)hipHostFree(h.ptr);
+      h.ptr = nullptr;
+    }
   }
   if (e == hipSuccess && !h.begin) e = hipEventCreate(&h.begin);
   if (e == hipSuccess && !h.end) e = hipEventCreate(&h.end);
+  std::lock_guard<std::mutex> lk(g_ws_mu);
+  g_ws[slot].host = h;
   if (e != hipSuccess) return fail(GC_ENOMEM, "pinned result block: %s", hipGetErrorString(e));
-  *out = h;
+  return GC_OK;
+}
+
+__global__ void clear_ctl_kernel(CoverCtl *ctl) {
+  reinterpret_cast<unsigned int *>(ctl)[threadIdx.x] = 0;
+}
+
+// Join state of a cover launch of a workspace in use, kept with it as well.  The
+// first use clears it on the call's own stream: the call's launch follows there,
+// and the workspace is free again only once the stream is idle.
+int workspace_ctl(int slot, hipStream_t stream, CoverCtl **out) {
+  {
+    std::lock_guard<std::mutex> lk(g_ws_mu);
+    *out = g_ws[slot].host.ctl;
+  }
+  if (*out) return GC_OK;
+  CoverCtl *ctl = nullptr;
+  hipError_t e = hipMalloc((void **)&ctl, sizeof(CoverCtl));
+  if (e != hipSuccess) return fail(GC_ENOMEM, "join state: %s", hipGetErrorString(e));
+  hipLaunchKernelGGL(clear_ctl_kernel, dim3(1), dim3(sizeof(CoverCtl) / sizeof(unsigned int)), 0, stream, ctl);
+  e = hipGetLastError();
+  if (e != hipSuccess) {
+    (void)hipFree(ctl);
+    return fail(GC_EDEVICE, "join state: %s", hipGetErrorString(e));
+  }
+  std::lock_guard<std::mutex> lk(g_ws_mu);
+  g_ws[slot].host.ctl = *out = ctl;
   return GC_OK;
 }
 
@@ -2262,6 +2292,7 @@ int run_cover(Job *J, hipStream_t stream, char *fixed, CoverCtl *fixed_ctl, floa
     rc = acquire_workspace(lay.bytes, &ws, &slot);
     if (rc) return rc;
     rc = workspace_host(slot, &host);
+    if (rc == GC_OK) rc = workspace_ctl(slot, stream, &host.ctl);
     if (rc) {
       release_workspace(slot);
       return rc;
