@@ -455,9 +455,14 @@ unsigned long long positions(int a, int b) {
 
 // The packing kernel of (n, w, d), or null where the t-subsets outgrow LDS, a
 // word has too many of them, or every two words clash or none do (t outside 1
-// .. w - 1): the screens.  Inside these limits it is always the faster one: a
-// position costs a few ns of one compute unit against 20 ns of grid barriers.
+// .. w - 1): the screens.  Inside these limits it is the faster one: a position
+// costs 1 to 8 ns of one compute unit against some 145 of grid barriers.  At their
+// edges, by the screens and here, ms: n = 38 w = 8 d = 8 7342 and 209, n = 48 w = 7
+// d = 8 10845 and 219, n = 29 w = 8 d = 6 615 and 14.8, n = 25 w = 8 d = 4 217 and
+// 4.9, n = 38 w = 7 d = 6 1869 and 30, n = 64 w = 5 d = 8 1112 and 10.3, n = 61 w =
+// 5 d = 4 1404 and 14.6.
 PackKernel pack_rule(int n, int w, int d, unsigned int *subsets) {
+  d = d < 65 ? d : 65;  // no two words are further apart than 64 (and d + 1 stays an int)
   const int out = (d + 1) / 2 - 1, t = w - out;
   if (w > kPackMaxW || out < 1 || out > kPackMaxOut || t < 1) return nullptr;
   const unsigned long long all = positions(n, t);

@@ -65,6 +65,19 @@ def test_single_codes(cuda, d):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("d", [17, 64, 65, 66, 2**26 + 1, TOP - 1, TOP])
+def test_constant_weight_words_of_64_bits(cuda, d):
+    import torch
+    print(f"[distance] cw64 d={d}", flush=True)
+    sys.stdout.flush()
+    for n, w in ((20, 8), (64, 2)):
+        words = torch.zeros(8, dtype=torch.int64, device="cuda")
+        count = torch.zeros(1, dtype=torch.int64, device="cuda")
+        gc.greedy_code_cw64(n, w, d, words, count)
+        assert words.tolist() == [2**w - 1] + 7 * [0] and int(count.item()) == 1
+
+
+@pytest.mark.gpu
 def test_batched_and_served(cuda):
     jobs = [(n, d, o) for d in DISTANCES for o in ORDERINGS for n in (1, N)]
     print(f"[distance] {len(jobs)} jobs", flush=True)
