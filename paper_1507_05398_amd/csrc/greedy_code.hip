@@ -63,6 +63,7 @@
 #include <string>
 #include <vector>
 
+#include "binomials.h"
 #include "cover.h"
 #include "gc_internal.h"
 #include "greedy_code.h"
@@ -533,16 +534,6 @@ __device__ __forceinline__ uint32_t position_word(const Tables &T, const Walk &K
   return __builtin_bitreverse32(~y & mask) >> (32 - n);
 }
 
-struct BinomTable {
-  uint32_t c[33 * 33];
-};
-constexpr BinomTable make_binom() {
-  BinomTable t{};
-  for (int a = 0; a <= 32; ++a)
-    for (int b = 0; b <= a; ++b)
-      t.c[33 * a + b] = b == 0 || b == a ? 1u : t.c[33 * (a - 1) + b - 1] + t.c[33 * (a - 1) + b];
-  return t;
-}
 __constant__ BinomTable kBinomials = make_binom();
 
 // Fill the tables of a walk (whole workgroup): binomials and the offsets of
@@ -562,7 +553,7 @@ __device__ void init_tables(Tables &T, const Walk &K, unsigned long long classes
     __syncthreads();
     return;
   }
-  for (int i = threadIdx.x; i < 33 * 33; i += blockDim.x) T.binom[i / 33][i % 33] = kBinomials.c[i];
+  for (int i = threadIdx.x; i < 33 * 33; i += blockDim.x) T.binom[i / 33][i % 33] = kBinomials.c[i / 33][i % 33];
   __syncthreads();
   if (threadIdx.x == 0) {
     unsigned long long acc = 0;

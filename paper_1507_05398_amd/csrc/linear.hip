@@ -19,6 +19,7 @@
 
 #include <algorithm>
 
+#include "binomials.h"
 #include "gc_internal.h"
 #include "greedy_code.h"
 #include "linear.h"
@@ -55,15 +56,6 @@ constexpr unsigned int kMaxHeld = kHeld * kBlock;
 constexpr int kScanBlock = 256;
 constexpr int kEmitBlock = 256;
 
-struct BinomTable {
-  uint32_t c[33][33];
-};
-constexpr BinomTable make_binom() {
-  BinomTable t{};
-  for (int a = 0; a <= 32; ++a)
-    for (int b = 0; b <= a; ++b) t.c[a][b] = b == 0 || b == a ? 1u : t.c[a - 1][b - 1] + t.c[a - 1][b];
-  return t;
-}
 __constant__ BinomTable kBinom = make_binom();
 constexpr BinomTable kHostBinom = make_binom();
 
