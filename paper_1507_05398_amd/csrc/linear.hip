@@ -61,6 +61,7 @@ constexpr BinomTable kHostBinom = make_binom();
 
 struct LinArgs {
   int n, d, ord, so;
+  int levels;             // position bits that occur
   unsigned long long start, stop, prefix, capacity;
   uint32_t *code;
   LinResult *res;
@@ -165,7 +166,7 @@ __global__ void __launch_bounds__(kScanBlock) lin_list_kernel(LinArgs P) {
 // label of a position).  The words' positions are in registers, or listed by
 // that bit in global memory.
 __device__ __forceinline__ bool border_search(LinLds<kLinWords> &L, ScanLds &S, uint32_t (*lam)[256], const LinArgs &P) {
-  const int tid = threadIdx.x, n = P.n;
+  const int tid = threadIdx.x;
   uint32_t held[kHeld];
   const bool in_registers = P.listed <= kMaxHeld;
   const unsigned int per = (P.listed + kBlock - 1) / kBlock;
@@ -183,7 +184,7 @@ __device__ __forceinline__ bool border_search(LinLds<kLinWords> &L, ScanLds &S, 
   if (tid < 2) L.best[tid] = ~0u;
   int r = 0, dim = 0, k = 0;
   uint32_t *bits32 = reinterpret_cast<uint32_t *>(L.bits);
-  for (; k < n; ++k) {
+  for (; k < P.levels; ++k) {
     const unsigned int nw = r < 6 ? 1u : 1u << (r - 6);
     if (nw > (unsigned int)kLinWords) break;
     for (unsigned int w = tid; w < nw; w += kBlock) L.bits[w] = 0;
@@ -217,7 +218,7 @@ __device__ __forceinline__ bool border_search(LinLds<kLinWords> &L, ScanLds &S, 
   if (tid == 0) L.dim = dim;
   lin_generators(L, dim);
   __syncthreads();
-  return k >= n;
+  return k >= P.levels;
 }
 
 // The generators, the range of code words to write, and (a resumed
@@ -358,6 +359,11 @@ int run_linear(Job *J, hipStream_t stream, char *fixed, size_t fixed_bytes, floa
   P.so = J->so;
   P.start = J->p_start;
   P.stop = J->p_stop ? J->p_stop : 1ull << K;
+  // Positions below 2^k are decided by k levels; lex and Gray: they are the walk of
+  // the first coordinates.
+  P.levels = 0;
+  while (P.levels < K && 1ull << P.levels < P.stop) ++P.levels;
+  if (J->ord != GC_BORDER) P.n = std::max(1, P.levels + J->so);
   P.prefix = J->m_start;
   P.capacity = J->capacity;
   P.code = J->code;

@@ -1,0 +1,60 @@
+"""Parts of walks: short ones from the start, where a linear search has few levels,
+and ranges after given words, where a rule on their number and the range's length
+chooses the builder.  Against the screens, which a tuning asks for."""
+import sys
+
+import numpy as np
+import pytest
+
+import paper_1507_05398_amd as gc
+
+pytestmark = pytest.mark.gpu
+SCREENS = dict(target_survivors=1000)
+
+
+@pytest.fixture(scope="module", autouse=True)
+def cuda():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a ROCm device"
+    gc.load()
+
+
+def log(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+def run(p, given, cap, **tuning):
+    """The code, and whether the buffer past it is as it was."""
+    import torch
+    words = torch.full((cap,), -1, dtype=torch.int32, device="cuda")
+    words[: len(given)] = torch.from_numpy(np.asarray(given, np.uint32).view(np.int32).copy())
+    count = torch.zeros(1, dtype=torch.int64, device="cuda")
+    gc.greedy_code_problem_device(p, words, count, **tuning)
+    got, m = words.cpu().numpy().view(np.uint32), int(count.item())
+    assert (got[m:] == 0xFFFFFFFF).all()
+    return got[:m]
+
+
+BASIS = [1 << j ^ (1 << j - 1 if j % 3 else 0) for j in range(20)]
+STOPS = [1, 2, 3, 4, 5, 63, 64, 65, 1000, 4096, 4097, 65535, 65536, 65537, 200001]
+
+
+@pytest.mark.parametrize("so", [False, True])
+@pytest.mark.parametrize("o", ["lex", "gray", "border"])
+@pytest.mark.parametrize("d", [2, 3, 6, 8, 13, 14])
+def test_short_walks(d, o, so):
+    if so and o == "border":
+        return  # not a problem
+    kw = dict(self_orthogonal=so, basis=BASIS if o == "border" else None)
+    log(f"[parts] n=20 d={d} {o} {so}")
+    for stop in STOPS:
+        p = gc.problem(20, d, o, stop=stop, **kw)
+        cap = stop + 4
+        got = run(p, [], cap)
+        assert np.array_equal(got, run(p, [], cap, **SCREENS)), stop
+        # and on from there
+        for end in (stop + 1, stop + 100, 262144):
+            p = gc.problem(20, d, o, start=stop, stop=end, prefix=len(got), **kw)
+            cap = len(got) + end - stop + 4
+            assert np.array_equal(run(p, got, cap), run(p, got, cap, **SCREENS)), (stop, end)
