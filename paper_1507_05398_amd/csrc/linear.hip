@@ -53,6 +53,10 @@ constexpr unsigned long long max_listed(int n) {
 // words there (n = 23, d = 5, 10902 words: 64 us a call, 77 with a list).
 constexpr int kHeld = 16;
 constexpr unsigned int kMaxHeld = kHeld * kBlock;
+// Given words that the searching workgroup compares with the code itself (it does
+// 1024 in 0.3 us; n = 26, d = 2 Gray, 29 million words 8565 us a call, with the
+// whole GPU 62).
+constexpr unsigned long long kCheckAlone = 1u << 14;
 constexpr int kScanBlock = 256;
 constexpr int kEmitBlock = 256;
 
@@ -247,7 +251,7 @@ __global__ void __launch_bounds__(kBlock) lin_find_kernel(LinArgs P, unsigned lo
     lin_word_tables(tab, L.gen, L.dim);
     __syncthreads();
   }
-  if (ok_s && P.prefix) {
+  if (ok_s && P.prefix && P.prefix <= kCheckAlone) {
     bool same = true;
     for (unsigned long long i = tid; i < P.prefix; i += kBlock) same &= P.code[i] == lin_word(tab, i);
     if (!__syncthreads_and(same)) ok_s = 0;
@@ -278,6 +282,29 @@ __global__ void __launch_bounds__(kBlock) lin_find_kernel(LinArgs P, unsigned lo
   if (ok_s)
     lin_emit(tab, P.code, begin_s, end_s, (unsigned long long)blockIdx.x * kBlock + tid,
              (unsigned long long)gridDim.x * kBlock);
+}
+
+// Takes `ok` back where the given words are not the code's beginning.
+__global__ void __launch_bounds__(kEmitBlock) lin_check_kernel(LinResult *res, const uint32_t *code,
+                                                               unsigned long long prefix) {
+  __shared__ __align__(16) uint32_t tab[4][256];
+  if (!res->ok) return;
+  lin_word_tables(tab, res->gen, res->dim);
+  __syncthreads();
+  bool same = true;
+  const unsigned long long stride = (unsigned long long)gridDim.x * kEmitBlock;
+  for (unsigned long long g = (unsigned long long)blockIdx.x * kEmitBlock + threadIdx.x; 4 * g < prefix; g += stride) {
+    const unsigned long long m = 4 * g;
+    if (m + 4 <= prefix) {
+      const uint32_t high = tab[1][(m >> 8) & 255] ^ tab[2][(m >> 16) & 255] ^ tab[3][(m >> 24) & 255];
+      const uint4 low = *reinterpret_cast<const uint4 *>(&tab[0][m & 255]);
+      const uint4 v = *reinterpret_cast<const uint4 *>(code + m);
+      same &= ((v.x ^ low.x ^ high) | (v.y ^ low.y ^ high) | (v.z ^ low.z ^ high) | (v.w ^ low.w ^ high)) == 0;
+    } else {
+      for (unsigned long long i = m; i < prefix; ++i) same &= code[i] == lin_word(tab, i);
+    }
+  }
+  if (!same) res->ok = 0;
 }
 
 __global__ void __launch_bounds__(kEmitBlock) lin_emit_kernel(const LinResult *res, uint32_t *code,
@@ -429,6 +456,11 @@ int run_linear(Job *J, hipStream_t stream, char *fixed, size_t fixed_bytes, floa
     const dim3 wgs(one_launch ? grid : 1);
     if (J->ord == GC_BORDER) hipLaunchKernelGGL(lin_find_kernel<true>, wgs, dim3(kBlock), 0, stream, P, J->count, one_launch);
     else hipLaunchKernelGGL(lin_find_kernel<false>, wgs, dim3(kBlock), 0, stream, P, J->count, one_launch);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess && P.prefix > kCheckAlone) {
+    const unsigned int checkers = (unsigned int)std::min<unsigned long long>(1024, P.prefix / (4 * kEmitBlock) + 1);
+    hipLaunchKernelGGL(lin_check_kernel, dim3(checkers), dim3(kEmitBlock), 0, stream, P.res, J->code, P.prefix);
     e = hipGetLastError();
   }
   if (e == hipSuccess && !one_launch) {

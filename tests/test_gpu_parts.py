@@ -58,3 +58,19 @@ def test_short_walks(d, o, so):
             p = gc.problem(20, d, o, start=stop, stop=end, prefix=len(got), **kw)
             cap = len(got) + end - stop + 4
             assert np.array_equal(run(p, got, cap), run(p, got, cap, **SCREENS)), (stop, end)
+
+
+@pytest.mark.parametrize("o", ["lex", "gray"])
+@pytest.mark.parametrize("n,d", [(17, 2), (20, 3)])
+def test_many_given_words(n, d, o):
+    cut = (1 << n) * 3 // 4 + 7
+    head = run(gc.problem(n, d, o, stop=cut), [], cut)
+    assert len(head) > 20000
+    for wrong in (None, 0, 1, len(head) // 2, 16384, len(head) - 1):
+        given = head.copy()
+        if wrong is not None:
+            given[wrong] ^= 1 << n - 1
+        log(f"[parts] n={n} d={d} {o} {len(given)} words, {wrong} wrong")
+        p = gc.problem(n, d, o, start=cut, prefix=len(given))
+        cap = len(given) + (1 << n) - cut + 4
+        assert np.array_equal(run(p, given, cap), run(p, given, cap, **SCREENS)), wrong
