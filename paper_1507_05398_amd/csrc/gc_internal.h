@@ -172,6 +172,8 @@ bool cover_job(const Job &J);
 // a wide team and two narrow ones 15.4 ms).
 constexpr double kWideWork = 274877906944.0;  // 2^38
 bool wide_job(const Job &J);
+// About how long a linear job with given words takes from its generators, us.
+double linear_given_us(const Job &J);
 // Builds a linear single code on `stream` and waits for it: outputs into *J and
 // *built, kernel_ms (may be null) the device time.  `fixed`: a workspace of
 // fixed_bytes to use instead of the pool (may be null).  *built stays false

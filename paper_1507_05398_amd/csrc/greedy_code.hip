@@ -2382,6 +2382,36 @@ bool wide_job(const Job &J) {
   return !one_xcd && std::ldexp((double)greedy_code_capacity(J.n, J.d), J.n) >= kWideWork;
 }
 
+// About how long the screens take over a job's positions at least, us: some windows
+// that grow to 2^18 positions, then those; less than half of what an even density of
+// accepted words costs (graded codes accept in bursts).
+static double screens_us(const Job &J) {
+  const double len = (double)(J.p_stop - J.p_start), b = std::log2(std::max(len, 1.0));
+  const double density = J.p_start ? std::min(1.0, (double)J.m_start / (double)J.p_start) : 0.0;
+  return 90.0 + 4.0 * std::min(b, 10.0) + 27.0 * std::min(std::max(b - 10.0, 0.0), 8.0) +
+         31.0 * std::max(len / 262144.0 - 1.0, 0.0) + 0.05 * density * len;
+}
+
+// About how long the marks of a cover job's given words take, with its start, us.
+static double cover_given_us(const Job &J) {
+  const unsigned int team = cover_team_size(J.n, J.d, J.so != 0, kCovTeam);
+  const bool windows = cover_by_windows(J.n, J.d, J.so != 0);
+  const double words = J.n > 6 ? (double)(1u << (J.n - 6)) / team : 1.0;
+  double near_words = 0;
+  for (int j = 0; j < J.d && j <= J.n - 6; ++j) near_words += (double)binom_host(J.n - 6, j);
+  const double mark = near_words / (7200.0 * team) + (windows ? 0.02 : 0.0);
+  return 40.0 + words * (windows ? 0.011 : 0.021) + (double)J.m_start * std::max(mark, 0.45e-3);
+}
+
+// A part of a walk after given words: the other builders pay for all of the code's
+// beginning (its marks, or a search), the screens for the positions.  Both are
+// estimated; without given words the others are always the faster ones.  (n = 24 d
+// = 4 grevlex after 234294 words, by the screens and by marks: 1 position 106 and
+// 1217 us, 2^18 577 and 1218, to the end 8.3 and 2.0 ms; n = 24 d = 8 grlex after
+// 3336, to the end 0.68 and 1.16 ms; n = 24 d = 13 lex after 4 words, 1 position 90
+// and 773 us, to the end 570 and 772.)
+static bool part_screened(const Job &J, double other_us) { return J.m_start && other_us > screens_us(J); }
+
 // A linear code, or one built by cover marks, uses one XCD whatever the team
 // has: from four such jobs up every XCD is a team of its own (30 jobs of
 // n <= 22, 4 and 8 teams: 1.37 to 1.98 and 0.95 to 1.97 ms over six job lists;
@@ -2651,7 +2681,9 @@ int greedy_code_problem_device(const gc_problem *p, uint32_t *d_words, uint64_t 
   Job J;
   fill_job_problem(&J, *p, d_words, capacity, d_count, tuning);
   float ms = 0.f;
-  if (linear_job(J) && !(tuning && tuning->grid_blocks)) {
+  // (A linear code has words before any position but the first.)
+  if (linear_job(J) && !(tuning && tuning->grid_blocks) && (J.p_start > 0) == (J.m_start > 0) &&
+      !part_screened(J, linear_given_us(J))) {
     bool built = false;
     rc = run_linear(&J, stream, nullptr, 0, stats ? &ms : nullptr, &built);
     if (rc) return rc;
@@ -2660,7 +2692,7 @@ int greedy_code_problem_device(const gc_problem *p, uint32_t *d_words, uint64_t 
       return job_result(J, capacity);
     }
   }
-  J.cover = cover_job(J) && !(tuning && tuning->grid_blocks);
+  J.cover = cover_job(J) && !(tuning && tuning->grid_blocks) && !part_screened(J, cover_given_us(J));
   if (J.cover) {
     bool built = false;
     rc = run_cover(&J, stream, nullptr, nullptr, stats ? &ms : nullptr, &built);

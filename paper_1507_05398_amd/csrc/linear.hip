@@ -18,6 +18,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "binomials.h"
 #include "gc_internal.h"
@@ -368,6 +369,20 @@ unsigned long long lin_words_least(int n, int d, int so) {
   while (most >> (m + 1)) ++m;
   const int r = n - so - 1 - m;
   return (r < 5 ? 1ull : 1ull << (r - 5)) * ((unsigned int)(d > 1 ? d - 1 : 0) | 1u);
+}
+
+double linear_given_us(const Job &J) {
+  // A search past the first labels: some ns a word of its bitmaps, whose number lies
+  // between the bounds; self-orthogonal ones test their labels one by one.
+  const double words = J.ord == GC_BORDER ? 0.0
+                                          : std::sqrt((double)lin_words_least(J.n, J.d, J.so) * (double)lin_words_most(J.n, J.d));
+  double us = 50.0 + 1e-3 * words + (J.so ? 0.4 * J.n * J.n : 0.0) + 1e-6 * (double)J.m_start;
+  if (J.ord == GC_BORDER) {
+    double listed = 0;
+    for (int s = 1; s < J.d && s <= J.n; ++s) listed += kHostBinom.c[J.n][s];
+    us += 100.0 + 0.5e-3 * listed;
+  }
+  return us;
 }
 
 bool linear_job(const Job &J) {

@@ -74,3 +74,26 @@ def test_many_given_words(n, d, o):
         p = gc.problem(n, d, o, start=cut, prefix=len(given))
         cap = len(given) + (1 << n) - cut + 4
         assert np.array_equal(run(p, given, cap), run(p, given, cap, **SCREENS)), wrong
+
+
+# Given words without positions before them, and positions without words.
+@pytest.mark.parametrize("o", ["lex", "gray", "grlex", "grevlex"])
+def test_words_and_positions_that_do_not_belong_together(o):
+    for p, given in ((gc.problem(12, 3, o, start=100), []), (gc.problem(12, 3, o, prefix=2), [5, 77]),
+                     (gc.problem(12, 3, o, start=1, prefix=3), [0, 0, 9])):
+        assert np.array_equal(run(p, given, 4100), run(p, given, 4100, **SCREENS))
+
+
+@pytest.mark.parametrize("kw", [{}, dict(weight=10), dict(self_orthogonal=True)])
+@pytest.mark.parametrize("n,d,o", [(20, 2, "grlex"), (21, 3, "grevlex"), (21, 4, "grlex"), (22, 6, "grlex"), (22, 8, "grevlex")])
+def test_graded_ranges_after_given_words(n, d, o, kw):
+    total = gc.problem_positions(gc.problem(n, d, o, **kw))
+    for num in (1, 4, 7):
+        cut = total * num // 8
+        head = run(gc.problem(n, d, o, stop=cut, **kw), [], cut + 4)
+        log(f"[parts] n={n} d={d} {o} {kw} {len(head)} words")
+        for length in (1, 1000, 1 << 14, 1 << 18, total):
+            stop = min(total, cut + length)
+            p = gc.problem(n, d, o, start=cut, stop=stop, prefix=len(head), **kw)
+            cap = len(head) + stop - cut + 4
+            assert np.array_equal(run(p, head, cap), run(p, head, cap, **SCREENS)), (cut, length)
