@@ -14,14 +14,15 @@ instances).  ``--workload sweep`` runs the whole sweep (four orderings x n in
 The headline value is algorithmic distance checks per second: the sum over
 instances of W_ee (checks done by a sequential newest-first scan with early
 exit, counted by the CPU oracle and stored in tests/golden/expected_codes.txt)
-divided by the wall time of the step.
+divided by the wall time of the step.  (An equivalent, where codes are built
+without distance checks; executed_checks_per_step says how many ran.)
 
 Also measured (one JSON line in all):
-  * roofline of the single-code kernels over every timed launch of the
-    workload (HIP events on the launch stream, recorded by the library): the
-    distance checks that the screens executed against the int8 matrix peak,
-    or, where no code of the workload takes a screen, the bytes of the code
-    words against the HBM peak;
+  * roofline of the single-code kernels (HIP events on the launch stream,
+    recorded by the library): the distance checks that the screens executed
+    against the int8 matrix peak, over the launches that executed any, or,
+    where no code of the workload takes a screen, the bytes of the code words
+    against the HBM peak, over every timed launch;
   * batched: the 256-instance workload (seed 1507) as one persistent launch,
     as a captured graph and as a loop of plain per-instance calls on the same
     buffers, with the built-in defaults and then autotuned;
@@ -205,36 +206,41 @@ def oracle_times(expected, workers):
 
 
 class LaunchLog:
-    """Kernel time, algorithmic and executed checks and words of every timed
-    single-code launch, and each instance's launch times."""
+    """Kernel time, algorithmic and executed checks and words of the timed
+    single-code launches, those that executed checks (the screens) apart from
+    the others, and each instance's launch times."""
 
     def __init__(self):
-        self.ms, self.w_ee, self.executed, self.launches = 0.0, 0, 0, 0
+        self.w_ee, self.executed = 0, 0
+        self.ms = {True: 0.0, False: 0.0}      # by whether checks were executed
+        self.launches = {True: 0, False: 0}
         self.ops = 0    # int8 operations: 2n per executed check
-        self.bytes = 0  # of the codes' words
+        self.bytes = 0  # of the words of codes built without checks
         self.per_key = {}
 
     def add(self, key, stats, w_ee):
-        self.ms += stats["kernel_ms"]
         self.w_ee += w_ee
         executed = stats["checks_near"] + stats["checks_deep"] + stats["checks_pairs"]
+        screened = executed > 0
+        self.ms[screened] += stats["kernel_ms"]
+        self.launches[screened] += 1
         self.ops += 2 * int(key.split("_")[0]) * executed
-        self.bytes += 4 * stats["count"]
         self.executed += executed
-        self.launches += 1
+        if not screened:
+            self.bytes += 4 * stats["count"]
         self.per_key.setdefault(key, []).append(stats["kernel_ms"])
 
     def median_ms(self):
         return {k: round(sorted(v)[len(v) // 2], 3) for k, v in self.per_key.items()}
 
     def gchecks(self):
-        return self.executed / (self.ms / 1e3) / 1e9 if self.ms else 0.0
+        return self.executed / (self.ms[True] / 1e3) / 1e9 if self.ms[True] else 0.0
 
     def gbytes(self):
-        return self.bytes / (self.ms / 1e3) / 1e9 if self.ms else 0.0
+        return self.bytes / (self.ms[False] / 1e3) / 1e9 if self.ms[False] else 0.0
 
     def tops(self):
-        return self.ops / (self.ms / 1e3) / 1e12 if self.ms else 0.0
+        return self.ops / (self.ms[True] / 1e3) / 1e12 if self.ms[True] else 0.0
 
 
 def bench_sweep(gc, torch, insts, expected, steps, warmup):
@@ -587,12 +593,14 @@ def main():
     if not args.no_batched:
         batched = bench_batched(gc, torch, max(args.steps, 3), args.warmup)
         progress("batched done")
+    screened = sweep.executed > 0
     timed = {
-        "launches": sweep.launches,
-        "avg_launch_ms": round(sweep.ms / max(sweep.launches, 1), 4),
-        "covers": "every timed launch of the workload (HIP events around each launch on its stream)",
+        "launches": sweep.launches[screened],
+        "avg_launch_ms": round(sweep.ms[screened] / max(sweep.launches[screened], 1), 4),
+        "covers": "every timed launch of the workload that executed checks" if screened else
+                  "every timed launch of the workload (HIP events around each launch on its stream)",
     }
-    if sweep.executed:
+    if screened:
         line["roofline"] = {
             "bound": "mfma",
             "kernel": "greedy_code_kernel",
