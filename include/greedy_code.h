@@ -86,8 +86,9 @@ typedef struct gc_stats {
  * ones included, a weight not) are linear; with every field zero they are
  * built from their generators.  GC_GRLEX and GC_GREVLEX codes (a weight and
  * self-orthogonal ones too) of n <= 24 are built by marking the ball of each
- * accepted word in a bitmap of the space.  Any field set asks
- * for the windowed screens, which build the same code. */
+ * accepted word in a bitmap of the space.  Where neither pays (a search that
+ * outgrows its memory, a few positions after many given words) and with any
+ * field set the windowed screens build the same code. */
 typedef struct gc_tuning {
     uint64_t near_depth;    /* newest code words screened before the in-window
                                resolve; 0 = default, UINT64_MAX = whole code */
@@ -316,8 +317,8 @@ int greedy_code_batch_tune(gc_job *jobs, int njobs, void *hip_stream, int *best_
  * go to a queue in pinned host memory that the running kernel's teams pull
  * from, so a job arriving while others build starts as soon as a team frees
  * up.  With teams 2 or 4, every XCD is a team of its own while no "wide" job
- * is open: one that the windowed screens build (see gc_tuning) and whose
- * exhaustive work bound 2^n * greedy_code_capacity(n, d) is at least 2^38.
+ * is open: one that the windowed screens build, or may have to (see
+ * gc_tuning), and whose exhaustive work bound 2^n * greedy_code_capacity(n, d) is at least 2^38.
  * Wide jobs go to a wide queue; while one is open, one team spanning 8 - teams
  * of the eight XCDs serves it, and the other jobs, in a narrow queue, are
  * served by `teams` teams of one XCD each and by the wide team whenever no
