@@ -474,8 +474,8 @@ int run_linear(Job *J, hipStream_t stream, char *fixed, size_t fixed_bytes, floa
     e = hipGetLastError();
   }
   if (e == hipSuccess && P.prefix > kCheckAlone) {
-    const unsigned int checkers = (unsigned int)std::min<unsigned long long>(1024, P.prefix / (4 * kEmitBlock) + 1);
-    hipLaunchKernelGGL(lin_check_kernel, dim3(checkers), dim3(kEmitBlock), 0, stream, P.res, J->code, P.prefix);
+    const unsigned int groups = (unsigned int)std::min<unsigned long long>(1024, P.prefix / (4 * kEmitBlock) + 1);
+    hipLaunchKernelGGL(lin_check_kernel, dim3(groups), dim3(kEmitBlock), 0, stream, P.res, J->code, P.prefix);
     e = hipGetLastError();
   }
   if (e == hipSuccess && !one_launch) {
